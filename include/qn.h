@@ -48,7 +48,9 @@
  *   fixed beta; every other beta_mode is rejected for it.
  *
  * Precision (transforms only; residual, norms, shift rule and the update are
- * always FP64): QN_PREC_FP64 (FP64 MFMA), QN_PREC_FP32 (FP32 MFMA),
+ * always FP64): QN_PREC_FP64 (FP64 MFMA; finite-difference axes whose doubled
+ * interval count factors into short lengths run as factored FP64 transforms
+ * instead of dense products), QN_PREC_FP32 (FP32 MFMA),
  * QN_PREC_BF16X3 (each operand split into bf16 hi + lo parts, three bf16 MFMA
  * products hi*hi + hi*lo + lo*hi accumulated in FP32), QN_PREC_BF16X6 (three
  * bf16 parts, the six part products of combined order below 3; FP32-level
@@ -357,7 +359,9 @@ qn_status qn_probe_mfma(int32_t precision, void* d_sink, size_t bytes, void* str
  * split-bf16 launches take the largest side that divides each extent.  qn_autotune times every admissible shape
  * of every launch on the bound workspace (its transform tensors are
  * overwritten; the x inverse is timed with a plain store) and keeps the
- * fastest for all later calls.  Results do not depend on the tile shapes
+ * fastest for all later calls.  Launches whose axis runs factored (FP64, see
+ * Precision) stay in the list for qn_tile_info and qn_set_tile but are not
+ * issued, so they are not timed.  Results do not depend on the tile shapes
  * (bitwise).  Synchronous.  The split-bf16 precisions use dense
  * (unfolded) products; their tiles are tuned the same way. */
 qn_status qn_autotune(qn_ctx ctx);

@@ -119,6 +119,12 @@ struct qn_ctx_s {
   int hp[3] = {0, 0, 0};
   std::vector<double> hSf[3];
   size_t off_Sf[3][2] = {};
+  // axes whose transforms run factored (qn_fast.hip): stage lengths, tables
+  bool fast[3] = {false, false, false};
+  bool any_fast = false, all_fast = false;
+  FastAxis fx[3] = {};
+  std::vector<double> htw[3], hlx[3];
+  size_t off_tw[3] = {0, 0, 0}, off_lx[3] = {0, 0, 0};
   // workspace layout (byte offsets)
   size_t off_S[3] = {0, 0, 0}, off_Slo[3] = {0, 0, 0}, off_Slo2[3] = {0, 0, 0}, off_lam[3] = {0, 0, 0};
   size_t off_W1 = 0, off_W2 = 0, off_part = 0, off_scal = 0, off_coef = 0, off_cscale = 0,
@@ -286,7 +292,7 @@ ResidualArgs residual_args(qn_ctx c, const double* U, const double* F, double* R
   const int* ext = R_caller ? c->n : c->p;
   a.R = R_caller ? (void*)R_caller : (void*)(c->ws + c->off_W1);
   // split-bf16 two-part transforms keep their tensors as bf16 part planes
-  a.out_prec = (R_caller || c->prec == QN_PREC_FP64) ? 0 : c->prec == QN_PREC_BF16X3 ? 2 : 1;
+  a.out_prec = R_caller ? 0 : transform_storage(c->prec);
   a.r_cstride = (long long)ext[2] * ext[1] * ext[0];
   a.r_zstride = ext[1] * ext[0];
   a.r_ystride = ext[0];
@@ -309,6 +315,11 @@ ResidualArgs residual_args(qn_ctx c, const double* U, const double* F, double* R
   a.bc = c->bc;
   a.partials = c->at<double>(c->off_part);
   a.xfold = (!R_caller && c->xfold) ? c->hp[0] : 0;  // the x product reads it folded
+  if (!R_caller && c->all_fast) {  // the padding is never read: write interior points only
+    a.ox = c->n[0];
+    a.oy = c->n[1];
+    a.oz = c->n[2];
+  }
   a.rz = c->dim == 3 ? residual_slab_depth(a.ox, a.oy, a.oz, residual_threads(c->nl, c->bc))
                       : residual_planar_rows(a.ox, a.oy);
   a.sem_k = c->sem_k;
@@ -558,6 +569,29 @@ FoldTile step_tile(qn_ctx c, const FoldStep& f, int i) {
   return pick_fold_tile(f.kind, c->ax[f.axis].bk, f.ncols, f.batch, f.rows);
 }
 
+// Axes whose transforms run factored: finite differences with a 2N that
+// splits into instantiated stage lengths, and line offsets within 32 bits.
+// FP64 transforms only: with FP32 or split-bf16 storage the factored passes
+// round differently from the dense ones at the level of the storage itself
+// (closer to the exact solve, 2e-7 against 5e-7), and callers of a single
+// reduced-precision solve would see other results.
+void choose_fast(qn_ctx c) {
+  c->any_fast = false;
+  c->all_fast = true;
+  for (int a = 0; a < c->dim; ++a) {
+    const int off = c->bc == QN_BC_NEUMANN ? 0 : 1;
+    FastAxis f{};
+    f.N = off ? c->n[a] + 1 : c->n[a] - 1;
+    f.off = off;
+    const long long es = a == 0 ? 1 : a == 1 ? c->p[0] : (long long)c->p[1] * c->p[0];
+    c->fast[a] = c->prec == QN_PREC_FP64 && c->sem_k == 0 && f.N >= 16 && fast_stages(f.N, &f.Q, &f.R) &&
+                 (f.R / 2 + 1) * es + 64 < (1LL << 28);
+    c->fx[a] = f;
+    c->any_fast = c->any_fast || c->fast[a];
+    c->all_fast = c->all_fast && c->fast[a];
+  }
+}
+
 EpiArgs epi_args(qn_ctx c, const double* coef, double* dense) {
   EpiArgs ep{};
   ep.inst_mod = 1;
@@ -578,15 +612,106 @@ EpiArgs epi_args(qn_ctx c, const double* coef, double* dense) {
   return ep;
 }
 
+// Factored pass over `axis` of the tensor at W (in place; the x forward pass
+// may read the caller's rhs, the x inverse one writes ep.dense).  The other
+// axes are covered up to their interior extents, in the storage order of a
+// factored axis, or padded where a dense product left the split order.
+hipError_t fast_pass(qn_ctx c, int axis, double* W, const double* rhs, bool inverse, bool divide,
+                     int epi_last, const EpiArgs& ep) {
+  const int px = c->p[0], py = c->p[1], pz = c->p[2], nx = c->n[0], ny = c->n[1], nz = c->n[2];
+  const long long zs = (long long)py * px, cs = (long long)pz * zs;
+  FastArgs a{};
+  a.ax = c->fx[axis];
+  a.ax.tw = c->ws + c->off_tw[axis];
+  a.ax.lam = c->at<double>(c->off_lx[axis]);
+  a.in = rhs ? rhs : W;
+  a.out = W;
+  a.skip = ep.skip;
+  a.inst_mod = 1;
+  a.om = nz;
+  a.s1 = cs;
+  a.s0 = zs;
+  if (axis == 0) {
+    a.rows = c->ncomp * nz * ny;
+    a.oy = ny;
+    a.ys = a.iys = px;
+    a.is1 = cs;
+    a.is0 = zs;
+    if (rhs) {
+      a.iys = nx;
+      a.is0 = (long long)ny * nx;
+      a.is1 = nz * a.is0;
+    }
+    a.dense = ep.dense;
+    a.dys = nx;
+    a.ds0 = (long long)ny * nx;
+    a.sub = epi_last == EPI_SUB_DENSE;
+    a.uscale = ep.uscale;
+    a.step = ep.step;
+    return launch_fast_rows(a, inverse, c->stream);
+  }
+  a.nx = c->fast[0] ? nx : px;
+  a.coef = ep.coef;
+  a.cscale = ep.cscale;
+  a.comp_div = 1;
+  a.lamX = ep.lamX;
+  if (axis == 1) {  // planes of every component; 2D with the divide: plane = component
+    a.es = px;
+    a.oy = 1;
+    return launch_fast_lines(a, c->ncomp * nz, divide, c->stream);
+  }
+  const int ey = c->fast[1] ? ny : py;
+  a.es = zs;
+  a.om = a.oy = ey;
+  a.s0 = px;
+  a.lamY = c->at<double>(c->off_lam[1]);
+  return launch_fast_lines(a, c->ncomp * ey, divide, c->stream);
+}
+
 // skip (device int, may be NULL): when set, every launch of the solve exits
-// at once (the quasi-Newton loop has stopped).
+// at once (the quasi-Newton loop has stopped).  rhs: the caller's right-hand
+// side when it is not in W1 (all axes factored).
 hipError_t solve_ws(qn_ctx c, const double* coef, double* dense, int epi_last,
-                    const int* skip = nullptr, const double* uscale = nullptr) {
+                    const int* skip = nullptr, const double* uscale = nullptr,
+                    const double* rhs = nullptr) {
   EpiArgs ep = epi_args(c, coef, dense);
   ep.skip = skip;
   ep.uscale = uscale;
   FoldStep st[6];
   const int ns = solve_plan(c, ep, epi_last, st);
+  if (c->any_fast) {
+    // the plan's launches in order, factored axes in place on the current
+    // tensor, dense ones into the other; the last forward axis, when
+    // factored, takes the divide and its inverse in the same pass
+    const int last = c->dim - 1;
+    void* cur = c->ws + c->off_W1;
+    void* other = c->ws + c->off_W2;
+    static const int kFwd[3] = {K_GEMM_X, K_GEMM_YZ, K_GEMM_YZ};
+    for (int i = 0; i < 2 * c->dim; ++i) {
+      const bool inverse = i >= c->dim;
+      const int axis = inverse ? 2 * c->dim - 1 - i : i;
+      if (c->fast[axis] && inverse && axis == last) continue;
+      hipError_t e;
+      if (c->fast[axis]) {
+        const bool divide = axis == last;
+        const int kid = divide ? K_GEMM_DIVIDE
+                               : inverse ? (axis == 0 ? K_GEMM_X_UPDATE : K_GEMM_YZ_INV) : kFwd[axis];
+        e = timed(c, kid, [&] {
+          return fast_pass(c, axis, (double*)cur, axis == 0 && !inverse ? rhs : nullptr, inverse, divide,
+                           epi_last, ep);
+        });
+      } else {
+        FoldStep f = st[i];
+        f.in = cur;
+        f.out = other;
+        const FoldTile t = step_tile(c, f, i);
+        e = timed(c, f.kid, [&] { return run_step(c, f, t); });
+        std::swap(cur, other);
+      }
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
   for (int i = 0; i < ns; ++i) {
     const FoldStep& f = st[i];
     const FoldTile t = step_tile(c, f, i);
@@ -798,6 +923,7 @@ qn_status qn_setup(const qn_grid* grid, double beta, int32_t nonlinearity, const
       for (double& l : c->hlam[a]) l /= length * length;
     c->lam_min_sum += c->hlam[a][0];  // lam_1 (Dirichlet) or 0 (Neumann) leads both orderings
   }
+  choose_fast(c);
   // 3D bf16x3: the forward y and z products run folded when both axes fit it
   c->fwdfold = c->prec == QN_PREC_BF16X3 && c->dim == 3 && c->sem_k == 0 && c->bc == QN_BC_DIRICHLET;
   for (int a = 1; a < 3 && c->fwdfold; ++a)
@@ -850,6 +976,17 @@ qn_status qn_setup(const qn_grid* grid, double beta, int32_t nonlinearity, const
       c->off_Sf[a][q] = off;
       off += align256(c->hSf[a].size() * 2);
     }
+  for (int a = 0; a < c->dim; ++a) {
+    if (!c->fast[a]) continue;
+    const FastAxis& f = c->fx[a];
+    fast_tables(f.N, f.Q, f.R, c->bc == QN_BC_NEUMANN, c->ih2[a], c->htw[a], c->hlx[a]);
+    c->off_tw[a] = off;
+    off += align256(c->htw[a].size() * 8);
+    c->off_lx[a] = off;
+    off += align256(c->hlx[a].size() * 8);
+    // modes in order instead of the folded products' split order
+    for (int i = 0; i < c->n[a]; ++i) c->hlam[a][i] = c->hlx[a][i + f.off];
+  }
   if (c->dim == 2) {  // unused z axis aliases y (never read)
     c->off_S[2] = c->off_S[1];
     c->off_Slo[2] = c->off_Slo[1];
@@ -963,6 +1100,13 @@ qn_status qn_bind_workspace(qn_ctx c, void* d_ws, size_t bytes) {
     if (e == hipSuccess)
       e = hipMemcpyAsync(c->ws + c->off_lam[a], c->hlam[a].data(), (size_t)c->p[a] * 8,
                          hipMemcpyHostToDevice, c->stream);
+    if (e == hipSuccess && c->fast[a]) {
+      e = hipMemcpyAsync(c->ws + c->off_tw[a], c->htw[a].data(), c->htw[a].size() * 8,
+                         hipMemcpyHostToDevice, c->stream);
+      if (e == hipSuccess)
+        e = hipMemcpyAsync(c->ws + c->off_lx[a], c->hlx[a].data(), c->hlx[a].size() * 8,
+                           hipMemcpyHostToDevice, c->stream);
+    }
     if (e == hipSuccess && c->sem_k > 0)
       e = hipMemcpyAsync(c->ws + c->off_Hb[a], c->hHb[a].data(), c->hHb[a].size() * 8,
                          hipMemcpyHostToDevice, c->stream);
@@ -1062,13 +1206,14 @@ qn_status qn_fdm_solve(qn_ctx c, const double* d_R, double scale, double shift, 
                 scale * c->lam_min_sum + shift);
   double* coef = c->at<double>(c->off_coef);
   hipError_t e = launch_set_coef(coef, scale, shift, c->stream);
-  if (e == hipSuccess)
+  if (e == hipSuccess && !c->all_fast)  // the factored x pass reads d_R itself
     e = timed(c, K_PAD_COPY, [&] {
       return launch_pad_copy(d_R, c->ws + c->off_W1, transform_storage(c->prec), c->ncomp,
                              c->n[0], c->n[1], c->n[2], c->p[0], c->p[1], c->p[2], c->stream,
                              c->xfold ? c->hp[0] : 0);
     });
-  if (e == hipSuccess) e = solve_ws(c, coef, d_X, EPI_STORE_DENSE);
+  if (e == hipSuccess)
+    e = solve_ws(c, coef, d_X, EPI_STORE_DENSE, nullptr, nullptr, c->all_fast ? d_R : nullptr);
   if (e != hipSuccess) return hip_fail(c, e, "fdm solve launch");
   return QN_OK;
 }
@@ -1266,7 +1411,8 @@ qn_status qn_autotune(qn_ctx c) {
     const FoldStep& f = st[i];
     best[i] = step_tile(c, f, i);
     FoldTile cand[16];
-    const int nc = step_candidates(c, f, cand);
+    // the factored transform of an axis takes the place of its dense launches
+    const int nc = c->fast[f.axis] ? 0 : step_candidates(c, f, cand);
     float best_ms = 1e30f;
     for (int k = 0; k < nc && e == hipSuccess; ++k) {
       const FoldTile t = cand[k];

@@ -48,6 +48,11 @@ struct Cls {
   // inverse and x inverse (+ update) launches
   FoldTile fR{32, 32, 0}, fL{32, 32, 0}, fLi{32, 32, 0}, fRi{32, 32, 0};
   FoldAxis ax{};
+  // factored transforms of both axes (qn_fast.hip; FP64) and their tables
+  bool fast = false;
+  FastAxis fx{};
+  std::vector<double> htw, hlx;
+  size_t off_tw = 0, off_lx = 0;
   double ih2 = 0.0;           // 1 / h^2 of both axes
   double lam_min = 0.0;       // smallest eigenvalue of the solve operator without the shift
   hipStream_t s = nullptr;    // per-class stream (default priority)
@@ -139,6 +144,52 @@ EpiArgs epi_for(qnb_ctx c, const Cls& k, double* dense_base) {
   return ep;
 }
 
+// The factored solve of class k in place on W1 (x forward, y forward + divide +
+// inverse, x inverse with the dense epilogue of ep), from W1 or, when rhs is
+// given, from the class block of a caller's pool.
+hipError_t class_fast_solve(qnb_ctx c, const Cls& k, const double* rhs, bool sub, const EpiArgs& ep,
+                            hipStream_t s) {
+  const int planes = k.ncomp * k.K;
+  const long long sl = (long long)k.p * k.p, nn = (long long)k.n * k.n;
+  FastArgs a{};
+  a.ax = k.fx;
+  a.ax.tw = c->ws + k.off_tw;
+  a.ax.lam = (const double*)(c->ws + k.off_lx);
+  a.out = (double*)(c->ws + k.off_W1);
+  a.in = rhs ? rhs : a.out;
+  a.skip = ep.skip;
+  a.inst_mod = ep.inst_mod;
+  a.om = planes;
+  a.s0 = sl;
+  a.rows = planes * k.n;
+  a.oy = k.n;
+  a.ys = k.p;
+  a.is0 = rhs ? nn : sl;
+  a.iys = rhs ? k.n : k.p;
+  hipError_t e = launch_fast_rows(a, false, s);
+  if (e != hipSuccess) return e;
+  FastArgs b = a;
+  b.nx = k.n;
+  b.es = k.p;
+  b.oy = 1;
+  b.coef = ep.coef;
+  b.coef_stride = ep.coef_stride;
+  b.cscale = ep.cscale;
+  b.comp_div = ep.cscale ? ep.comp_div : 1;
+  b.lamX = ep.lamX;
+  e = launch_fast_lines(b, planes, true, s);
+  if (e != hipSuccess) return e;
+  a.in = a.out;
+  a.is0 = sl;
+  a.iys = k.p;
+  a.dense = ep.dense;
+  a.ds0 = nn;
+  a.dys = k.n;
+  a.sub = sub;
+  a.step = ep.step;
+  return launch_fast_rows(a, true, s);
+}
+
 // Shift rule of the finalize kernel for a qn_beta_mode.
 int batch_rule(int beta_mode) {
   switch (beta_mode) {
@@ -161,7 +212,7 @@ hipError_t class_iteration(qnb_ctx c, Cls& k, double* U, const double* F, double
   a.r_cstride = (long long)k.K * k.p * k.p;
   a.r_zstride = k.p * k.p;
   a.r_ystride = k.p;
-  a.ox = a.oy = k.p;
+  a.ox = a.oy = k.fast ? k.n : k.p;  // the factored passes never read the padding
   a.oz = k.K;
   a.nx = a.ny = k.n;
   a.nz = k.K;
@@ -190,6 +241,7 @@ hipError_t class_iteration(qnb_ctx c, Cls& k, double* U, const double* F, double
   void* W2 = c->ws + k.off_W2;
   const GemmOperands S = ops(c, k);
   EpiArgs ep = epi_for(c, k, U);
+  if (k.fast) return class_fast_solve(c, k, nullptr, true, ep, s);
   const int rows = k.ncomp * k.K * k.p;
   const int slabs = k.ncomp * k.K;
   const long long sl = (long long)k.p * k.p;
@@ -391,12 +443,27 @@ qn_status qnb_setup_ex(int32_t count, const int32_t* n, const int32_t* ncomp, in
     }
     k.off_lam = off;
     off += a256((size_t)k.p * 8);
+    const int foff = c->bc == QN_BC_NEUMANN ? 0 : 1;
+    k.fx.N = foff ? k.n + 1 : k.n - 1;
+    k.fx.off = foff;
+    k.fast = precision == QN_PREC_FP64 && k.fx.N >= 16 && fast_stages(k.fx.N, &k.fx.Q, &k.fx.R);
+    if (k.fast) {
+      fast_tables(k.fx.N, k.fx.Q, k.fx.R, foff == 0, k.ih2, k.htw, k.hlx);
+      k.off_tw = off;
+      off += a256(k.htw.size() * 8);
+      k.off_lx = off;
+      off += a256(k.hlx.size() * 8);
+      for (int i = 0; i < k.n; ++i) k.hlam[i] = k.hlx[i + foff];  // modes in order
+    }
     const size_t te = (size_t)k.ncomp * k.K * pp * c->elem();
     k.off_W1 = off;
     off += a256(te);
-    k.off_W2 = off;
-    off += a256(te);
-    k.bpi = residual_max_blocks(k.p, k.p, 1, RESIDUAL_PLANAR_ROWS, true);
+    k.off_W2 = k.off_W1;  // the factored passes work in place
+    if (!k.fast) {
+      k.off_W2 = off;
+      off += a256(te);
+    }
+    k.bpi = residual_max_blocks(k.fast ? k.n : k.p, k.fast ? k.n : k.p, 1, RESIDUAL_PLANAR_ROWS, true);
     k.off_part = off;
     off += a256((size_t)k.bpi * k.K * 4 * sizeof(double));
     k.off_state = off;
@@ -512,6 +579,13 @@ qn_status qnb_bind_workspace(qnb_ctx c, void* d_ws, size_t bytes) {
         e = hipMemcpyAsync(c->ws + k.off_Slo, lo.data(), pp * 2, hipMemcpyHostToDevice, c->stream);
       if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     }
+    if (e == hipSuccess && k.fast) {
+      e = hipMemcpyAsync(c->ws + k.off_tw, k.htw.data(), k.htw.size() * 8, hipMemcpyHostToDevice,
+                         c->stream);
+      if (e == hipSuccess)
+        e = hipMemcpyAsync(c->ws + k.off_lx, k.hlx.data(), k.hlx.size() * 8, hipMemcpyHostToDevice,
+                           c->stream);
+    }
     if (e == hipSuccess)
       e = hipMemcpyAsync(c->ws + k.off_lam, k.hlam.data(), (size_t)k.p * 8, hipMemcpyHostToDevice,
                          c->stream);
@@ -534,6 +608,7 @@ qn_status qnb_autotune(qnb_ctx c) {
   if (e != hipSuccess) return hip_bad(c, e, "autotune events");
   const int cand[3] = {32, 64, 128};
   for (auto& k : c->cls) {
+    if (k.fast) continue;  // no dense product to tune
     EpiArgs ep = epi_for(c, k, nullptr);
     ep.skip = nullptr;  // time every tile
     const GemmOperands S = ops(c, k);
@@ -634,6 +709,14 @@ qn_status qnb_fdm_solve(qnb_ctx c, const double* d_R, double scale, double shift
     if (e != hipSuccess) break;
     void* W1 = c->ws + k.off_W1;
     void* W2 = c->ws + k.off_W2;
+    if (k.fast) {
+      EpiArgs ep = epi_for(c, k, d_X);
+      ep.skip = nullptr;  // every instance
+      ep.coef = coef;
+      ep.coef_stride = 0;
+      e = class_fast_solve(c, k, d_R + k.off_field, false, ep, c->stream);
+      continue;
+    }
     // the class block (ncomp, K, n, n) -> (ncomp, K, P, P), zero padding
     e = launch_pad_copy(d_R + k.off_field, W1, transform_storage(c->prec), k.ncomp, k.n, k.n,
                         k.K, k.p, k.p, k.K, c->stream);

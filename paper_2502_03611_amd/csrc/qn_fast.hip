@@ -1,0 +1,320 @@
+// Factored mode products: the eigen-transform of an axis in two register
+// stages instead of one dense product with S.
+//
+// With N = n + 1 (Dirichlet) or n - 1 (Neumann) intervals the 1D eigenvectors
+// of the finite-difference stiffness matrix (Section 3.2 eq. Sy, Section 4.2)
+// are sin(pi j k / N) or cos(pi j k / N): S x is the length-2N DFT of x
+// continued oddly (evenly) about both ends.  For 2N = Q R the DFT splits
+// (Cooley-Tukey): with j = R a + b, k = k1 + Q k2,
+//   Y_b[k1] = sum_a x[R a + b] w_Q^{a k1},   T_b[k1] = w_2N^{b k1} Y_b[k1],
+//   X[k1 + Q k2] = sum_b w_R^{b k2} T_b[k1].
+// The continuation makes T_{R-b} = -+ conj(T_b) and X purely imaginary
+// (real), so only b = 0 .. R/2 and k1 = 0 .. Q/2 are formed, every x is loaded
+// once, and both stages are real: one thread owns a class j = +-b (mod R) of
+// one line in stage 1 and a class k = +-k1 (mod Q) in stage 2, and the classes
+// are exchanged once through LDS.  A transform of 512 intervals (32 x 32)
+// takes about 20 multiply-adds per point where the reflection-folded dense
+// product takes 256, so the kernels are bound by HBM: 16 bytes per point and
+// pass.  Sums have at most 16 terms per stage, so rounding
+// is below the dense product's.
+//
+// Along the axis a thread reads and writes in strides of R (Q) elements, so
+// no staging is needed for coalescing: y and z passes put 16 neighbouring
+// lines, 128 bytes, in consecutive lanes; x passes put
+// the R/2 + 1 classes of one row in consecutive lanes, whose loads are
+// consecutive elements.  The last forward axis keeps its modes in registers,
+// divides them by the shifted eigenvalue sums (Section 4.1 eq. fin_inverse)
+// and runs the inverse transform at once: one pass over HBM for the forward
+// transform, the divide and the inverse one.  The transforms are their own
+// inverses (scale sqrt(2/N) in the twiddles).
+//
+// Stage lengths are compile-time (qn_fast.h); a workgroup-uniform switch
+// selects them, so one kernel serves every N whose 2N factors.
+
+#include <algorithm>
+#include <atomic>
+
+#include "qn_fast.h"
+#include "qn_internal.h"
+#include "qn_mfma.h"
+
+namespace qn {
+namespace {
+
+#define QN_FAST_SWITCH(len)              \
+  if constexpr (BIG) {                   \
+    switch (len) { QN_FAST_BIG(X) }      \
+  } else {                               \
+    switch (len) { QN_FAST_SMALL(X) }    \
+  }
+
+typedef double T;
+constexpr int FAST_THREADS = 320;  // at most 17 (33) classes of 16 (8) lines
+
+
+// ------------------------------------------------------------- y and z passes
+
+// One transform (DIV = 0) or forward transform, divide and inverse transform
+// (DIV = 1) of the lines of C consecutive x positions, in place.
+template <bool BIG, int DIV>
+__global__ __launch_bounds__(FAST_THREADS, 2) void k_fast_lines(FastArgs a) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  Pair<T>* lds = reinterpret_cast<Pair<T>*>(smem);
+  const int C = 1 << a.lc;
+  const int xt = blockIdx.x % a.xtiles, o = blockIdx.x / a.xtiles;
+  const int plane = o / a.oy;
+  const int inst = plane % a.inst_mod;
+  if (a.skip && a.skip[inst]) return;
+  const int N = a.ax.N, Q = a.ax.Q, R = a.ax.R, off = a.ax.off;
+  const T sg = off ? T(-1) : T(1);
+  const int t = threadIdx.x, line = t & (C - 1), c = t >> a.lc;
+  const int x0 = xt * C;
+  const int xl = x0 + line < a.nx ? line : a.nx - 1 - x0;  // lanes past the end repeat the last line
+  const bool live_x = x0 + line < a.nx;
+  T* base = a.out + (long long)(o / a.om) * a.s1 + (long long)(o % a.om) * a.s0 + x0;
+  const unsigned es = (unsigned)a.es;
+  const Pair<T>* tw = (const Pair<T>*)a.ax.tw;
+  const int rh = R >> 1, qh = Q >> 1;
+  const bool in1 = c <= rh, in2 = c <= qh;
+
+#define X(L)                                                                                       \
+  case L: {                                                                                        \
+    if (in1) {                                                                                     \
+      T x[L];                                                                                      \
+      load_class<L, T>((const T*)base, xl + c * es, xl + (rh - c) * es, N, R, c, off, sg, a.es, x);       \
+      stage1<L, T>(x, tw, c, lds + (c << a.lc) + line, (rh + 1) << a.lc);                          \
+    }                                                                                              \
+    break;                                                                                         \
+  }
+  QN_FAST_SWITCH(Q)
+#undef X
+  __syncthreads();
+  if constexpr (DIV == 0) {
+#define X(L)                                                                                       \
+  case L: {                                                                                        \
+    if (in2) {                                                                                     \
+      T v[L];                                                                                      \
+      stage2<L, T>(lds + (((rh + 1) * c) << a.lc) + line, C, v);                                   \
+      if (live_x)                                                                                  \
+        for_modes<L>(Q, N, c, off, [&](int k2, int pos, bool mir) {                                \
+          base[(long long)pos * a.es + line] = mir ? sg * v[k2] : v[k2];                           \
+        });                                                                                        \
+    }                                                                                              \
+    break;                                                                                         \
+  }
+    QN_FAST_SWITCH(R)
+#undef X
+  } else {
+    const double* coef = a.coef + (long long)inst * a.coef_stride;
+    const double scale = coef[0] * (a.cscale ? a.cscale[plane / a.comp_div] : 1.0), beta = coef[1];
+    const double lam0 = a.lamX[x0 + xl] + (a.lamY ? a.lamY[o % a.oy] : 0.0);
+#define X(L)                                                                                       \
+  case L: {                                                                                        \
+    T v[L];                                                                                        \
+    if (in2) {                                                                                     \
+      stage2<L, T>(lds + (((rh + 1) * c) << a.lc) + line, C, v);                                   \
+      const double* lam = a.ax.lam + c; /* lam[k], k = 0 .. 2N - 1: continued evenly */            \
+      _Pragma("unroll") for (int k2 = 0; k2 < L; ++k2) {                                           \
+        v[k2] = quot(v[k2], scale * (lam0 + lam[(long long)Q * k2]) + beta);                       \
+      }                                                                                            \
+      if (off) { /* the modes k = 0 and k = N do not exist */                                      \
+        if (c == 0) {                                                                              \
+          v[0] = T(0);                                                                             \
+          if (L % 2 == 0) v[L / 2] = T(0);                                                         \
+        }                                                                                          \
+        if (L % 2 == 1 && 2 * c == Q) v[(L - 1) / 2] = T(0);                                       \
+      }                                                                                            \
+    }                                                                                              \
+    __syncthreads(); /* stage 2 reads done; the same LDS takes the inverse's pairs */              \
+    if (in2) stage1<L, T>(v, tw, c, lds + (c << a.lc) + line, (qh + 1) << a.lc);                   \
+    break;                                                                                         \
+  }
+    QN_FAST_SWITCH(R)
+#undef X
+    __syncthreads();
+#define X(L)                                                                                       \
+  case L: {                                                                                        \
+    if (in1) {                                                                                     \
+      T v[L];                                                                                      \
+      stage2<L, T>(lds + (((qh + 1) * c) << a.lc) + line, C, v);                                   \
+      if (live_x)                                                                                  \
+        for_modes<L>(R, N, c, off, [&](int k2, int pos, bool mir) {                                \
+          base[(long long)pos * a.es + line] = mir ? sg * v[k2] : v[k2];                           \
+        });                                                                                        \
+    }                                                                                              \
+    break;                                                                                         \
+  }
+    QN_FAST_SWITCH(Q)
+#undef X
+  }
+}
+
+// ------------------------------------------------------------------- x passes
+
+// Transform of rows (the contiguous axis): a.rows rows of the tensor, a.lines
+// per workgroup.  EPI 0: into a.out (padded layout); EPI 1: into the caller's
+// array a.dense (interior layout), stored or subtracted.
+template <bool BIG, int EPI>
+__global__ __launch_bounds__(FAST_THREADS, 2) void k_fast_rows(FastArgs a) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  Pair<T>* lds = reinterpret_cast<Pair<T>*>(smem);
+  const int N = a.ax.N, Q = a.ax.Q, R = a.ax.R, off = a.ax.off;
+  const T sg = off ? T(-1) : T(1);
+  const int rh = R >> 1, qh = Q >> 1;
+  const int t = threadIdx.x;
+  const int r0 = blockIdx.x * a.lines;
+  const int rlast = min(r0 + a.lines, a.rows) - 1;
+  const int pl0 = r0 / a.oy, pl1 = rlast / a.oy;
+  if (a.skip) {  // every instance of the workgroup's rows has stopped
+    bool any = false;
+    for (int p = pl0; p <= pl1; ++p) any = any || !a.skip[p % a.inst_mod];
+    if (!any) return;
+  }
+  const Pair<T>* tw = (const Pair<T>*)a.ax.tw;
+  // offset of row r from the tensor's start, in the padded (in, out) or
+  // interior (dense) layout
+  auto row_off = [&](int r, long long s1, long long s0, long long ys) {
+    const int p = r / a.oy;
+    return (long long)(p / a.om) * s1 + (long long)(p % a.om) * s0 + (long long)(r - p * a.oy) * ys;
+  };
+  const int line1 = t / (rh + 1), c1 = t - line1 * (rh + 1);
+  const int line2 = t / (qh + 1), c2 = t - line2 * (qh + 1);
+  const bool in1 = line1 < a.lines;
+  const int row2 = r0 + line2;
+  const bool in2 = line2 < a.lines && row2 <= rlast;
+  const int rp = (rh + 1) | 1;  // odd class stride: stage 2 reads hit distinct banks
+  const long long b0 = row_off(r0, a.is1, a.is0, a.iys);
+  const T* base = a.in + b0;
+  const unsigned lo = (unsigned)(row_off(min(r0 + line1, rlast), a.is1, a.is0, a.iys) - b0);
+
+#define X(L)                                                                                       \
+  case L: {                                                                                        \
+    if (in1) {                                                                                     \
+      T x[L];                                                                                      \
+      load_class<L, T>(base, lo + c1, lo + rh - c1, N, R, c1, off, sg, 1, x);                 \
+      stage1<L, T>(x, tw, c1, lds + line1 * (qh + 1) * rp + c1, rp);                               \
+    }                                                                                              \
+    break;                                                                                         \
+  }
+  QN_FAST_SWITCH(Q)
+#undef X
+  __syncthreads();
+  if (!in2) return;
+  if (a.skip && a.skip[(row2 / a.oy) % a.inst_mod]) return;
+  const Pair<T>* lp = lds + (line2 * (qh + 1) + c2) * rp;
+  if constexpr (EPI == 0) {
+    T* out = a.out + row_off(row2, a.s1, a.s0, a.ys);
+#define X(L)                                                                                       \
+  case L: {                                                                                        \
+    T v[L];                                                                                        \
+    stage2<L, T>(lp, 1, v);                                                                        \
+    for_modes<L>(Q, N, c2, off,                                                                    \
+                 [&](int k2, int pos, bool mir) { out[pos] = mir ? sg * v[k2] : v[k2]; });         \
+    break;                                                                                         \
+  }
+    QN_FAST_SWITCH(R)
+#undef X
+  } else {
+    double* out = a.dense + row_off(row2, a.om * a.ds0, a.ds0, a.dys);
+    if (a.sub) {
+      const double us = a.uscale ? *a.uscale : 1.0, st = a.step;
+#define X(L)                                                                                       \
+  case L: {                                                                                        \
+    T v[L];                                                                                        \
+    double old[L];                                                                                 \
+    /* old values in flight during stage 2, for lengths whose registers allow it */                \
+    if (L <= 32) for_modes<L>(Q, N, c2, off, [&](int k2, int pos, bool) { old[k2] = out[pos]; });  \
+    stage2<L, T>(lp, 1, v);                                                                        \
+    for_modes<L>(Q, N, c2, off, [&](int k2, int pos, bool mir) {                                   \
+      out[pos] = us * (L <= 32 ? old[k2] : out[pos]) - st * (mir ? sg * v[k2] : v[k2]);            \
+    });                                                                                            \
+    break;                                                                                         \
+  }
+      QN_FAST_SWITCH(R)
+#undef X
+    } else {
+#define X(L)                                                                                       \
+  case L: {                                                                                        \
+    T v[L];                                                                                        \
+    stage2<L, T>(lp, 1, v);                                                                        \
+    for_modes<L>(Q, N, c2, off, [&](int k2, int pos, bool mir) {                                   \
+      out[pos] = mir ? sg * v[k2] : v[k2];                                                         \
+    });                                                                                            \
+    break;                                                                                         \
+  }
+      QN_FAST_SWITCH(R)
+#undef X
+    }
+  }
+}
+
+// Kernels of more than 64 KB of LDS need the limit raised once per device.
+template <typename K>
+hipError_t allow_lds(K kernel, size_t bytes) {
+  static std::atomic<unsigned long long> done{0};  // one bit per device
+  if (bytes <= 64 * 1024) return hipSuccess;
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const unsigned long long bit = 1ull << (dev & 63);
+  if (done.load(std::memory_order_relaxed) & bit) return hipSuccess;
+  e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+  if (e == hipSuccess) done.fetch_or(bit, std::memory_order_relaxed);
+  return e;
+}
+
+constexpr size_t kLdsTarget = 80 * 1024;  // two workgroups per CU
+
+int round64(int v) { return (v + 63) & ~63; }
+
+template <bool BIG, int DIV>
+hipError_t lines_launch(FastArgs a, int nouter, hipStream_t st) {
+  const int qh = a.ax.Q / 2 + 1, rh = a.ax.R / 2 + 1;
+  int lc = BIG ? 3 : 4;
+  auto bytes = [&](int l) { return (size_t)qh * rh * sizeof(Pair<T>) << l; };
+  while (lc > 2 && bytes(lc) > kLdsTarget) --lc;
+  // small grids: fewer lines per workgroup until every CU has two
+  while (lc > 2 && (long long)((a.nx + (1 << lc) - 1) >> lc) * nouter < 512) --lc;
+  a.lc = lc;
+  a.xtiles = (a.nx + (1 << lc) - 1) >> lc;
+  const int nt = round64(std::max(qh, rh) << lc);
+  auto kern = k_fast_lines<BIG, DIV>;
+  hipError_t e = allow_lds(kern, bytes(lc));
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3((unsigned)a.xtiles * nouter), dim3(nt), bytes(lc), st, a);
+  return hipGetLastError();
+}
+
+template <bool BIG, int EPI>
+hipError_t rows_launch(FastArgs a, hipStream_t st) {
+  const int qh = a.ax.Q / 2 + 1, rh = a.ax.R / 2 + 1, nb = std::max(qh, rh);
+  const size_t per = (size_t)qh * (rh | 1) * sizeof(Pair<T>);
+  int lines = 256 / nb;
+  lines = std::min<int>(lines, std::max<size_t>(1, kLdsTarget / per));
+  // small grids: fewer rows per workgroup (but a whole wave) until every CU has two
+  lines = std::min(lines, std::max(std::max(1, 64 / nb), a.rows / 512));
+  a.lines = lines;
+  auto kern = k_fast_rows<BIG, EPI>;
+  hipError_t e = allow_lds(kern, per * lines);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3((a.rows + lines - 1) / lines), dim3(round64(lines * nb)),
+                     per * lines, st, a);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_fast_lines(const FastArgs& a, int nouter, bool divide, hipStream_t st) {
+  const bool big = std::max(a.ax.Q, a.ax.R) > 32;
+  if (big) return divide ? lines_launch<true, 1>(a, nouter, st) : lines_launch<true, 0>(a, nouter, st);
+  return divide ? lines_launch<false, 1>(a, nouter, st) : lines_launch<false, 0>(a, nouter, st);
+}
+
+hipError_t launch_fast_rows(const FastArgs& a, bool dense, hipStream_t st) {
+  const bool big = std::max(a.ax.Q, a.ax.R) > 32;
+  if (big) return dense ? rows_launch<true, 1>(a, st) : rows_launch<true, 0>(a, st);
+  return dense ? rows_launch<false, 1>(a, st) : rows_launch<false, 0>(a, st);
+}
+
+}  // namespace qn

@@ -5,6 +5,7 @@
 #include <cmath>
 #include <cstdint>
 #include <cstring>
+#include <iterator>
 #include <vector>
 
 namespace qn {
@@ -382,6 +383,57 @@ inline float bf16_value(uint16_t h) {
   float f;
   std::memcpy(&f, &u, 4);
   return f;
+}
+
+// Stage lengths of the factored transform of an axis of N intervals
+// (qn_fast.hip): 2N = Q R, both instantiated, with the fewest multiply-adds
+// per point; false when 2N has no such factorisation.
+inline bool fast_stages(int N, int* Qo, int* Ro) {
+  static const int big[] = {20, 24, 28, 30, 32, 36, 40, 44, 48, 50, 52, 56, 60, 64};
+  auto is_big = [](int q) { return std::find(std::begin(big), std::end(big), q) != std::end(big); };
+  // multiply-adds of an unrolled stage: even lengths halve, odd ones are contracted
+  auto work = [](int q) {
+    double w = 0.0;
+    for (; q > 2 && q % 2 == 0; q /= 2) w += q * q / 8.0 + 1.5 * q;
+    return w + (q > 2 ? q * q / 2.0 + q : q);
+  };
+  double best = 1e300;
+  for (int q = 4; q <= 64; ++q) {
+    if ((2 * N) % q != 0) continue;
+    const int r = 2 * N / q;
+    const bool small = q <= 32 && r >= 4 && r <= 32;
+    if (!small && !(is_big(q) && is_big(r))) continue;
+    // the small kernel (shorter stages, more waves in flight) where it applies
+    const double w = work(q) / q + work(r) / r + (small ? 0.0 : 1e6);
+    if (w < best) {
+      best = w;
+      *Qo = q;
+      *Ro = r;
+    }
+  }
+  return best < 1e300;
+}
+
+// Device tables of a factored axis: twiddle pairs (see FastAxis) and the
+// eigenvalues 4 h^-2 sin^2(pi k / 2N) of the modes k = 0 .. 2N - 1, continued
+// evenly (k = 0 and N do not exist for Dirichlet data and get the largest).
+inline void fast_tables(int N, int Q, int R, bool neumann, double ih2, std::vector<double>& tw,
+                        std::vector<double>& lam) {
+  const double pi = 3.14159265358979323846, nrm = std::sqrt(2.0 / N);
+  const int nt = (Q / 2) * (R / 2) + 1;
+  tw.resize(2 * (size_t)nt);
+  for (int i = 0; i < nt; ++i) {  // i <= N / 2
+    const double c = nrm * (2 * i == N ? 0.0 : std::cos(pi * i / N)), s = nrm * std::sin(pi * i / N);
+    tw[2 * i] = neumann ? -s : c;
+    tw[2 * i + 1] = neumann ? c : s;
+  }
+  lam.resize(2 * (size_t)N);
+  for (int k = 0; k <= N; ++k) {
+    const double s = std::sin(pi * k / (2.0 * N));
+    lam[k] = 4.0 * ih2 * s * s;
+  }
+  if (!neumann) lam[0] = lam[N] = lam[N - 1];
+  for (int k = N + 1; k < 2 * N; ++k) lam[k] = lam[2 * N - k];
 }
 
 }  // namespace qn

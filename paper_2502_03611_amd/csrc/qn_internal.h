@@ -174,6 +174,51 @@ hipError_t launch_fold(int kind, int prec, const FoldOperands& f, const void* in
                        const FoldAxis& ax, int ncols, int batch, long long bstride, int rows,
                        int epi, const EpiArgs& ep, const FoldTile& t, hipStream_t st);
 
+// Factored mode products (qn_fast.hip): axes whose doubled interval count 2N
+// (N = n + 1 Dirichlet, n - 1 Neumann, finite differences) is a product Q R of
+// instantiated stage lengths; FP64.  tw: device pairs sqrt(2/N) (cos, sin)(pi
+// i / N) for i <= (Q/2)(R/2) ((-sin, cos) for Neumann data); lam: device eigenvalues of the modes k = 0 .. 2N - 1,
+// continued evenly; off: 1 Dirichlet (position = mode - 1), 0 Neumann.
+struct FastAxis {
+  int N, Q, R, off;
+  const void* tw;
+  const double* lam;
+};
+// Line passes (launch_fast_lines), in place on `out`: nx lines (x positions)
+// of each of the nouter outer indices o, line (o, x) at element (o / om) s1 +
+// (o % om) s0 + x, axis stride es; plane = o / oy.  With the divide:
+// eigenvalues lamX[x] + lamY[o % oy] of the other axes, coefficients as
+// EpiArgs (instance plane % inst_mod, component plane / comp_div).
+// Row passes (launch_fast_rows): rows r of the contiguous axis, plane r / oy,
+// row y = r % oy; plane p at (p / om) s1 + (p % om) s0, row stride ys (input:
+// is1, is0, iys; the caller's array dense: ds0 per plane, dys per row), stored
+// or (sub) dense = uscale * dense - step * result.
+struct FastArgs {
+  FastAxis ax;
+  const double* in;
+  double* out;
+  int nx, rows;
+  int oy, om;
+  long long s1, s0, ys, es;
+  long long is1, is0, iys;
+  double* dense;
+  long long ds0, dys;
+  int sub;
+  const double* uscale;
+  double step;
+  const double* coef;
+  int coef_stride;
+  const double* cscale;
+  int comp_div;
+  const double* lamX;
+  const double* lamY;
+  const int* skip;
+  int inst_mod;
+  int lc, xtiles, lines;  // filled by the launchers
+};
+hipError_t launch_fast_lines(const FastArgs& a, int nouter, bool divide, hipStream_t st);
+hipError_t launch_fast_rows(const FastArgs& a, bool dense, hipStream_t st);
+
 // Residual of the nonlinear problem, written (with zero padding) into the
 // transform workspace or into a dense caller array.  out_prec: 0 fp64, 1 fp32.
 struct ResidualArgs {
