@@ -123,6 +123,9 @@ struct qn_ctx_s {
   bool fast[3] = {false, false, false};
   bool any_fast = false, all_fast = false;
   FastAxis fx[3] = {};
+  // element strides of y, z and the component in the tensor at W1 when every
+  // axis is factored (it may reach into W2, which such solves do not use)
+  long long fs[3] = {0, 0, 0};
   std::vector<double> htw[3], hlx[3];
   size_t off_tw[3] = {0, 0, 0}, off_lx[3] = {0, 0, 0};
   // workspace layout (byte offsets)
@@ -319,6 +322,9 @@ ResidualArgs residual_args(qn_ctx c, const double* U, const double* F, double* R
     a.ox = c->n[0];
     a.oy = c->n[1];
     a.oz = c->n[2];
+    a.r_ystride = (int)c->fs[0];
+    a.r_zstride = (int)c->fs[1];
+    a.r_cstride = c->fs[2];
   }
   a.rz = c->dim == 3 ? residual_slab_depth(a.ox, a.oy, a.oz, residual_threads(c->nl, c->bc))
                       : residual_planar_rows(a.ox, a.oy);
@@ -583,12 +589,22 @@ void choose_fast(qn_ctx c) {
     FastAxis f{};
     f.N = off ? c->n[a] + 1 : c->n[a] - 1;
     f.off = off;
-    const long long es = a == 0 ? 1 : a == 1 ? c->p[0] : (long long)c->p[1] * c->p[0];
+    const long long es = a == 0 ? 1 : a == 1 ? c->p[0] : (long long)c->p[1] * c->p[0] + 16;
     c->fast[a] = c->prec == QN_PREC_FP64 && c->sem_k == 0 && f.N >= 16 && fast_stages(f.N, &f.Q, &f.R) &&
                  (f.R / 2 + 1) * es + 64 < (1LL << 28);
     c->fx[a] = f;
     c->any_fast = c->any_fast || c->fast[a];
     c->all_fast = c->all_fast && c->fast[a];
+  }
+  if (c->all_fast) {
+    // 128-byte rows; an odd number of 128-byte lines per plane, so that the z
+    // passes' strides do not return to the same memory channels (511^3: plane
+    // stride 2 MiB 0.82 ms for the z pass, 2 MiB - 4 KiB 0.70, odd 0.69; the y
+    // passes 0.47 and 0.45 ms)
+    c->fs[0] = (c->n[0] + 15) & ~15;
+    const long long lines = c->n[1] * c->fs[0] / 16;
+    c->fs[1] = 16 * (lines | 1);
+    c->fs[2] = c->n[2] * c->fs[1];
   }
 }
 
@@ -619,7 +635,8 @@ EpiArgs epi_args(qn_ctx c, const double* coef, double* dense) {
 hipError_t fast_pass(qn_ctx c, int axis, double* W, const double* rhs, bool inverse, bool divide,
                      int epi_last, const EpiArgs& ep) {
   const int px = c->p[0], py = c->p[1], pz = c->p[2], nx = c->n[0], ny = c->n[1], nz = c->n[2];
-  const long long zs = (long long)py * px, cs = (long long)pz * zs;
+  const long long ys = c->all_fast ? c->fs[0] : px, zs = c->all_fast ? c->fs[1] : (long long)py * px,
+                  cs = c->all_fast ? c->fs[2] : (long long)pz * py * px;
   FastArgs a{};
   a.ax = c->fx[axis];
   a.ax.tw = c->ws + c->off_tw[axis];
@@ -634,7 +651,7 @@ hipError_t fast_pass(qn_ctx c, int axis, double* W, const double* rhs, bool inve
   if (axis == 0) {
     a.rows = c->ncomp * nz * ny;
     a.oy = ny;
-    a.ys = a.iys = px;
+    a.ys = a.iys = ys;
     a.is1 = cs;
     a.is0 = zs;
     if (rhs) {
@@ -656,14 +673,14 @@ hipError_t fast_pass(qn_ctx c, int axis, double* W, const double* rhs, bool inve
   a.comp_div = 1;
   a.lamX = ep.lamX;
   if (axis == 1) {  // planes of every component; 2D with the divide: plane = component
-    a.es = px;
+    a.es = ys;
     a.oy = 1;
     return launch_fast_lines(a, c->ncomp * nz, divide, c->stream);
   }
   const int ey = c->fast[1] ? ny : py;
   a.es = zs;
   a.om = a.oy = ey;
-  a.s0 = px;
+  a.s0 = ys;
   a.lamY = c->at<double>(c->off_lam[1]);
   return launch_fast_lines(a, c->ncomp * ey, divide, c->stream);
 }
@@ -870,6 +887,12 @@ qn_status qn_setup(const qn_grid* grid, double beta, int32_t nonlinearity, const
   for (int i = 0; i < 4; ++i) c->gs[i] = gs[i];
   c->lam_min_sum = 0.0;
   for (int a = 0; a < 3; ++a) {
+    const double ih = (c->bc == QN_BC_NEUMANN ? c->n[a] - 1 : c->n[a] + 1) / length;
+    if (a < c->dim) c->ih2[a] = ih * ih;
+    c->p[a] = a >= c->dim ? 1 : c->fold ? 2 * fold_block(c->n[a]) : (c->n[a] + 31) / 32 * 32;
+  }
+  choose_fast(c);
+  for (int a = 0; a < 3; ++a) {
     if (a >= c->dim) {
       c->p[a] = 1;
       continue;
@@ -906,6 +929,15 @@ qn_status qn_setup(const qn_grid* grid, double beta, int32_t nonlinearity, const
     }
     c->hx[a].resize((size_t)n);
     for (int i = 0; i < n; ++i) c->hx[a][i] = (c->bc == QN_BC_NEUMANN ? i : i + 1) / ih;
+    if (c->fast[a]) {  // modes in order; no dense operand
+      const FastAxis& f = c->fx[a];
+      c->ax[a] = FoldAxis{n, n / 2, n & 1, fold_block(n)};  // of the launches it replaces
+      fast_tables(f.N, f.Q, f.R, c->bc == QN_BC_NEUMANN, c->ih2[a], c->htw[a], c->hlx[a]);
+      c->hlam[a].assign((size_t)c->p[a], c->hlx[a][f.N - 1]);
+      for (int i = 0; i < n; ++i) c->hlam[a][i] = c->hlx[a][i + f.off];
+      c->lam_min_sum += c->hlam[a][0];
+      continue;
+    }
     if (c->fold) {
       const int bk = fold_block(n);
       c->ax[a] = FoldAxis{n, n / 2, n & 1, bk};
@@ -923,7 +955,6 @@ qn_status qn_setup(const qn_grid* grid, double beta, int32_t nonlinearity, const
       for (double& l : c->hlam[a]) l /= length * length;
     c->lam_min_sum += c->hlam[a][0];  // lam_1 (Dirichlet) or 0 (Neumann) leads both orderings
   }
-  choose_fast(c);
   // 3D bf16x3: the forward y and z products run folded when both axes fit it
   c->fwdfold = c->prec == QN_PREC_BF16X3 && c->dim == 3 && c->sem_k == 0 && c->bc == QN_BC_DIRICHLET;
   for (int a = 1; a < 3 && c->fwdfold; ++a)
@@ -978,14 +1009,10 @@ qn_status qn_setup(const qn_grid* grid, double beta, int32_t nonlinearity, const
     }
   for (int a = 0; a < c->dim; ++a) {
     if (!c->fast[a]) continue;
-    const FastAxis& f = c->fx[a];
-    fast_tables(f.N, f.Q, f.R, c->bc == QN_BC_NEUMANN, c->ih2[a], c->htw[a], c->hlx[a]);
     c->off_tw[a] = off;
     off += align256(c->htw[a].size() * 8);
     c->off_lx[a] = off;
     off += align256(c->hlx[a].size() * 8);
-    // modes in order instead of the folded products' split order
-    for (int i = 0; i < c->n[a]; ++i) c->hlam[a][i] = c->hlx[a][i + f.off];
   }
   if (c->dim == 2) {  // unused z axis aliases y (never read)
     c->off_S[2] = c->off_S[1];
@@ -1056,7 +1083,8 @@ qn_status qn_bind_workspace(qn_ctx c, void* d_ws, size_t bytes) {
   if (e != hipSuccess) return hip_fail(c, e, "zero workspace");
   for (int a = 0; a < c->dim; ++a) {
     const size_t pp = c->hS[a].size();
-    if (c->prec == QN_PREC_FP64) {
+    if (c->fast[a]) {
+    } else if (c->prec == QN_PREC_FP64) {
       e = hipMemcpyAsync(c->ws + c->off_S[a], c->hS[a].data(), pp * 8, hipMemcpyHostToDevice,
                          c->stream);
     } else if (c->prec == QN_PREC_FP32) {

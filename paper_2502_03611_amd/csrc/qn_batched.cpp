@@ -407,7 +407,15 @@ qn_status qnb_setup_ex(int32_t count, const int32_t* n, const int32_t* ncomp, in
   for (auto& k : c->cls) {
     const double ih = (c->bc == QN_BC_NEUMANN ? k.n - 1 : k.n + 1) / c->length;
     k.ih2 = ih * ih;
-    if (c->bc == QN_BC_NEUMANN) {
+    const int foff = c->bc == QN_BC_NEUMANN ? 0 : 1;
+    k.fx.N = foff ? k.n + 1 : k.n - 1;
+    k.fx.off = foff;
+    k.fast = precision == QN_PREC_FP64 && k.fx.N >= 16 && fast_stages(k.fx.N, &k.fx.Q, &k.fx.R);
+    if (k.fast) {  // modes in order; no dense operand
+      fast_tables(k.fx.N, k.fx.Q, k.fx.R, foff == 0, k.ih2, k.htw, k.hlx);
+      k.hlam.assign((size_t)k.p, k.hlx[k.fx.N - 1]);
+      for (int i = 0; i < k.n; ++i) k.hlam[i] = k.hlx[i + foff];
+    } else if (c->bc == QN_BC_NEUMANN) {
       fold_cosine(k.n, k.ih2, k.ax.bk, k.hS, k.hlam);
     } else {
       if (c->fold)
@@ -443,19 +451,13 @@ qn_status qnb_setup_ex(int32_t count, const int32_t* n, const int32_t* ncomp, in
     }
     k.off_lam = off;
     off += a256((size_t)k.p * 8);
-    const int foff = c->bc == QN_BC_NEUMANN ? 0 : 1;
-    k.fx.N = foff ? k.n + 1 : k.n - 1;
-    k.fx.off = foff;
-    k.fast = precision == QN_PREC_FP64 && k.fx.N >= 16 && fast_stages(k.fx.N, &k.fx.Q, &k.fx.R);
     if (k.fast) {
-      fast_tables(k.fx.N, k.fx.Q, k.fx.R, foff == 0, k.ih2, k.htw, k.hlx);
       k.off_tw = off;
       off += a256(k.htw.size() * 8);
       k.off_lx = off;
       off += a256(k.hlx.size() * 8);
-      for (int i = 0; i < k.n; ++i) k.hlam[i] = k.hlx[i + foff];  // modes in order
     }
-    const size_t te = (size_t)k.ncomp * k.K * pp * c->elem();
+    const size_t te = (size_t)k.ncomp * k.K * k.p * k.p * c->elem();
     k.off_W1 = off;
     off += a256(te);
     k.off_W2 = k.off_W1;  // the factored passes work in place
@@ -561,7 +563,8 @@ qn_status qnb_bind_workspace(qnb_ctx c, void* d_ws, size_t bytes) {
   for (auto& k : c->cls) {
     const size_t pp = k.hS.size();
     if (e != hipSuccess) break;
-    if (c->prec == QN_PREC_FP64) {
+    if (k.fast) {
+    } else if (c->prec == QN_PREC_FP64) {
       e = hipMemcpyAsync(c->ws + k.off_S, k.hS.data(), pp * 8, hipMemcpyHostToDevice, c->stream);
     } else if (c->prec == QN_PREC_FP32) {
       std::vector<float> s32(pp);

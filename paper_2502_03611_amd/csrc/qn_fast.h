@@ -8,11 +8,11 @@
 #include <hip/hip_runtime.h>
 #endif
 
-// Instantiated stage lengths: pairs (Q, R) from the first list (one kernel),
-// or from the second (longer stages, more registers).
-#define QN_FAST_SMALL(X) \
-  X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16) X(17) X(18) X(19) X(20) \
-  X(21) X(22) X(23) X(24) X(25) X(26) X(27) X(28) X(29) X(30) X(31) X(32)
+// Instantiated stage lengths, one kernel per list (a pair (Q, R) needs both in
+// the same list): even lengths to 32, which need at most 128 registers, all
+// lengths to 32, and longer stages.
+#define QN_FAST_EVEN(X) X(4) X(6) X(8) X(10) X(12) X(14) X(16) X(18) X(20) X(22) X(24) X(26) X(28) X(30) X(32)
+#define QN_FAST_ODD(X) X(5) X(7) X(9) X(11) X(13) X(15) X(17) X(19) X(21) X(23) X(25) X(27) X(29) X(31)
 #define QN_FAST_BIG(X) X(20) X(24) X(28) X(30) X(32) X(36) X(40) X(44) X(48) X(50) X(52) X(56) X(60) X(64)
 
 namespace qn {
@@ -183,17 +183,28 @@ __device__ __forceinline__ void irdft(const T (&p)[PB], const T (&q)[PB], T (&ou
 }
 
 template <typename T>
-struct alignas(2 * sizeof(T)) Pair {
+struct alignas(2 * sizeof(T)) Pair {  // twiddle
   T p, q;
 };
 
+// Element at byte offset `off` from a workgroup-uniform address: kept apart
+// so that the address stays in scalar registers.
+template <typename T>
+__device__ __forceinline__ T ld(const T* s, unsigned off) {
+  return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(s) + off);
+}
+template <typename T>
+__device__ __forceinline__ void st(T* s, unsigned off, T v) {
+  *reinterpret_cast<T*>(reinterpret_cast<char*>(s) + off) = v;
+}
+
 // Loads the class b of one line for a stage of length Q over stride R:
-// x[a] = continued x at j = R a + b.  base: element j = off of the workgroup's
-// first line (uniform); voff: this thread's line offset + b es (elements);
-// moff: line offset + (R/2 - b) es.
+// x[a] = continued x at j = R a + b.  base: position 0 of the workgroup's
+// first line (uniform); voff, moff: byte offsets of the line plus b (R/2 - b)
+// axis strides es.
 template <int Q, typename T, typename P>
-__device__ __forceinline__ void load_class(P base, unsigned voff, unsigned moff, int N,
-                                           int R, int b, int off, T sg, long long es, T (&x)[Q]) {
+__device__ __forceinline__ void load_class(P base, unsigned voff, unsigned moff, int N, int R,
+                                           int b, int off, T sg, long long es, T (&x)[Q]) {
   const int rh = R >> 1;
 #pragma unroll
   for (int a = 0; a < Q; ++a) {
@@ -203,18 +214,19 @@ __device__ __forceinline__ void load_class(P base, unsigned voff, unsigned moff,
       // j = 0 (b = 0) and, for odd Q, j = N (b = R/2) vanish for Dirichlet data
       const bool edge = (a == 0 && b == 0) || ((Q & 1) && a == (Q - 1) / 2 && 2 * b == R);
       const bool dead = ((a == 0) || ((Q & 1) && a == (Q - 1) / 2)) && edge && off;
-      x[a] = dead ? T(0) : (T)s[voff];
+      x[a] = dead ? T(0) : ld(s, voff);
     } else {
       // j = R a + b > N continues to 2N - j = (2N - R a - R/2) + (R/2 - b)
       const P s = base + (long long)(2 * N - a * R - rh - off) * es;
       const bool dead = 2 * a == Q && b == 0 && off;
-      x[a] = dead ? T(0) : sg * (T)s[moff];
+      x[a] = dead ? T(0) : sg * ld(s, moff);
     }
   }
 }
 
 // Visits the modes of class k1 held as v[k2], k = k1 + Q k2, that are not
-// duplicates: f(k2, position) with position = the stored index of the mode.
+// duplicates: f(k2, u, mirrored), stored at position u + k1 or, mirrored
+// (2N - k), u + (Q/2 - k1).
 template <int R, typename F>
 __device__ __forceinline__ void for_modes(int Q, int N, int k1, int off, F&& f) {
   const bool self = k1 == 0 || 2 * k1 == Q;  // k and 2N - k lie in the same class
@@ -225,37 +237,28 @@ __device__ __forceinline__ void for_modes(int Q, int N, int k1, int off, F&& f) 
       bool live = true;
       if (k2 == 0) live = !(k1 == 0 && off);
       if ((R & 1) && k2 == (R - 1) / 2) live = !(2 * k1 == Q && off);
-      if (live) f(k2, k1 + Q * k2 - off, false);
+      if (live) f(k2, Q * k2 - off, false);
     } else {
       const bool live = !self || (2 * k2 == R && k1 == 0 && !off);
-      if (live) f(k2, 2 * N - k1 - Q * k2 - off, true);
+      if (live) f(k2, 2 * N - Q * k2 - (Q >> 1) - off, true);
     }
   }
 }
 
-// Stage 1 of class b: DFT over a, twiddle, pairs into LDS at k1 * ks.
-template <int Q, typename T>
-__device__ __forceinline__ void stage1(const T (&x)[Q], const Pair<T>* __restrict__ tw, int b,
-                                       Pair<T>* lds, int ks) {
+// Stage 1 of class b: DFT over a and twiddle; emit(k, p, q) for k = 0 .. Q/2.
+template <int Q, typename T, typename E>
+__device__ __forceinline__ void stage1_emit(const T (&x)[Q], const Pair<T>* __restrict__ tw, int b,
+                                            E&& emit) {
   rdft<Q, 1>(x, [&](int k, T C, T S) {
-    const Pair<T> w = tw[b * k];  // scale * (cos, sin)(2 pi b k / 2N), rotated for Neumann data
-    Pair<T> o;
-    o.p = C * w.q + S * w.p;
-    o.q = C * w.p - S * w.q;
-    lds[k * ks] = o;
+    const Pair<T> w = ld(tw, (unsigned)(b * k) * (unsigned)sizeof(Pair<T>));
+    // w = scale (cos, sin)(2 pi b k / 2N), rotated for Neumann data
+    emit(k, C * w.q + S * w.p, C * w.p - S * w.q);
   });
 }
 
-// Stage 2 of class k1: pairs of b = 0 .. R/2 from LDS (stride bs), DFT over b.
-template <int R, typename T>
-__device__ __forceinline__ void stage2(const Pair<T>* lds, int bs, T (&out)[R]) {
-  T p[R / 2 + 1], q[R / 2 + 1];
-#pragma unroll
-  for (int b = 0; b <= R / 2; ++b) {
-    const Pair<T> v = lds[b * bs];
-    p[b] = v.p;
-    q[b] = v.q;
-  }
+// Stage 2 of class k1: DFT over b of the pairs of b = 0 .. R/2.
+template <int R, typename T, int M>
+__device__ __forceinline__ void stage2(T (&p)[M], const T (&q)[M], T (&out)[R]) {
   p[0] *= T(0.5);
   if constexpr (R % 2 == 0) p[R / 2] *= T(0.5);
   irdft<R, 1>(p, q, out);

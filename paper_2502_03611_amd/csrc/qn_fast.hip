@@ -36,28 +36,59 @@
 
 #include "qn_fast.h"
 #include "qn_internal.h"
-#include "qn_mfma.h"
 
 namespace qn {
 namespace {
 
-#define QN_FAST_SWITCH(len)              \
-  if constexpr (BIG) {                   \
-    switch (len) { QN_FAST_BIG(X) }      \
-  } else {                               \
-    switch (len) { QN_FAST_SMALL(X) }    \
+// Kernel families: stage lengths all even and at most 32, any to 32, longer.
+enum Family { EVEN = 0, ANY = 1, BIG = 2 };
+#define QN_FAST_SWITCH(len)                                \
+  if constexpr (FAM == BIG) {                              \
+    switch (len) { QN_FAST_BIG(X) }                        \
+  } else if constexpr (FAM == ANY) {                       \
+    switch (len) { QN_FAST_EVEN(X) QN_FAST_ODD(X) }        \
+  } else {                                                 \
+    switch (len) { QN_FAST_EVEN(X) }                       \
   }
 
 typedef double T;
 constexpr int FAST_THREADS = 320;  // at most 17 (33) classes of 16 (8) lines
 
 
+// x / d for d > 0: the hardware reciprocal (relative error e0), one Newton
+// step (e0^2) and one residual correction of the quotient (e0^4 and an FP64
+// rounding; e0 is about 2^-23).
+__device__ __forceinline__ double quotient(double x, double d) {
+  double r = __builtin_amdgcn_rcp(d);
+  r = __builtin_fma(__builtin_fma(-d, r, 1.0), r, r);
+  const double q = x * r;
+  return __builtin_fma(__builtin_fma(-d, q, x), r, q);
+}
+
+// Stage 1 of class b into LDS, pair k at k * ks; stage 2 from LDS, pair b at b * bs.
+template <int Q, typename T>
+__device__ __forceinline__ void stage1_lds(const T (&x)[Q], const Pair<T>* __restrict__ tw, int b,
+                                       Pair<T>* lds, int ks) {
+  stage1_emit<Q, T>(x, tw, b, [&](int k, T p, T q) { lds[k * ks] = Pair<T>{p, q}; });
+}
+template <int R, typename T>
+__device__ __forceinline__ void stage2_lds(const Pair<T>* lds, int bs, T (&out)[R]) {
+  T p[R / 2 + 1], q[R / 2 + 1];
+#pragma unroll
+  for (int b = 0; b <= R / 2; ++b) {
+    const Pair<T> v = lds[b * bs];
+    p[b] = v.p;
+    q[b] = v.q;
+  }
+  stage2<R, T>(p, q, out);
+}
+
 // ------------------------------------------------------------- y and z passes
 
 // One transform (DIV = 0) or forward transform, divide and inverse transform
 // (DIV = 1) of the lines of C consecutive x positions, in place.
-template <bool BIG, int DIV>
-__global__ __launch_bounds__(FAST_THREADS, 2) void k_fast_lines(FastArgs a) {
+template <int FAM, int DIV>
+__global__ __launch_bounds__(FAST_THREADS, FAM == EVEN ? 4 : 2) void k_fast_lines(FastArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   Pair<T>* lds = reinterpret_cast<Pair<T>*>(smem);
   const int C = 1 << a.lc;
@@ -72,7 +103,7 @@ __global__ __launch_bounds__(FAST_THREADS, 2) void k_fast_lines(FastArgs a) {
   const int xl = x0 + line < a.nx ? line : a.nx - 1 - x0;  // lanes past the end repeat the last line
   const bool live_x = x0 + line < a.nx;
   T* base = a.out + (long long)(o / a.om) * a.s1 + (long long)(o % a.om) * a.s0 + x0;
-  const unsigned es = (unsigned)a.es;
+  const unsigned eb = (unsigned)a.es * 8, lb = line * 8, xb = xl * 8;  // bytes: axis stride, line
   const Pair<T>* tw = (const Pair<T>*)a.ax.tw;
   const int rh = R >> 1, qh = Q >> 1;
   const bool in1 = c <= rh, in2 = c <= qh;
@@ -81,8 +112,8 @@ __global__ __launch_bounds__(FAST_THREADS, 2) void k_fast_lines(FastArgs a) {
   case L: {                                                                                        \
     if (in1) {                                                                                     \
       T x[L];                                                                                      \
-      load_class<L, T>((const T*)base, xl + c * es, xl + (rh - c) * es, N, R, c, off, sg, a.es, x);       \
-      stage1<L, T>(x, tw, c, lds + (c << a.lc) + line, (rh + 1) << a.lc);                          \
+      load_class<L, T>((const T*)base, xb + c * eb, xb + (rh - c) * eb, N, R, c, off, sg, a.es, x); \
+      stage1_lds<L, T>(x, tw, c, lds + (c << a.lc) + line, (rh + 1) << a.lc);                          \
     }                                                                                              \
     break;                                                                                         \
   }
@@ -94,10 +125,10 @@ __global__ __launch_bounds__(FAST_THREADS, 2) void k_fast_lines(FastArgs a) {
   case L: {                                                                                        \
     if (in2) {                                                                                     \
       T v[L];                                                                                      \
-      stage2<L, T>(lds + (((rh + 1) * c) << a.lc) + line, C, v);                                   \
+      stage2_lds<L, T>(lds + (((rh + 1) * c) << a.lc) + line, C, v);                                   \
       if (live_x)                                                                                  \
-        for_modes<L>(Q, N, c, off, [&](int k2, int pos, bool mir) {                                \
-          base[(long long)pos * a.es + line] = mir ? sg * v[k2] : v[k2];                           \
+        for_modes<L>(Q, N, c, off, [&](int k2, int u, bool mir) {                                  \
+          st(base + (long long)u * a.es, lb + (mir ? qh - c : c) * eb, mir ? sg * v[k2] : v[k2]);  \
         });                                                                                        \
     }                                                                                              \
     break;                                                                                         \
@@ -107,15 +138,15 @@ __global__ __launch_bounds__(FAST_THREADS, 2) void k_fast_lines(FastArgs a) {
   } else {
     const double* coef = a.coef + (long long)inst * a.coef_stride;
     const double scale = coef[0] * (a.cscale ? a.cscale[plane / a.comp_div] : 1.0), beta = coef[1];
-    const double lam0 = a.lamX[x0 + xl] + (a.lamY ? a.lamY[o % a.oy] : 0.0);
+    const double den0 = scale * (a.lamX[x0 + xl] + (a.lamY ? a.lamY[o % a.oy] : 0.0)) + beta;
 #define X(L)                                                                                       \
   case L: {                                                                                        \
     T v[L];                                                                                        \
     if (in2) {                                                                                     \
-      stage2<L, T>(lds + (((rh + 1) * c) << a.lc) + line, C, v);                                   \
-      const double* lam = a.ax.lam + c; /* lam[k], k = 0 .. 2N - 1: continued evenly */            \
+      stage2_lds<L, T>(lds + (((rh + 1) * c) << a.lc) + line, C, v);                                   \
+      const unsigned cb = c * 8; /* lam[k], k = 0 .. 2N - 1: continued evenly */                   \
       _Pragma("unroll") for (int k2 = 0; k2 < L; ++k2) {                                           \
-        v[k2] = quot(v[k2], scale * (lam0 + lam[(long long)Q * k2]) + beta);                       \
+        v[k2] = quotient(v[k2], __builtin_fma(scale, ld(a.ax.lam + Q * k2, cb), den0));            \
       }                                                                                            \
       if (off) { /* the modes k = 0 and k = N do not exist */                                      \
         if (c == 0) {                                                                              \
@@ -126,7 +157,7 @@ __global__ __launch_bounds__(FAST_THREADS, 2) void k_fast_lines(FastArgs a) {
       }                                                                                            \
     }                                                                                              \
     __syncthreads(); /* stage 2 reads done; the same LDS takes the inverse's pairs */              \
-    if (in2) stage1<L, T>(v, tw, c, lds + (c << a.lc) + line, (qh + 1) << a.lc);                   \
+    if (in2) stage1_lds<L, T>(v, tw, c, lds + (c << a.lc) + line, (qh + 1) << a.lc);                   \
     break;                                                                                         \
   }
     QN_FAST_SWITCH(R)
@@ -136,10 +167,10 @@ __global__ __launch_bounds__(FAST_THREADS, 2) void k_fast_lines(FastArgs a) {
   case L: {                                                                                        \
     if (in1) {                                                                                     \
       T v[L];                                                                                      \
-      stage2<L, T>(lds + (((qh + 1) * c) << a.lc) + line, C, v);                                   \
+      stage2_lds<L, T>(lds + (((qh + 1) * c) << a.lc) + line, C, v);                                   \
       if (live_x)                                                                                  \
-        for_modes<L>(R, N, c, off, [&](int k2, int pos, bool mir) {                                \
-          base[(long long)pos * a.es + line] = mir ? sg * v[k2] : v[k2];                           \
+        for_modes<L>(R, N, c, off, [&](int k2, int u, bool mir) {                                  \
+          st(base + (long long)u * a.es, lb + (mir ? rh - c : c) * eb, mir ? sg * v[k2] : v[k2]);  \
         });                                                                                        \
     }                                                                                              \
     break;                                                                                         \
@@ -154,8 +185,8 @@ __global__ __launch_bounds__(FAST_THREADS, 2) void k_fast_lines(FastArgs a) {
 // Transform of rows (the contiguous axis): a.rows rows of the tensor, a.lines
 // per workgroup.  EPI 0: into a.out (padded layout); EPI 1: into the caller's
 // array a.dense (interior layout), stored or subtracted.
-template <bool BIG, int EPI>
-__global__ __launch_bounds__(FAST_THREADS, 2) void k_fast_rows(FastArgs a) {
+template <int FAM, int EPI>
+__global__ __launch_bounds__(FAST_THREADS, FAM == EVEN && EPI == 0 ? 4 : 2) void k_fast_rows(FastArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   Pair<T>* lds = reinterpret_cast<Pair<T>*>(smem);
   const int N = a.ax.N, Q = a.ax.Q, R = a.ax.R, off = a.ax.off;
@@ -167,15 +198,15 @@ __global__ __launch_bounds__(FAST_THREADS, 2) void k_fast_rows(FastArgs a) {
   const int pl0 = r0 / a.oy, pl1 = rlast / a.oy;
   if (a.skip) {  // every instance of the workgroup's rows has stopped
     bool any = false;
-    for (int p = pl0; p <= pl1; ++p) any = any || !a.skip[p % a.inst_mod];
+    for (int pl = pl0; pl <= pl1; ++pl) any = any || !a.skip[pl % a.inst_mod];
     if (!any) return;
   }
   const Pair<T>* tw = (const Pair<T>*)a.ax.tw;
   // offset of row r from the tensor's start, in the padded (in, out) or
   // interior (dense) layout
   auto row_off = [&](int r, long long s1, long long s0, long long ys) {
-    const int p = r / a.oy;
-    return (long long)(p / a.om) * s1 + (long long)(p % a.om) * s0 + (long long)(r - p * a.oy) * ys;
+    const int pl = r / a.oy;
+    return (long long)(pl / a.om) * s1 + (long long)(pl % a.om) * s0 + (long long)(r - pl * a.oy) * ys;
   };
   const int line1 = t / (rh + 1), c1 = t - line1 * (rh + 1);
   const int line2 = t / (qh + 1), c2 = t - line2 * (qh + 1);
@@ -183,16 +214,16 @@ __global__ __launch_bounds__(FAST_THREADS, 2) void k_fast_rows(FastArgs a) {
   const int row2 = r0 + line2;
   const bool in2 = line2 < a.lines && row2 <= rlast;
   const int rp = (rh + 1) | 1;  // odd class stride: stage 2 reads hit distinct banks
+
   const long long b0 = row_off(r0, a.is1, a.is0, a.iys);
   const T* base = a.in + b0;
-  const unsigned lo = (unsigned)(row_off(min(r0 + line1, rlast), a.is1, a.is0, a.iys) - b0);
-
+  const unsigned lo = 8 * (unsigned)(row_off(min(r0 + line1, rlast), a.is1, a.is0, a.iys) - b0);
 #define X(L)                                                                                       \
   case L: {                                                                                        \
     if (in1) {                                                                                     \
       T x[L];                                                                                      \
-      load_class<L, T>(base, lo + c1, lo + rh - c1, N, R, c1, off, sg, 1, x);                 \
-      stage1<L, T>(x, tw, c1, lds + line1 * (qh + 1) * rp + c1, rp);                               \
+      load_class<L, T>(base, lo + 8 * c1, lo + 8 * (rh - c1), N, R, c1, off, sg, 1, x);            \
+      stage1_lds<L, T>(x, tw, c1, lds + line1 * (qh + 1) * rp + c1, rp);                               \
     }                                                                                              \
     break;                                                                                         \
   }
@@ -201,51 +232,36 @@ __global__ __launch_bounds__(FAST_THREADS, 2) void k_fast_rows(FastArgs a) {
   __syncthreads();
   if (!in2) return;
   if (a.skip && a.skip[(row2 / a.oy) % a.inst_mod]) return;
-  const Pair<T>* lp = lds + (line2 * (qh + 1) + c2) * rp;
-  if constexpr (EPI == 0) {
-    T* out = a.out + row_off(row2, a.s1, a.s0, a.ys);
+  T* o = EPI == 0 ? a.out : a.dense;
+  const long long os1 = EPI == 0 ? a.s1 : a.om * a.ds0, os0 = EPI == 0 ? a.s0 : a.ds0,
+                  oys = EPI == 0 ? a.ys : a.dys;
+  const long long o0 = row_off(r0, os1, os0, oys);
+  o += o0;
+  const unsigned ro = 8 * (unsigned)(row_off(row2, os1, os0, oys) - o0);
+  const unsigned vo = ro + 8 * c2, mo = ro + 8 * (qh - c2);
+  const bool sub = EPI == 1 && a.sub != 0;  // a stored solve reads no old values
+  const double us = sub && a.uscale ? *a.uscale : 1.0, sp = a.step;
 #define X(L)                                                                                       \
   case L: {                                                                                        \
-    T v[L];                                                                                        \
-    stage2<L, T>(lp, 1, v);                                                                        \
-    for_modes<L>(Q, N, c2, off,                                                                    \
-                 [&](int k2, int pos, bool mir) { out[pos] = mir ? sg * v[k2] : v[k2]; });         \
-    break;                                                                                         \
-  }
-    QN_FAST_SWITCH(R)
-#undef X
-  } else {
-    double* out = a.dense + row_off(row2, a.om * a.ds0, a.ds0, a.dys);
-    if (a.sub) {
-      const double us = a.uscale ? *a.uscale : 1.0, st = a.step;
-#define X(L)                                                                                       \
-  case L: {                                                                                        \
-    T v[L];                                                                                        \
-    double old[L];                                                                                 \
+    T v[L], old[L];                                                                                \
     /* old values in flight during stage 2, for lengths whose registers allow it */                \
-    if (L <= 32) for_modes<L>(Q, N, c2, off, [&](int k2, int pos, bool) { old[k2] = out[pos]; });  \
-    stage2<L, T>(lp, 1, v);                                                                        \
-    for_modes<L>(Q, N, c2, off, [&](int k2, int pos, bool mir) {                                   \
-      out[pos] = us * (L <= 32 ? old[k2] : out[pos]) - st * (mir ? sg * v[k2] : v[k2]);            \
-    });                                                                                            \
+    if (L <= 32 && sub)                                                                            \
+      for_modes<L>(Q, N, c2, off,                                                                  \
+                   [&](int k2, int u, bool mir) { old[k2] = ld(o + u, mir ? mo : vo); });          \
+    stage2_lds<L, T>(lds + (line2 * (qh + 1) + c2) * rp, 1, v);                                        \
+    if (sub)                                                                                       \
+      for_modes<L>(Q, N, c2, off, [&](int k2, int u, bool mir) {                                   \
+        const double prev = L <= 32 ? old[k2] : ld(o + u, mir ? mo : vo);                          \
+        st(o + u, mir ? mo : vo, us * prev - sp * (mir ? sg * v[k2] : v[k2]));                     \
+      });                                                                                          \
+    else                                                                                           \
+      for_modes<L>(Q, N, c2, off, [&](int k2, int u, bool mir) {                                   \
+        st(o + u, mir ? mo : vo, mir ? sg * v[k2] : v[k2]);                                        \
+      });                                                                                          \
     break;                                                                                         \
   }
-      QN_FAST_SWITCH(R)
+  QN_FAST_SWITCH(R)
 #undef X
-    } else {
-#define X(L)                                                                                       \
-  case L: {                                                                                        \
-    T v[L];                                                                                        \
-    stage2<L, T>(lp, 1, v);                                                                        \
-    for_modes<L>(Q, N, c2, off, [&](int k2, int pos, bool mir) {                                   \
-      out[pos] = mir ? sg * v[k2] : v[k2];                                                         \
-    });                                                                                            \
-    break;                                                                                         \
-  }
-      QN_FAST_SWITCH(R)
-#undef X
-    }
-  }
 }
 
 // Kernels of more than 64 KB of LDS need the limit raised once per device.
@@ -268,10 +284,9 @@ constexpr size_t kLdsTarget = 80 * 1024;  // two workgroups per CU
 
 int round64(int v) { return (v + 63) & ~63; }
 
-template <bool BIG, int DIV>
-hipError_t lines_launch(FastArgs a, int nouter, hipStream_t st) {
+template <typename K>
+hipError_t lines_launch(K kern, int lc, FastArgs a, int nouter, hipStream_t st) {
   const int qh = a.ax.Q / 2 + 1, rh = a.ax.R / 2 + 1;
-  int lc = BIG ? 3 : 4;
   auto bytes = [&](int l) { return (size_t)qh * rh * sizeof(Pair<T>) << l; };
   while (lc > 2 && bytes(lc) > kLdsTarget) --lc;
   // small grids: fewer lines per workgroup until every CU has two
@@ -279,14 +294,13 @@ hipError_t lines_launch(FastArgs a, int nouter, hipStream_t st) {
   a.lc = lc;
   a.xtiles = (a.nx + (1 << lc) - 1) >> lc;
   const int nt = round64(std::max(qh, rh) << lc);
-  auto kern = k_fast_lines<BIG, DIV>;
   hipError_t e = allow_lds(kern, bytes(lc));
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3((unsigned)a.xtiles * nouter), dim3(nt), bytes(lc), st, a);
   return hipGetLastError();
 }
 
-template <bool BIG, int EPI>
+template <int FAM, int EPI>
 hipError_t rows_launch(FastArgs a, hipStream_t st) {
   const int qh = a.ax.Q / 2 + 1, rh = a.ax.R / 2 + 1, nb = std::max(qh, rh);
   const size_t per = (size_t)qh * (rh | 1) * sizeof(Pair<T>);
@@ -295,7 +309,7 @@ hipError_t rows_launch(FastArgs a, hipStream_t st) {
   // small grids: fewer rows per workgroup (but a whole wave) until every CU has two
   lines = std::min(lines, std::max(std::max(1, 64 / nb), a.rows / 512));
   a.lines = lines;
-  auto kern = k_fast_rows<BIG, EPI>;
+  auto kern = k_fast_rows<FAM, EPI>;
   hipError_t e = allow_lds(kern, per * lines);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3((a.rows + lines - 1) / lines), dim3(round64(lines * nb)),
@@ -305,16 +319,32 @@ hipError_t rows_launch(FastArgs a, hipStream_t st) {
 
 }  // namespace
 
+namespace {
+int family(const FastAxis& ax) {
+  return std::max(ax.Q, ax.R) > 32 ? BIG : ((ax.Q | ax.R) & 1) ? ANY : EVEN;
+}
+}  // namespace
+
 hipError_t launch_fast_lines(const FastArgs& a, int nouter, bool divide, hipStream_t st) {
-  const bool big = std::max(a.ax.Q, a.ax.R) > 32;
-  if (big) return divide ? lines_launch<true, 1>(a, nouter, st) : lines_launch<true, 0>(a, nouter, st);
-  return divide ? lines_launch<false, 1>(a, nouter, st) : lines_launch<false, 0>(a, nouter, st);
+  switch (family(a.ax)) {
+    case EVEN:
+      return divide ? lines_launch(k_fast_lines<EVEN, 1>, 4, a, nouter, st)
+                    : lines_launch(k_fast_lines<EVEN, 0>, 4, a, nouter, st);
+    case ANY:
+      return divide ? lines_launch(k_fast_lines<ANY, 1>, 4, a, nouter, st)
+                    : lines_launch(k_fast_lines<ANY, 0>, 4, a, nouter, st);
+    default:
+      return divide ? lines_launch(k_fast_lines<BIG, 1>, 3, a, nouter, st)
+                    : lines_launch(k_fast_lines<BIG, 0>, 3, a, nouter, st);
+  }
 }
 
 hipError_t launch_fast_rows(const FastArgs& a, bool dense, hipStream_t st) {
-  const bool big = std::max(a.ax.Q, a.ax.R) > 32;
-  if (big) return dense ? rows_launch<true, 1>(a, st) : rows_launch<true, 0>(a, st);
-  return dense ? rows_launch<false, 1>(a, st) : rows_launch<false, 0>(a, st);
+  switch (family(a.ax)) {
+    case EVEN: return dense ? rows_launch<EVEN, 1>(a, st) : rows_launch<EVEN, 0>(a, st);
+    case ANY: return dense ? rows_launch<ANY, 1>(a, st) : rows_launch<ANY, 0>(a, st);
+    default: return dense ? rows_launch<BIG, 1>(a, st) : rows_launch<BIG, 0>(a, st);
+  }
 }
 
 }  // namespace qn

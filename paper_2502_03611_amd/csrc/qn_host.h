@@ -403,8 +403,9 @@ inline bool fast_stages(int N, int* Qo, int* Ro) {
     const int r = 2 * N / q;
     const bool small = q <= 32 && r >= 4 && r <= 32;
     if (!small && !(is_big(q) && is_big(r))) continue;
-    // the small kernel (shorter stages, more waves in flight) where it applies
-    const double w = work(q) / q + work(r) / r + (small ? 0.0 : 1e6);
+    // two even lengths, then any to 32, then the longer ones: fewer registers
+    // per thread, so more waves in flight
+    const double w = work(q) / q + work(r) / r + (!small ? 1e6 : ((q | r) & 1) ? 1e3 : 0.0);
     if (w < best) {
       best = w;
       *Qo = q;

@@ -19,8 +19,8 @@ struct Checked {  // stands in for the kernels' element pointers
   std::vector<T>* v;
   long long at;
   Checked operator+(long long d) const { return {v, at + d}; }
-  T& operator[](unsigned i) const {
-    const long long k = at + (long long)i;
+  T& at_byte(unsigned b) const {
+    const long long k = at + (long long)(b / sizeof(T));
     if (k < 0 || k >= (long long)v->size()) {
       std::printf("out of range: %lld of %zu\n", k, v->size());
       std::exit(2);
@@ -29,15 +29,18 @@ struct Checked {  // stands in for the kernels' element pointers
   }
 };
 
+template <typename T>
+T ld(Checked<T> s, unsigned off) { return s.at_byte(off); }
+
 template <int Q, typename T>
 void one_stage1(Checked<T> base, int N, int R, int off, T sg, long long es, int line,
                 const Pair<T>* tw, Pair<T>* lds) {
   const int rh = R / 2;
   for (int b = 0; b <= rh; ++b) {
     T x[Q];
-    load_class<Q, T>(base, (unsigned)(line + b * es), (unsigned)(line + (rh - b) * es), N, R, b,
-                        off, sg, es, x);
-    stage1<Q, T>(x, tw, b, lds + b, rh + 1);
+    load_class<Q, T>(base, (unsigned)sizeof(T) * (unsigned)(line + b * es),
+                     (unsigned)sizeof(T) * (unsigned)(line + (rh - b) * es), N, R, b, off, sg, es, x);
+    stage1_emit<Q, T>(x, tw, b, [&](int k, T p, T q) { lds[k * (rh + 1) + b] = {p, q}; });
   }
 }
 
@@ -46,8 +49,14 @@ void one_stage2(const Pair<T>* lds, int Q, int N, int off, T sg, std::vector<T>&
                 std::vector<int>& hits) {
   for (int k1 = 0; k1 <= Q / 2; ++k1) {
     T v[R];
-    stage2<R, T>(lds + (R / 2 + 1) * k1, 1, v);
-    for_modes<R>(Q, N, k1, off, [&](int k2, int pos, bool mir) {
+    T p[33], q[33];
+    for (int b = 0; b <= R / 2; ++b) {
+      p[b] = lds[(R / 2 + 1) * k1 + b].p;
+      q[b] = lds[(R / 2 + 1) * k1 + b].q;
+    }
+    stage2<R, T>(p, q, v);
+    for_modes<R>(Q, N, k1, off, [&](int k2, int u, bool mir) {
+      const int pos = u + (mir ? Q / 2 - k1 : k1);
       if (pos < 0 || pos >= (int)out.size()) {
         std::printf("mode out of range: %d of %zu\n", pos, out.size());
         std::exit(2);
