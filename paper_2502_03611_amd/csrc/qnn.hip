@@ -196,65 +196,196 @@ __global__ __launch_bounds__(512) void k_conv32(const float* __restrict__ in,
   }
 }
 
+// The same layer for launches with many tiles (batches): one workgroup per CU
+// (125 KB of LDS) keeps all 288 x 32 weights and walks the tiles blockIdx,
+// blockIdx + gridDim, ...; the next tile's input is loaded into registers
+// while the matrix cores work on the current one, and each A fragment serves
+// both halves of the output channels.  k_conv32 stages every tile twice (once
+// per half) with nothing else resident on the CU to cover it.  Same
+// accumulation order, so the same bits.  16 x 255^2: MODE 0 0.37 -> 0.25 ms,
+// MODE 1 0.44 -> 0.30 ms (FP32 matrix-core floor 0.12 ms).
+template <int MODE>
+__global__ __launch_bounds__(512) void k_conv32_tiles(const float* __restrict__ in,
+                                                      const float* __restrict__ wk,
+                                                      const float* __restrict__ bias,
+                                                      const float* __restrict__ zprev,
+                                                      float* __restrict__ out0,
+                                                      float* __restrict__ out1, int H, int W,
+                                                      int tiles_x, int tiles_y, int ntiles) {
+  __shared__ __attribute__((aligned(16))) float s_in[HY * HX * CP];
+  __shared__ __attribute__((aligned(16))) float s_w[288 * 32];
+  constexpr int NI = (HY * HX * 8 + 511) / 512;  // float4 per thread and tile
+  const int tid = threadIdx.x;
+  for (int i = tid; i < 288 * 8; i += 512)
+    reinterpret_cast<float4*>(s_w)[i] = reinterpret_cast<const float4*>(wk)[i];
+  float4 ri[NI];
+  auto gload = [&](int t) {
+    const int tx = t % tiles_x, ty = (t / tiles_x) % tiles_y, b = t / (tiles_x * tiles_y);
+    const int y0 = ty * CT_Y, x0 = tx * CT_X;
+#pragma unroll
+    for (int n = 0; n < NI; ++n) {
+      const int i = tid + n * 512, c4 = i & 7, pix = i >> 3;
+      const int yy = y0 + pix / HX - 1, xx = x0 + pix % HX - 1;
+      ri[n] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (pix < HY * HX && yy >= 0 && yy < H && xx >= 0 && xx < W)
+        ri[n] = reinterpret_cast<const float4*>(in + (((long long)b * H + yy) * W + xx) * 32)[c4];
+    }
+  };
+  const int lane = tid & 63, wave = tid >> 6;
+  const int lr = lane & 15, lk = lane >> 4;
+  int t = blockIdx.x;
+  if (t < ntiles) gload(t);
+  for (; t < ntiles; t += gridDim.x) {
+    __syncthreads();  // every wave is done with the previous tile
+#pragma unroll
+    for (int n = 0; n < NI; ++n) {
+      const int i = tid + n * 512;
+      if (i < HY * HX * 8) *reinterpret_cast<float4*>(&s_in[(i >> 3) * CP + (i & 7) * 4]) = ri[n];
+    }
+    __syncthreads();
+    if (t + (int)gridDim.x < ntiles) gload(t + gridDim.x);
+    const int tx = t % tiles_x, ty = (t / tiles_x) % tiles_y, b = t / (tiles_x * tiles_y);
+    const int y0 = ty * CT_Y, x0 = tx * CT_X;
+    f4v acc[4][2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[i][0] = acc[i][1] = f4v{0, 0, 0, 0};
+    for (int tap = 0; tap < 9; ++tap) {
+      const int dy = tap / 3, dx = tap % 3;
+#pragma unroll
+      for (int c0 = 0; c0 < 32; c0 += 4) {
+        const float* bw = &s_w[(tap * 32 + c0 + lk) * 32 + lr];
+        const float b0 = bw[0], b1 = bw[16];
+#pragma unroll
+        for (int mb = 0; mb < 4; ++mb) {
+          const int r = 2 * wave + (mb >> 1), xh = (mb & 1) * 16;
+          const float a = s_in[((r + dy) * HX + xh + lr + dx) * CP + c0 + lk];
+          acc[mb][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b0, acc[mb][0], 0, 0, 0);
+          acc[mb][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b1, acc[mb][1], 0, 0, 0);
+        }
+      }
+    }
+#pragma unroll
+    for (int mb = 0; mb < 4; ++mb) {
+      const int y = y0 + 2 * wave + (mb >> 1);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int x = x0 + (mb & 1) * 16 + 4 * lk + q;
+        if (y >= H || x >= W) continue;
+        const long long base = (((long long)b * H + y) * W + x) * 32;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int c = 16 * h + lr;
+          const float v = acc[mb][h][q];
+          if (MODE == 0) {
+            const float z = v + bias[c];
+            if (out0) out0[base + c] = z;
+            out1[base + c] = gelu(z);
+          } else {
+            out0[base + c] = v * gelu_grad(zprev[base + c]);
+          }
+        }
+      }
+    }
+  }
+}
+
 constexpr int GT_Y = 8, GT_X = 32;            // weight-gradient pixel tile
 constexpr int GHY = GT_Y + 2, GHX = GT_X + 2;  // with halo
 constexpr int DS = 48;                         // LDS stride of the dz tile
 
-// Partial weight gradient of a 32 -> 32 layer over one 8 x 32 pixel tile:
+// Weight gradient of a 32 -> 32 layer over 8 x 32 pixel tiles:
 // part[co*288 + ci*9 + tap] = sum_p dz[p][co] * act[p + tap][ci] and
 // part[9216 + co] = sum_p dz[p][co].  GEMM M = 32 (co) x N = 288 (tap, ci) x
-// K = 256 pixels; wave w owns row block w&1 and column blocks (w>>1) + 2i.
-__global__ __launch_bounds__(256) void k_conv32_wgrad(const float* __restrict__ act,
-                                                      const float* __restrict__ dz,
-                                                      float* __restrict__ part, int H, int W,
-                                                      int tiles_x, int tiles_y) {
+// K = 256 pixels per tile.  One workgroup per CU (98 KB of LDS) walks the
+// tiles blockIdx, blockIdx + gridDim, ...: the next tile's loads are in
+// registers while the matrix cores work on the current one, each tile's FP32
+// sums are added to FP64 accumulators, and only one partial per half
+// workgroup leaves the chip (one per tile: 151 MB per layer at 16 images of
+// 255^2).  Two wave groups take the two halves of a tile's pixels, so every
+// SIMD holds two waves; wave w of a group owns row block w&1 and column
+// blocks (w>>1) + 2i.  16 x 255^2: 0.47 -> 0.26 ms.
+constexpr int WG_THREADS = 512;
+__global__ __launch_bounds__(WG_THREADS) void k_conv32_wgrad(const float* __restrict__ act,
+                                                             const float* __restrict__ dz,
+                                                             double* __restrict__ part, int H, int W,
+                                                             int tiles_x, int tiles_y, int ntiles) {
   __shared__ __attribute__((aligned(16))) float s_a[GHY * GHX * CP];
   __shared__ __attribute__((aligned(16))) float s_d[GT_Y * GT_X * DS];
+  constexpr int NA = (GHY * GHX * 8 + WG_THREADS - 1) / WG_THREADS;  // float4 per thread and tile
+  constexpr int ND = GT_Y * GT_X * 8 / WG_THREADS;
   const int tid = threadIdx.x;
-  int t = blockIdx.x;
-  const int tx = t % tiles_x;
-  t /= tiles_x;
-  const int ty = t % tiles_y;
-  const int b = t / tiles_y;
-  const int y0 = ty * GT_Y, x0 = tx * GT_X;
-  for (int i = tid; i < GHY * GHX * 8; i += 256) {
-    const int c4 = i & 7, pix = i >> 3;
-    const int hy = pix / GHX, hx = pix % GHX;
-    const int yy = y0 + hy - 1, xx = x0 + hx - 1;
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (yy >= 0 && yy < H && xx >= 0 && xx < W)
-      v = reinterpret_cast<const float4*>(act + (((long long)b * H + yy) * W + xx) * 32)[c4];
-    *reinterpret_cast<float4*>(&s_a[pix * CP + c4 * 4]) = v;
-  }
-  for (int i = tid; i < GT_Y * GT_X * 8; i += 256) {
-    const int c4 = i & 7, pix = i >> 3;
-    const int yy = y0 + pix / GT_X, xx = x0 + pix % GT_X;
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (yy < H && xx < W)
-      v = reinterpret_cast<const float4*>(dz + (((long long)b * H + yy) * W + xx) * 32)[c4];
-    *reinterpret_cast<float4*>(&s_d[pix * DS + c4 * 4]) = v;
-  }
-  __syncthreads();
-
-  const int lane = tid & 63, wave = tid >> 6;
+  float4 ra[NA], rd[ND];
+  auto gload = [&](int t) {
+    const int tx = t % tiles_x, ty = (t / tiles_x) % tiles_y, b = t / (tiles_x * tiles_y);
+    const int y0 = ty * GT_Y, x0 = tx * GT_X;
+#pragma unroll
+    for (int n = 0; n < NA; ++n) {
+      const int i = tid + n * WG_THREADS, c4 = i & 7, pix = i >> 3;
+      const int yy = y0 + pix / GHX - 1, xx = x0 + pix % GHX - 1;
+      ra[n] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (pix < GHY * GHX && yy >= 0 && yy < H && xx >= 0 && xx < W)
+        ra[n] = reinterpret_cast<const float4*>(act + (((long long)b * H + yy) * W + xx) * 32)[c4];
+    }
+#pragma unroll
+    for (int n = 0; n < ND; ++n) {
+      const int i = tid + n * WG_THREADS, c4 = i & 7, pix = i >> 3;
+      const int yy = y0 + pix / GT_X, xx = x0 + pix % GT_X;
+      rd[n] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (yy < H && xx < W)
+        rd[n] = reinterpret_cast<const float4*>(dz + (((long long)b * H + yy) * W + xx) * 32)[c4];
+    }
+  };
+  const int lane = tid & 63, grp = tid >> 8, wave = (tid >> 6) & 3;
   const int lr = lane & 15, lk = lane >> 4;
   const int mb = wave & 1;
-  f4v acc[9];
+  double sum[9][4];
 #pragma unroll
-  for (int i = 0; i < 9; ++i) acc[i] = f4v{0, 0, 0, 0};
-  for (int kp = 0; kp < GT_Y * GT_X; kp += 4) {
-    const int p = kp + lk;
-    const int py = p / GT_X, px = p % GT_X;
-    const float a = s_d[p * DS + mb * 16 + lr];
+  for (int i = 0; i < 9; ++i)
 #pragma unroll
-    for (int i = 0; i < 9; ++i) {
-      const int nb = (wave >> 1) + 2 * i;
-      const int tap = nb >> 1, ci = (nb & 1) * 16 + lr;
-      const float bv = s_a[((py + tap / 3) * GHX + px + tap % 3) * CP + ci];
-      acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, bv, acc[i], 0, 0, 0);
+    for (int q = 0; q < 4; ++q) sum[i][q] = 0.0;
+  double bsum = 0.0;
+  int t = blockIdx.x;
+  if (t < ntiles) gload(t);
+  for (; t < ntiles; t += gridDim.x) {
+    __syncthreads();  // every wave is done with the previous tile
+#pragma unroll
+    for (int n = 0; n < NA; ++n) {
+      const int i = tid + n * WG_THREADS;
+      if (i < GHY * GHX * 8) *reinterpret_cast<float4*>(&s_a[(i >> 3) * CP + (i & 7) * 4]) = ra[n];
     }
+#pragma unroll
+    for (int n = 0; n < ND; ++n) {
+      const int i = tid + n * WG_THREADS;
+      *reinterpret_cast<float4*>(&s_d[(i >> 3) * DS + (i & 7) * 4]) = rd[n];
+    }
+    __syncthreads();
+    if (t + (int)gridDim.x < ntiles) gload(t + gridDim.x);
+    f4v acc[9];
+#pragma unroll
+    for (int i = 0; i < 9; ++i) acc[i] = f4v{0, 0, 0, 0};
+    for (int kp = 128 * grp; kp < 128 * grp + 128; kp += 4) {
+      const int p = kp + lk;
+      const int py = p / GT_X, px = p % GT_X;
+      const float a = s_d[p * DS + mb * 16 + lr];
+#pragma unroll
+      for (int i = 0; i < 9; ++i) {
+        const int nb = (wave >> 1) + 2 * i;
+        const int tap = nb >> 1, ci = (nb & 1) * 16 + lr;
+        const float bv = s_a[((py + tap / 3) * GHX + px + tap % 3) * CP + ci];
+        acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, bv, acc[i], 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 9; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) sum[i][q] += (double)acc[i][q];
+    // bias: 16 threads per channel, 16 pixels each
+    float s = 0.f;
+#pragma unroll
+    for (int p = 0; p < 16; ++p) s += s_d[((tid >> 5) * 16 + p) * DS + (tid & 31)];
+    bsum += (double)s;
   }
-  float* pw = part + (long long)blockIdx.x * QNN_WGRAD_STRIDE;
+  double* pw = part + (2LL * blockIdx.x + grp) * QNN_WGRAD_STRIDE;
 #pragma unroll
   for (int i = 0; i < 9; ++i) {
     const int nb = (wave >> 1) + 2 * i;
@@ -262,13 +393,18 @@ __global__ __launch_bounds__(256) void k_conv32_wgrad(const float* __restrict__ 
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int co = mb * 16 + 4 * lk + q;
-      pw[co * 288 + ci * 9 + tap] = acc[i][q];
+      pw[co * 288 + ci * 9 + tap] = sum[i][q];
     }
   }
-  if (tid < 32) {
-    float s = 0.f;
-    for (int p = 0; p < GT_Y * GT_X; ++p) s += s_d[p * DS + tid];
-    pw[9216 + tid] = s;
+  // bias sums of the group's eight threads per channel, in a fixed order
+  __syncthreads();
+  double* sb = reinterpret_cast<double*>(s_d);
+  sb[tid] = bsum;
+  __syncthreads();
+  if ((tid & 255) < 32) {
+    double b = 0.0;
+    for (int g = 0; g < 8; ++g) b += sb[256 * grp + 32 * g + (tid & 31)];
+    pw[9216 + (tid & 31)] = b;
   }
 }
 
@@ -362,7 +498,11 @@ __global__ __launch_bounds__(1024) void k_sum_partials(const double* __restrict_
   }
 }
 
-// dz4[q][ci] = gelu'(z4[q][ci]) * sum_tap gout[q - tap + 1] * W5[ci][tap]
+// dz4[q][ci] = gelu'(z4[q][ci]) * sum_tap gout[q - tap + 1] * W5[ci][tap].
+// Eight lanes per pixel, lane c4 over channels 4 c4 .. 4 c4 + 3 (16-byte loads
+// and stores; the eight lanes cover the pixel's 128-byte run), weights in
+// registers, grid stride.  Bound by HBM (266 MB at 16 x 255^2): one thread
+// per pixel over all 32 channels took 0.79 ms there, this 0.086 ms.
 __global__ __launch_bounds__(256) void k_out_bwd(const float* __restrict__ gout,
                                                  const float* __restrict__ p5,
                                                  const float* __restrict__ z4,
@@ -370,22 +510,28 @@ __global__ __launch_bounds__(256) void k_out_bwd(const float* __restrict__ gout,
   __shared__ float sw[288];
   for (int i = threadIdx.x; i < 288; i += 256) sw[i] = p5[i];
   __syncthreads();
-  const int p = blockIdx.x * 256 + threadIdx.x;
-  if (p >= npix) return;
-  const int x = p % W, y = (p / W) % H, b = p / (W * H);
-  float g[9];
+  const int c4 = threadIdx.x & 7;
+  float w[4][9];
 #pragma unroll
-  for (int t = 0; t < 9; ++t) {
-    const int yy = y - (t / 3 - 1), xx = x - (t % 3 - 1);
-    g[t] = (yy >= 0 && yy < H && xx >= 0 && xx < W) ? gout[((long long)b * H + yy) * W + xx] : 0.f;
-  }
-  const long long base = (long long)p * 32;
-#pragma unroll 4
-  for (int c = 0; c < 32; ++c) {
-    float s = 0.f;
+  for (int j = 0; j < 4; ++j)
 #pragma unroll
-    for (int t = 0; t < 9; ++t) s += g[t] * sw[c * 9 + t];
-    dz4[base + c] = s * gelu_grad(z4[base + c]);
+    for (int t = 0; t < 9; ++t) w[j][t] = sw[(4 * c4 + j) * 9 + t];
+  const int stride = gridDim.x * 32;
+  for (int p = (blockIdx.x * 256 + threadIdx.x) >> 3; p < npix; p += stride) {
+    const int x = p % W, y = (p / W) % H, b = p / (W * H);
+    const float4 z = reinterpret_cast<const float4*>(z4 + (long long)p * 32)[c4];
+    float s[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < 9; ++t) {
+      const int yy = y - (t / 3 - 1), xx = x - (t % 3 - 1);
+      const float g =
+          (yy >= 0 && yy < H && xx >= 0 && xx < W) ? gout[((long long)b * H + yy) * W + xx] : 0.f;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) s[j] += g * w[j][t];
+    }
+    reinterpret_cast<float4*>(dz4 + (long long)p * 32)[c4] =
+        make_float4(s[0] * gelu_grad(z.x), s[1] * gelu_grad(z.y), s[2] * gelu_grad(z.z),
+                    s[3] * gelu_grad(z.w));
   }
 }
 
@@ -442,16 +588,27 @@ __global__ __launch_bounds__(640) void k_small_wgrad(const float* __restrict__ G
   }
 }
 
-// grads[dst + j] = sum_{w < nparts} part[w * stride + j], j < len (fixed order,
-// accumulated in FP64).
-__global__ __launch_bounds__(256) void k_reduce_parts(const float* __restrict__ part, int nparts,
-                                                      int stride, int len,
-                                                      float* __restrict__ dst) {
-  const int j = blockIdx.x * 256 + threadIdx.x;
-  if (j >= len) return;
+// dst[j] = sum_{w < nparts} part[w * stride + j], j < len, in FP64 and a fixed
+// order: 32 threads per column sum every 32nd partial, then those 32 sums.
+// (One thread per column, 37 workgroups, took 1.3 ms over 4096 partials.)
+template <typename P>
+__global__ __launch_bounds__(1024) void k_reduce_parts(const P* __restrict__ part, int nparts,
+                                                       int stride, int len,
+                                                       float* __restrict__ dst) {
+  __shared__ double red[32][33];
+  const int c = threadIdx.x & 31, g = threadIdx.x >> 5, j = blockIdx.x * 32 + c;
   double s = 0.0;
-  for (int w = 0; w < nparts; ++w) s += part[(long long)w * stride + j];
-  dst[j] = (float)s;
+  if (j < len) {
+#pragma unroll 8
+    for (int w = g; w < nparts; w += 32) s += (double)part[(long long)w * stride + j];
+  }
+  red[g][c] = s;
+  __syncthreads();
+  if (g == 0 && j < len) {
+    double t = 0.0;
+    for (int i = 0; i < 32; ++i) t += red[i][c];
+    dst[j] = (float)t;
+  }
 }
 
 // Layer l (2..4) parameters -> k-major forward weights Wf[tap*32 + ci][co] and
@@ -500,6 +657,13 @@ template <int MODE>
 static void launch_conv32(const float* in, const float* wk, const float* bias, const float* zprev,
                           float* out0, float* out1, int H, int W, int batch, hipStream_t st) {
   const int tx = (W + CT_X - 1) / CT_X, ty = (H + CT_Y - 1) / CT_Y;
+  // at least two tiles per CU keep the tile loop's loads ahead of its
+  // arithmetic; below that the split over output-channel halves fills the chip
+  if ((long long)tx * ty * batch >= 512) {
+    hipLaunchKernelGGL((k_conv32_tiles<MODE>), dim3(256), dim3(512), 0, st, in, wk, bias, zprev, out0,
+                       out1, H, W, tx, ty, tx * ty * batch);
+    return;
+  }
   hipLaunchKernelGGL((k_conv32<MODE>), dim3((unsigned)(2 * tx * ty * batch)), dim3(512), 0, st, in,
                      wk, bias, zprev, out0, out1, H, W, tx, ty);
 }
@@ -744,21 +908,23 @@ hipError_t loss_grad(const Buffers& B, const double* f, const double* v, const d
   hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(1024), 0, st, B.lpart, (int)nb,
                      1.0 / (double)npix, B.loss);
   // layer 5
-  hipLaunchKernelGGL(k_out_bwd, dim3(nb), dim3(256), 0, st, B.gout, B.params + OFF_L5, B.z[3], B.d[0],
+  hipLaunchKernelGGL(k_out_bwd, dim3(std::min(blocks(8LL * npix, 256), 4096u)), dim3(256), 0, st, B.gout, B.params + OFF_L5, B.z[3], B.d[0],
                      H, W, npix);
   const int gtx = (W + GT_X - 1) / GT_X, gty = (H + GT_Y - 1) / GT_Y;
   const int nparts = gtx * gty * batch;
   hipLaunchKernelGGL((k_small_wgrad<0>), dim3((unsigned)nparts), dim3(640), 0, st, B.gout, B.a[3],
                      B.part, H, W, gtx, gty);
-  hipLaunchKernelGGL(k_reduce_parts, dim3(blocks(289, 256)), dim3(256), 0, st, B.part, nparts,
+  hipLaunchKernelGGL(k_reduce_parts<float>, dim3(blocks(289, 32)), dim3(1024), 0, st, B.part, nparts,
                      QNN_SMALL_STRIDE, 289, B.grads + OFF_L5);
   // layers 4, 3, 2: weight gradient from (a[l-1], dz_l), then dz_{l-1}
   int cur = 0;
   for (int l = 3; l >= 1; --l) {
-    hipLaunchKernelGGL(k_conv32_wgrad, dim3((unsigned)nparts), dim3(256), 0, st, B.a[l - 1],
-                       B.d[cur], B.part, H, W, gtx, gty);
-    hipLaunchKernelGGL(k_reduce_parts, dim3(blocks(9248, 256)), dim3(256), 0, st, B.part, nparts,
-                       QNN_WGRAD_STRIDE, 9248, B.grads + layer_offset(l));
+    const int ng = std::min(nparts, QNN_WGRAD_GROUPS);
+    double* part64 = reinterpret_cast<double*>(B.part);
+    hipLaunchKernelGGL(k_conv32_wgrad, dim3((unsigned)ng), dim3(WG_THREADS), 0, st, B.a[l - 1],
+                       B.d[cur], part64, H, W, gtx, gty, nparts);
+    hipLaunchKernelGGL(k_reduce_parts<double>, dim3(blocks(9248, 32)), dim3(1024), 0, st,
+                       (const double*)part64, 2 * ng, QNN_WGRAD_STRIDE, 9248, B.grads + layer_offset(l));
     launch_conv32<1>(B.d[cur], B.wb[l - 1], (const float*)nullptr, B.z[l - 1], B.d[cur ^ 1],
                      (float*)nullptr, H, W, batch, st);
     cur ^= 1;
@@ -766,7 +932,7 @@ hipError_t loss_grad(const Buffers& B, const double* f, const double* v, const d
   // layer 1
   hipLaunchKernelGGL((k_small_wgrad<1>), dim3((unsigned)nparts), dim3(640), 0, st, B.d[cur], B.x0,
                      B.part, H, W, gtx, gty);
-  hipLaunchKernelGGL(k_reduce_parts, dim3(blocks(L1_SIZE, 256)), dim3(256), 0, st, B.part, nparts,
+  hipLaunchKernelGGL(k_reduce_parts<float>, dim3(blocks(L1_SIZE, 32)), dim3(1024), 0, st, B.part, nparts,
                      QNN_SMALL_STRIDE, L1_SIZE, B.grads + OFF_L1);
   return hipGetLastError();
 }

@@ -108,7 +108,11 @@ qn_status qnn_create(int32_t H, int32_t W, int32_t max_batch, qnn_net* out) {
   for (int i = 0; i < 2; ++i) o.d[i] = take(pix * 32 * 4);
   o.out = take(pix * 4);
   o.gout = take(pix * 4);
-  o.part = take(tiles * qnn::QNN_WGRAD_STRIDE * 4);
+  // FP32 partials of the first and last layer per tile, FP64 ones of the
+  // middle layers two per workgroup
+  o.part = take(std::max<size_t>((size_t)tiles * qnn::QNN_SMALL_STRIDE * 4,
+                                 2 * std::min<size_t>(tiles, qnn::QNN_WGRAD_GROUPS) *
+                                     qnn::QNN_WGRAD_STRIDE * 8));
   o.lpart = take(((pix + 255) / 256) * 8);
   o.loss = take(8);
   o.wh = take(qnn::WH_SIZE * 2);

@@ -16,8 +16,9 @@ constexpr int OFF_L1 = 0;
 constexpr int OFF_L5 = L1_SIZE + 3 * 9248;
 __host__ __device__ constexpr int layer_offset(int l) { return l == 0 ? 0 : L1_SIZE + (l - 1) * 9248; }
 
-// Per-workgroup partial strides of the weight-gradient kernels (floats).
-constexpr int QNN_WGRAD_STRIDE = 9248;  // 32 x 288 weights + 32 biases
+// Partial strides of the weight-gradient kernels (elements).
+constexpr int QNN_WGRAD_STRIDE = 9248;  // 32 x 288 weights + 32 biases (FP64 partials)
+constexpr int QNN_WGRAD_GROUPS = 256;   // most workgroups, two partials each
 constexpr int QNN_SMALL_STRIDE = L1_SIZE;
 
 struct Buffers {

@@ -126,6 +126,26 @@ def test_loss_and_gradient_parity(B, H, W):
             o += sz
 
 
+@pytest.mark.parametrize("B,H,W", [(5, 97, 161), (130, 17, 33)])
+def test_gradient_parity_over_many_tiles(B, H, W):
+    """Batches whose ragged tiles outnumber the workgroups that walk them:
+    390 and 780 weight-gradient tiles (at most 256 workgroups) and 210 and
+    520 convolution tiles (the second walks them with 256 workgroups).  FP32 sums
+    of 288 products per activation and of at most 128 pixels per gradient
+    partial, summed in FP64: the bounds of the small images hold."""
+    print(f"net grad {B}x{H}x{W}", flush=True)
+    theta = onet.he_init(13).astype(np.float32).astype(np.float64)
+    f, v, target = inputs(B, H, W, 3)
+    net = Net(H, W, max_batch=B)
+    net.set_params(theta)
+    loss = net.loss_grad(dev(f), dev(v), dev(target))
+    g = net.get_grads()
+    assert np.array_equal(g, (net.loss_grad(dev(f), dev(v), dev(target)), net.get_grads())[1])
+    ref_loss, ref_g = onet.loss_and_grad(theta, onet.features(f, v), target)
+    assert loss == pytest.approx(ref_loss, rel=2e-5)
+    assert rel(g, ref_g) <= 2e-4
+
+
 def test_adam_steps_match_oracle_and_are_deterministic():
     H, W = 12, 34
     theta = onet.he_init(5).astype(np.float32).astype(np.float64)
