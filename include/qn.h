@@ -361,7 +361,9 @@ qn_status qn_probe_mfma(int32_t precision, void* d_sink, size_t bytes, void* str
  * overwritten; the x inverse is timed with a plain store) and keeps the
  * fastest for all later calls.  Launches whose axis runs factored (FP64, see
  * Precision) stay in the list for qn_tile_info and qn_set_tile but are not
- * issued, so they are not timed.  Results do not depend on the tile shapes
+ * issued, so they are not timed; nor are any when the grid's padding makes the
+ * untiled form of the FP64 and FP32 products the faster one, until
+ * qn_set_tile pins a tile (qn_autotune then goes back to that form).  Results do not depend on the tile shapes
  * (bitwise).  Synchronous.  The split-bf16 precisions use dense
  * (unfolded) products; their tiles are tuned the same way. */
 qn_status qn_autotune(qn_ctx ctx);

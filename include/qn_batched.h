@@ -117,7 +117,8 @@ qn_status qnb_set_stream(qnb_ctx ctx, void* stream);
 qn_status qnb_fdm_solve(qnb_ctx ctx, const double* d_R, double scale, double shift, double* d_X);
 
 /* Time every admissible tile shape of every class's mode products on the
- * bound workspace (contents are overwritten) and keep the fastest.
+ * bound workspace (contents are overwritten) and keep the fastest (classes
+ * whose products are not tiled, see qn_autotune, are left alone).
  * Synchronous. */
 qn_status qnb_autotune(qnb_ctx ctx);
 /* Number of classes, and class k's (n, ncomp, instance count, tile_m, tile_n

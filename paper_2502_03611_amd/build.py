@@ -18,7 +18,7 @@ CSRC = os.path.join(HERE, "csrc")
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libqn.so")
 
-SOURCES = ["qn_fast.hip", "qn_gemm_fold.hip", "qn_gemm_bf16.hip", "qn_pointwise.hip", "qn_sem.hip", "qn_probe.hip",
+SOURCES = ["qn_fast.hip", "qn_gemm_strip64.hip", "qn_gemm_strip32.hip", "qn_gemm_fold.hip", "qn_gemm_bf16.hip", "qn_pointwise.hip", "qn_sem.hip", "qn_probe.hip",
            "qn_api.cpp", "qnn.hip", "qnn_api.cpp", "qn_batched.cpp"]
 
 FLAGS = [

@@ -123,8 +123,12 @@ struct qn_ctx_s {
   bool fast[3] = {false, false, false};
   bool any_fast = false, all_fast = false;
   FastAxis fx[3] = {};
-  // element strides of y, z and the component in the tensor at W1 when every
-  // axis is factored (it may reach into W2, which such solves do not use)
+  // FP64 and FP32 products in the strip form (qn_gemm_strip.h) unless tiles are
+  // pinned or tuned
+  bool strip = false;
+  // element strides of y, z and the component in the transform tensors of the
+  // solves that touch interior data only (interior()); with every axis
+  // factored the one tensor at W1 may reach into W2, which they do not use
   long long fs[3] = {0, 0, 0};
   std::vector<double> htw[3], hlx[3];
   size_t off_tw[3] = {0, 0, 0}, off_lx[3] = {0, 0, 0};
@@ -148,6 +152,8 @@ struct qn_ctx_s {
   long long launches[K_COUNT] = {};
 
   size_t elem() const { return prec == QN_PREC_FP64 ? 8 : 4; }
+  // factored and strip passes leave the padding alone: never read, never written
+  bool interior() const { return all_fast || (strip && !tuned); }
   size_t tensor_elems() const { return (size_t)ncomp * p[2] * p[1] * p[0]; }
   template <typename T>
   T* at(size_t off) const { return reinterpret_cast<T*>(ws + off); }
@@ -318,7 +324,7 @@ ResidualArgs residual_args(qn_ctx c, const double* U, const double* F, double* R
   a.bc = c->bc;
   a.partials = c->at<double>(c->off_part);
   a.xfold = (!R_caller && c->xfold) ? c->hp[0] : 0;  // the x product reads it folded
-  if (!R_caller && c->all_fast) {  // the padding is never read: write interior points only
+  if (!R_caller && c->interior()) {
     a.ox = c->n[0];
     a.oy = c->n[1];
     a.oz = c->n[2];
@@ -596,15 +602,23 @@ void choose_fast(qn_ctx c) {
     c->any_fast = c->any_fast || c->fast[a];
     c->all_fast = c->all_fast && c->fast[a];
   }
+  const bool dense[3] = {!c->fast[0], !c->fast[1], !c->fast[2]};
+  c->strip = c->fold && use_strips(c->dim, c->n, c->p, dense, c->ncomp);
+  // An odd number of 128-byte lines per plane, so that the z passes' strides do
+  // not return to the same memory channels (511^3 factored: plane stride 2 MiB
+  // 0.82 ms for the z pass, 2 MiB - 4 KiB 0.70, odd 0.69; the y passes 0.47 and
+  // 0.45 ms).  Split spectral axes reach position bk + floor(n / 2).
+  auto odd_lines = [](long long elems) { return 16 * ((elems / 16) | 1); };
   if (c->all_fast) {
-    // 128-byte rows; an odd number of 128-byte lines per plane, so that the z
-    // passes' strides do not return to the same memory channels (511^3: plane
-    // stride 2 MiB 0.82 ms for the z pass, 2 MiB - 4 KiB 0.70, odd 0.69; the y
-    // passes 0.47 and 0.45 ms)
     c->fs[0] = (c->n[0] + 15) & ~15;
-    const long long lines = c->n[1] * c->fs[0] / 16;
-    c->fs[1] = 16 * (lines | 1);
+    c->fs[1] = odd_lines(c->n[1] * c->fs[0]);
     c->fs[2] = c->n[2] * c->fs[1];
+  } else {
+    const long long full = (long long)c->p[1] * c->p[0];
+    const int ey = c->fast[1] ? c->n[1] : std::max(c->n[1], c->p[1] / 2 + c->n[1] / 2);
+    c->fs[0] = c->p[0];
+    c->fs[1] = std::min(full, odd_lines(ey * c->fs[0]));
+    c->fs[2] = c->p[2] * c->fs[1];
   }
 }
 
@@ -635,8 +649,9 @@ EpiArgs epi_args(qn_ctx c, const double* coef, double* dense) {
 hipError_t fast_pass(qn_ctx c, int axis, double* W, const double* rhs, bool inverse, bool divide,
                      int epi_last, const EpiArgs& ep) {
   const int px = c->p[0], py = c->p[1], pz = c->p[2], nx = c->n[0], ny = c->n[1], nz = c->n[2];
-  const long long ys = c->all_fast ? c->fs[0] : px, zs = c->all_fast ? c->fs[1] : (long long)py * px,
-                  cs = c->all_fast ? c->fs[2] : (long long)pz * py * px;
+  const bool in = c->interior();
+  const long long ys = in ? c->fs[0] : px, zs = in ? c->fs[1] : (long long)py * px,
+                  cs = in ? c->fs[2] : (long long)pz * py * px;
   FastArgs a{};
   a.ax = c->fx[axis];
   a.ax.tw = c->ws + c->off_tw[axis];
@@ -667,7 +682,12 @@ hipError_t fast_pass(qn_ctx c, int axis, double* W, const double* rhs, bool inve
     a.step = ep.step;
     return launch_fast_rows(a, inverse, c->stream);
   }
-  a.nx = c->fast[0] ? nx : px;
+  // the other axes: interior positions, or all of a padded tensor
+  const FoldAxis &x = c->ax[0], &y = c->ax[1];
+  a.ce = c->fast[0] ? nx : in ? x.h + x.odd : px;
+  a.cbk = x.bk;
+  a.co = !c->fast[0] && in ? x.h : 0;
+  a.oe = nz;
   a.coef = ep.coef;
   a.cscale = ep.cscale;
   a.comp_div = 1;
@@ -677,17 +697,88 @@ hipError_t fast_pass(qn_ctx c, int axis, double* W, const double* rhs, bool inve
     a.oy = 1;
     return launch_fast_lines(a, c->ncomp * nz, divide, c->stream);
   }
-  const int ey = c->fast[1] ? ny : py;
   a.es = zs;
-  a.om = a.oy = ey;
+  a.om = a.oy = c->fast[1] || in ? ny : py;
+  a.oe = c->fast[1] ? ny : in ? y.h + y.odd : py;
+  a.obk = y.bk;
   a.s0 = ys;
   a.lamY = c->at<double>(c->off_lam[1]);
-  return launch_fast_lines(a, c->ncomp * ey, divide, c->stream);
+  return launch_fast_lines(a, c->ncomp * a.om, divide, c->stream);
+}
+
+// Strip-form product along `axis` from `in` into `out` (or, x inverse, into
+// ep.dense); rhs: x forward from the caller's right-hand side.
+hipError_t strip_pass(qn_ctx c, int axis, const void* in, void* out, const double* rhs,
+                      bool inverse, bool divide, int epi_last, const EpiArgs& ep) {
+  const int nx = c->n[0], ny = c->n[1], nz = c->n[2];
+  const FoldAxis& ax = c->ax[axis];
+  const FoldOperands f = fold_ops(c, axis);
+  StripArgs a{};
+  a.in = rhs ? (const void*)rhs : in;
+  a.out = out;
+  a.Fe = inverse ? f.Fe : f.FeT;
+  a.Fo = inverse ? f.Fo : f.FoT;
+  a.n = ax.n;
+  a.h = ax.h;
+  a.odd = ax.odd;
+  a.bk = ax.bk;
+  a.skip = ep.skip;
+  a.inst_mod = 1;
+  a.s1 = a.is1 = c->fs[2];
+  a.s0 = a.is0 = c->fs[1];
+  a.om = nz;
+  const bool fp64 = c->prec == QN_PREC_FP64;
+  if (axis == 0) {
+    a.rows = c->ncomp * nz * ny;
+    a.oy = ny;
+    a.ys = a.iys = c->fs[0];
+    if (rhs) {
+      a.iys = nx;
+      a.is0 = (long long)ny * nx;
+      a.is1 = nz * a.is0;
+    }
+    a.dense = ep.dense;
+    a.dys = nx;
+    a.ds0 = (long long)ny * nx;
+    a.sub = epi_last == EPI_SUB_DENSE;
+    a.uscale = ep.uscale;
+    a.step = ep.step;
+    const int kind = inverse ? STRIP_INV : STRIP_FWD;
+    return fp64 ? launch_strip64(true, kind, a, c->stream)
+                : launch_strip32(true, kind, rhs != nullptr, a, c->stream);
+  }
+  const FoldAxis& x = c->ax[0];
+  a.ce = c->fast[0] ? nx : x.h + x.odd;
+  a.cbk = x.bk;
+  a.co = c->fast[0] ? 0 : x.h;
+  a.lamX = ep.lamX;
+  a.lamM = c->at<double>(c->off_lam[axis]);
+  a.coef = ep.coef;
+  a.cscale = ep.cscale;
+  a.comp_div = 1;
+  if (axis == 1) {  // planes of every component; 2D with the divide: plane = component
+    a.es = c->fs[0];
+    a.nouter = c->ncomp * nz;
+    a.oy = 1;
+    a.oe = nz;
+  } else {
+    const FoldAxis& y = c->ax[1];
+    a.es = c->fs[1];
+    a.nouter = c->ncomp * ny;
+    a.om = a.oy = ny;
+    a.oe = c->fast[1] ? ny : y.h + y.odd;
+    a.obk = y.bk;
+    a.s0 = c->fs[0];
+    a.lamY = c->at<double>(c->off_lam[1]);
+  }
+  const int kind = inverse ? STRIP_INV : divide ? STRIP_DIV : STRIP_FWD;
+  return fp64 ? launch_strip64(false, kind, a, c->stream)
+              : launch_strip32(false, kind, false, a, c->stream);
 }
 
 // skip (device int, may be NULL): when set, every launch of the solve exits
 // at once (the quasi-Newton loop has stopped).  rhs: the caller's right-hand
-// side when it is not in W1 (all axes factored).
+// side when it is not in W1 (interior() solves).
 hipError_t solve_ws(qn_ctx c, const double* coef, double* dense, int epi_last,
                     const int* skip = nullptr, const double* uscale = nullptr,
                     const double* rhs = nullptr) {
@@ -696,36 +787,29 @@ hipError_t solve_ws(qn_ctx c, const double* coef, double* dense, int epi_last,
   ep.uscale = uscale;
   FoldStep st[6];
   const int ns = solve_plan(c, ep, epi_last, st);
-  if (c->any_fast) {
+  if (c->any_fast || c->interior()) {
     // the plan's launches in order, factored axes in place on the current
-    // tensor, dense ones into the other; the last forward axis, when
+    // tensor, the others into the other tensor; the last forward axis, when
     // factored, takes the divide and its inverse in the same pass
     const int last = c->dim - 1;
     void* cur = c->ws + c->off_W1;
     void* other = c->ws + c->off_W2;
-    static const int kFwd[3] = {K_GEMM_X, K_GEMM_YZ, K_GEMM_YZ};
     for (int i = 0; i < 2 * c->dim; ++i) {
       const bool inverse = i >= c->dim;
       const int axis = inverse ? 2 * c->dim - 1 - i : i;
       if (c->fast[axis] && inverse && axis == last) continue;
-      hipError_t e;
-      if (c->fast[axis]) {
-        const bool divide = axis == last;
-        const int kid = divide ? K_GEMM_DIVIDE
-                               : inverse ? (axis == 0 ? K_GEMM_X_UPDATE : K_GEMM_YZ_INV) : kFwd[axis];
-        e = timed(c, kid, [&] {
-          return fast_pass(c, axis, (double*)cur, axis == 0 && !inverse ? rhs : nullptr, inverse, divide,
-                           epi_last, ep);
-        });
-      } else {
+      const double* r = axis == 0 && !inverse ? rhs : nullptr;
+      const bool divide = axis == last && !inverse;
+      const hipError_t e = timed(c, st[i].kid, [&] {
+        if (c->fast[axis]) return fast_pass(c, axis, (double*)cur, r, inverse, divide, epi_last, ep);
+        if (c->interior()) return strip_pass(c, axis, cur, other, r, inverse, divide, epi_last, ep);
         FoldStep f = st[i];
         f.in = cur;
         f.out = other;
-        const FoldTile t = step_tile(c, f, i);
-        e = timed(c, f.kid, [&] { return run_step(c, f, t); });
-        std::swap(cur, other);
-      }
+        return run_step(c, f, step_tile(c, f, i));
+      });
       if (e != hipSuccess) return e;
+      if (!c->fast[axis]) std::swap(cur, other);
     }
     return hipSuccess;
   }
@@ -1234,14 +1318,14 @@ qn_status qn_fdm_solve(qn_ctx c, const double* d_R, double scale, double shift, 
                 scale * c->lam_min_sum + shift);
   double* coef = c->at<double>(c->off_coef);
   hipError_t e = launch_set_coef(coef, scale, shift, c->stream);
-  if (e == hipSuccess && !c->all_fast)  // the factored x pass reads d_R itself
+  if (e == hipSuccess && !c->interior())  // else the x pass reads d_R itself
     e = timed(c, K_PAD_COPY, [&] {
       return launch_pad_copy(d_R, c->ws + c->off_W1, transform_storage(c->prec), c->ncomp,
                              c->n[0], c->n[1], c->n[2], c->p[0], c->p[1], c->p[2], c->stream,
                              c->xfold ? c->hp[0] : 0);
     });
   if (e == hipSuccess)
-    e = solve_ws(c, coef, d_X, EPI_STORE_DENSE, nullptr, nullptr, c->all_fast ? d_R : nullptr);
+    e = solve_ws(c, coef, d_X, EPI_STORE_DENSE, nullptr, nullptr, c->interior() ? d_R : nullptr);
   if (e != hipSuccess) return hip_fail(c, e, "fdm solve launch");
   return QN_OK;
 }
@@ -1421,6 +1505,10 @@ qn_status qn_eigen_iterate(qn_ctx c, double* d_U, double rtol, int32_t max_iter,
 qn_status qn_autotune(qn_ctx c) {
   qn_status s = check_ctx(c, true);
   if (s != QN_OK) return s;
+  if (c->all_fast || c->strip) {  // no tiled launch is issued: drop pinned tiles
+    c->tuned = false;
+    return QN_OK;
+  }
   hipEvent_t t0 = nullptr, t1 = nullptr;
   hipError_t e = hipEventCreate(&t0);
   if (e == hipSuccess) e = hipEventCreate(&t1);

@@ -53,6 +53,8 @@ struct Cls {
   FastAxis fx{};
   std::vector<double> htw, hlx;
   size_t off_tw = 0, off_lx = 0;
+  bool strip = false;         // dense products in the strip form (qn_gemm_strip.h)
+  bool interior() const { return fast || strip; }  // passes that leave the padding alone
   double ih2 = 0.0;           // 1 / h^2 of both axes
   double lam_min = 0.0;       // smallest eigenvalue of the solve operator without the shift
   hipStream_t s = nullptr;    // per-class stream (default priority)
@@ -169,7 +171,8 @@ hipError_t class_fast_solve(qnb_ctx c, const Cls& k, const double* rhs, bool sub
   hipError_t e = launch_fast_rows(a, false, s);
   if (e != hipSuccess) return e;
   FastArgs b = a;
-  b.nx = k.n;
+  b.ce = k.n;
+  b.oe = planes;
   b.es = k.p;
   b.oy = 1;
   b.coef = ep.coef;
@@ -188,6 +191,79 @@ hipError_t class_fast_solve(qnb_ctx c, const Cls& k, const double* rhs, bool sub
   a.sub = sub;
   a.step = ep.step;
   return launch_fast_rows(a, true, s);
+}
+
+// The strip-form solve of class k, from W1 or from the class block of a
+// caller's pool.
+hipError_t class_strip_solve(qnb_ctx c, const Cls& k, const double* rhs, bool sub, const EpiArgs& ep,
+                             hipStream_t s) {
+  const int planes = k.ncomp * k.K;
+  const long long sl = (long long)k.p * k.p, nn = (long long)k.n * k.n;
+  const FoldOperands f = fops(c, k);
+  void* W1 = c->ws + k.off_W1;
+  void* W2 = c->ws + k.off_W2;
+  auto launch = [&](bool rows, int kind, const StripArgs& a) {
+    return c->prec == QN_PREC_FP64 ? launch_strip64(rows, kind, a, s)
+                                   : launch_strip32(rows, kind, a.in == rhs, a, s);
+  };
+  StripArgs a{};
+  a.n = k.ax.n;
+  a.h = k.ax.h;
+  a.odd = k.ax.odd;
+  a.bk = k.ax.bk;
+  a.skip = ep.skip;
+  a.inst_mod = ep.inst_mod;
+  a.om = a.oe = a.nouter = planes;
+  a.s0 = sl;
+  a.ce = k.ax.h + k.ax.odd;
+  a.cbk = k.ax.bk;
+  a.co = k.ax.h;
+  a.comp_div = 1;
+  // x forward
+  StripArgs r = a;
+  r.in = rhs ? (const void*)rhs : W1;
+  r.out = W2;
+  r.Fe = f.FeT;
+  r.Fo = f.FoT;
+  r.rows = planes * k.n;
+  r.oy = k.n;
+  r.ys = k.p;
+  r.is0 = rhs ? nn : sl;
+  r.iys = rhs ? k.n : k.p;
+  hipError_t e = launch(true, STRIP_FWD, r);
+  if (e != hipSuccess) return e;
+  // y forward + divide, y inverse
+  a.oy = 1;
+  a.es = k.p;
+  a.in = W2;
+  a.out = W1;
+  a.Fe = f.FeT;
+  a.Fo = f.FoT;
+  a.lamM = a.lamX = ep.lamX;
+  a.coef = ep.coef;
+  a.coef_stride = ep.coef_stride;
+  a.cscale = ep.cscale;
+  if (ep.cscale) a.comp_div = ep.comp_div;
+  e = launch(false, STRIP_DIV, a);
+  if (e != hipSuccess) return e;
+  a.in = W1;
+  a.out = W2;
+  a.Fe = f.Fe;
+  a.Fo = f.Fo;
+  e = launch(false, STRIP_INV, a);
+  if (e != hipSuccess) return e;
+  // x inverse into the pool
+  r.in = W2;
+  r.is0 = sl;
+  r.iys = k.p;
+  r.Fe = f.Fe;
+  r.Fo = f.Fo;
+  r.dense = ep.dense;
+  r.ds0 = nn;
+  r.dys = k.n;
+  r.sub = sub;
+  r.step = ep.step;
+  return launch(true, STRIP_INV, r);
 }
 
 // Shift rule of the finalize kernel for a qn_beta_mode.
@@ -212,7 +288,7 @@ hipError_t class_iteration(qnb_ctx c, Cls& k, double* U, const double* F, double
   a.r_cstride = (long long)k.K * k.p * k.p;
   a.r_zstride = k.p * k.p;
   a.r_ystride = k.p;
-  a.ox = a.oy = k.fast ? k.n : k.p;  // the factored passes never read the padding
+  a.ox = a.oy = k.interior() ? k.n : k.p;
   a.oz = k.K;
   a.nx = a.ny = k.n;
   a.nz = k.K;
@@ -242,6 +318,7 @@ hipError_t class_iteration(qnb_ctx c, Cls& k, double* U, const double* F, double
   const GemmOperands S = ops(c, k);
   EpiArgs ep = epi_for(c, k, U);
   if (k.fast) return class_fast_solve(c, k, nullptr, true, ep, s);
+  if (k.strip) return class_strip_solve(c, k, nullptr, true, ep, s);
   const int rows = k.ncomp * k.K * k.p;
   const int slabs = k.ncomp * k.K;
   const long long sl = (long long)k.p * k.p;
@@ -465,7 +542,11 @@ qn_status qnb_setup_ex(int32_t count, const int32_t* n, const int32_t* ncomp, in
       k.off_W2 = off;
       off += a256(te);
     }
-    k.bpi = residual_max_blocks(k.fast ? k.n : k.p, k.fast ? k.n : k.p, 1, RESIDUAL_PLANAR_ROWS, true);
+    const int ext[2] = {k.n, k.n}, pad[2] = {k.p, k.p};
+    const bool dense[2] = {true, true};
+    k.strip = c->fold && !k.fast && use_strips(2, ext, pad, dense, k.ncomp * k.K);
+    const int ex = k.interior() ? k.n : k.p;
+    k.bpi = residual_max_blocks(ex, ex, 1, RESIDUAL_PLANAR_ROWS, true);
     k.off_part = off;
     off += a256((size_t)k.bpi * k.K * 4 * sizeof(double));
     k.off_state = off;
@@ -611,7 +692,7 @@ qn_status qnb_autotune(qnb_ctx c) {
   if (e != hipSuccess) return hip_bad(c, e, "autotune events");
   const int cand[3] = {32, 64, 128};
   for (auto& k : c->cls) {
-    if (k.fast) continue;  // no dense product to tune
+    if (k.interior()) continue;  // no tiled launch is issued
     EpiArgs ep = epi_for(c, k, nullptr);
     ep.skip = nullptr;  // time every tile
     const GemmOperands S = ops(c, k);
@@ -712,12 +793,14 @@ qn_status qnb_fdm_solve(qnb_ctx c, const double* d_R, double scale, double shift
     if (e != hipSuccess) break;
     void* W1 = c->ws + k.off_W1;
     void* W2 = c->ws + k.off_W2;
-    if (k.fast) {
+    if (k.interior()) {
       EpiArgs ep = epi_for(c, k, d_X);
       ep.skip = nullptr;  // every instance
       ep.coef = coef;
       ep.coef_stride = 0;
-      e = class_fast_solve(c, k, d_R + k.off_field, false, ep, c->stream);
+      const double* r = d_R + k.off_field;
+      e = k.fast ? class_fast_solve(c, k, r, false, ep, c->stream)
+                 : class_strip_solve(c, k, r, false, ep, c->stream);
       continue;
     }
     // the class block (ncomp, K, n, n) -> (ncomp, K, P, P), zero padding

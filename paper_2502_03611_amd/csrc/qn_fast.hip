@@ -99,10 +99,12 @@ __global__ __launch_bounds__(FAST_THREADS, FAM == EVEN ? 4 : 2) void k_fast_line
   const int N = a.ax.N, Q = a.ax.Q, R = a.ax.R, off = a.ax.off;
   const T sg = off ? T(-1) : T(1);
   const int t = threadIdx.x, line = t & (C - 1), c = t >> a.lc;
-  const int x0 = xt * C;
-  const int xl = x0 + line < a.nx ? line : a.nx - 1 - x0;  // lanes past the end repeat the last line
-  const bool live_x = x0 + line < a.nx;
-  T* base = a.out + (long long)(o / a.om) * a.s1 + (long long)(o % a.om) * a.s0 + x0;
+  const bool lower = xt < a.xsplit;  // even and odd modes of a dense x axis, or all of a natural one
+  const int x0 = lower ? xt * C : a.cbk + (xt - a.xsplit) * C, lim = lower ? a.ce : a.cbk + a.co;
+  const int xl = x0 + line < lim ? line : lim - 1 - x0;  // lanes past the end repeat the last line
+  const bool live_x = x0 + line < lim;
+  const int oi = o % a.om, opos = oi < a.oe ? oi : a.obk + oi - a.oe;
+  T* base = a.out + (long long)(o / a.om) * a.s1 + (long long)opos * a.s0 + x0;
   const unsigned eb = (unsigned)a.es * 8, lb = line * 8, xb = xl * 8;  // bytes: axis stride, line
   const Pair<T>* tw = (const Pair<T>*)a.ax.tw;
   const int rh = R >> 1, qh = Q >> 1;
@@ -138,7 +140,7 @@ __global__ __launch_bounds__(FAST_THREADS, FAM == EVEN ? 4 : 2) void k_fast_line
   } else {
     const double* coef = a.coef + (long long)inst * a.coef_stride;
     const double scale = coef[0] * (a.cscale ? a.cscale[plane / a.comp_div] : 1.0), beta = coef[1];
-    const double den0 = scale * (a.lamX[x0 + xl] + (a.lamY ? a.lamY[o % a.oy] : 0.0)) + beta;
+    const double den0 = scale * (a.lamX[x0 + xl] + (a.lamY ? a.lamY[opos] : 0.0)) + beta;
 #define X(L)                                                                                       \
   case L: {                                                                                        \
     T v[L];                                                                                        \
@@ -290,9 +292,11 @@ hipError_t lines_launch(K kern, int lc, FastArgs a, int nouter, hipStream_t st) 
   auto bytes = [&](int l) { return (size_t)qh * rh * sizeof(Pair<T>) << l; };
   while (lc > 2 && bytes(lc) > kLdsTarget) --lc;
   // small grids: fewer lines per workgroup until every CU has two
-  while (lc > 2 && (long long)((a.nx + (1 << lc) - 1) >> lc) * nouter < 512) --lc;
+  auto tiles = [&](int cols, int l) { return (cols + (1 << l) - 1) >> l; };
+  while (lc > 2 && (long long)(tiles(a.ce, lc) + tiles(a.co, lc)) * nouter < 512) --lc;
   a.lc = lc;
-  a.xtiles = (a.nx + (1 << lc) - 1) >> lc;
+  a.xsplit = tiles(a.ce, lc);
+  a.xtiles = a.xsplit + tiles(a.co, lc);
   const int nt = round64(std::max(qh, rh) << lc);
   hipError_t e = allow_lds(kern, bytes(lc));
   if (e != hipSuccess) return e;

@@ -437,4 +437,31 @@ inline void fast_tables(int N, int Q, int R, bool neumann, double ih2, std::vect
   for (int k = N + 1; k < 2 * N; ++k) lam[k] = lam[2 * N - k];
 }
 
+// Whether the dense products of a solve take the strip form (qn_gemm_strip.h):
+// at least 2^20 values (below that a strip launch leaves the chip to too few
+// waves: 200^2 FP64 0.046 against 0.036 ms of tile launches) and at least 1.25
+// times as many matrix-core operations in the padded tiles as in the strips
+// (whose rate is 0.8-0.9 of the tiles': 255^3 0.73 against 0.67 ms at a ratio
+// of 1.0, 400^3 4.1 against 6.6 ms at 1.35, 200^3 0.41 against 0.52 ms at 1.9).  n, p, dense: extents, padded
+// extents and which axes have a dense product.
+inline bool use_strips(int dim, const int* n, const int* p, const bool* dense, int fields) {
+  double values = fields, tiles = 0.0, strips = 0.0;
+  for (int a = 0; a < dim; ++a) values *= n[a];
+  if (values < 1048576.0) return false;
+  auto up16 = [](int v) { return (v + 15) / 16 * 16; };
+  for (int a = 0; a < dim; ++a) {
+    if (!dense[a]) continue;
+    const int ne = (n[a] + 1) / 2;
+    double t = (double)p[a] * up16(ne), s = 2.0 * up16(ne) * (ne + 3);
+    for (int b = 0; b < dim; ++b)
+      if (b != a) {
+        t *= p[b];
+        s *= b == 0 ? 2.0 * up16((n[0] + 1) / 2) : (double)n[b];
+      }
+    tiles += t;
+    strips += s;
+  }
+  return tiles > 1.25 * strips;
+}
+
 }  // namespace qn

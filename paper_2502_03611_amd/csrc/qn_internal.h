@@ -174,6 +174,47 @@ hipError_t launch_fold(int kind, int prec, const FoldOperands& f, const void* in
                        const FoldAxis& ax, int ncols, int batch, long long bstride, int rows,
                        int epi, const EpiArgs& ep, const FoldTile& t, hipStream_t st);
 
+// Strip form of the folded mode products (qn_gemm_strip.h): interior data
+// only, any extents, the same bits as the tile form.  Transformed axis: n, h,
+// odd, bk as FoldAxis; Fe, Fo: FeT, FoT (forward) or Fe, Fo (inverse).
+// Left (y, z): outer indices o < nouter at (o / om) s1 + pos(o % om) s0 (pos:
+// oi for oi < oe, else obk + oi - oe: a split y axis), columns (x positions)
+// [0, ce) and [cbk, cbk + co), axis stride es.  plane = o / oy (left), r / oy
+// (right): instance plane % inst_mod, component plane / comp_div.
+// Right (x): rows r, plane r / oy, row r % oy; plane p of the input at
+// (p / om) is1 + (p % om) is0, row stride iys (output s1, s0, ys); the inverse
+// writes the caller's array dense (ds0 per plane, dys per row).
+enum StripKind : int { STRIP_FWD = 0, STRIP_DIV = 1, STRIP_INV = 2 };
+struct StripArgs {
+  const void* in;
+  void* out;
+  const void* Fe;
+  const void* Fo;
+  int n, h, odd, bk;
+  int nouter, om, oy, oe, obk;
+  int ce, cbk, co;
+  int rows;
+  long long s1, s0, ys, es;
+  long long is1, is0, iys;
+  double* dense;
+  long long ds0, dys;
+  int sub;
+  const double* uscale;
+  double step;
+  const double* lamM;
+  const double* lamX;
+  const double* lamY;
+  const double* coef;
+  int coef_stride;
+  const double* cscale;
+  int comp_div;
+  const int* skip;
+  int inst_mod;
+  int ge, groups, strips, mtiles;  // filled by the launchers
+};
+hipError_t launch_strip64(bool rows, int kind, const StripArgs& a, hipStream_t st);
+hipError_t launch_strip32(bool rows, int kind, bool in64, const StripArgs& a, hipStream_t st);
+
 // Factored mode products (qn_fast.hip): axes whose doubled interval count 2N
 // (N = n + 1 Dirichlet, n - 1 Neumann, finite differences) is a product Q R of
 // instantiated stage lengths; FP64.  tw: device pairs sqrt(2/N) (cos, sin)(pi
@@ -184,11 +225,11 @@ struct FastAxis {
   const void* tw;
   const double* lam;
 };
-// Line passes (launch_fast_lines), in place on `out`: nx lines (x positions)
-// of each of the nouter outer indices o, line (o, x) at element (o / om) s1 +
-// (o % om) s0 + x, axis stride es; plane = o / oy.  With the divide:
-// eigenvalues lamX[x] + lamY[o % oy] of the other axes, coefficients as
-// EpiArgs (instance plane % inst_mod, component plane / comp_div).
+// Line passes (launch_fast_lines), in place on `out`: lines at x positions
+// [0, ce) and [cbk, cbk + co) of each of the nouter outer indices o, line
+// (o, x) at element (o / om) s1 + pos(o % om) s0 + x (pos as in StripArgs),
+// axis stride es; plane = o / oy.  With the divide: eigenvalues lamX[x] +
+// lamY[pos] of the other axes, coefficients as EpiArgs (instance plane % inst_mod, component plane / comp_div).
 // Row passes (launch_fast_rows): rows r of the contiguous axis, plane r / oy,
 // row y = r % oy; plane p at (p / om) s1 + (p % om) s0, row stride ys (input:
 // is1, is0, iys; the caller's array dense: ds0 per plane, dys per row), stored
@@ -197,8 +238,8 @@ struct FastArgs {
   FastAxis ax;
   const double* in;
   double* out;
-  int nx, rows;
-  int oy, om;
+  int ce, cbk, co, rows;
+  int oy, om, oe, obk;
   long long s1, s0, ys, es;
   long long is1, is0, iys;
   double* dense;
@@ -214,7 +255,7 @@ struct FastArgs {
   const double* lamY;
   const int* skip;
   int inst_mod;
-  int lc, xtiles, lines;  // filled by the launchers
+  int lc, xtiles, xsplit, lines;  // filled by the launchers
 };
 hipError_t launch_fast_lines(const FastArgs& a, int nouter, bool divide, hipStream_t st);
 hipError_t launch_fast_rows(const FastArgs& a, bool dense, hipStream_t st);
