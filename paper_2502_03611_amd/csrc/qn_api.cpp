@@ -134,7 +134,7 @@ struct qn_ctx_s {
   size_t off_tw[3] = {0, 0, 0}, off_lx[3] = {0, 0, 0};
   // workspace layout (byte offsets)
   size_t off_S[3] = {0, 0, 0}, off_Slo[3] = {0, 0, 0}, off_Slo2[3] = {0, 0, 0}, off_lam[3] = {0, 0, 0};
-  size_t off_W1 = 0, off_W2 = 0, off_part = 0, off_scal = 0, off_coef = 0, off_cscale = 0,
+  size_t off_W1 = 0, off_W2 = 0, off_part = 0, off_scal = 0, off_cscale = 0,
          need = 0;
   double step = 1.0;  // qn_iterate: U -= step * dU
   double gs[4] = {0.0, 0.0, 0.0, 0.0};  // Gray-Scott: D_A, D_S, rho, mu
@@ -622,7 +622,7 @@ void choose_fast(qn_ctx c) {
   }
 }
 
-EpiArgs epi_args(qn_ctx c, const double* coef, double* dense) {
+EpiArgs epi_args(qn_ctx c, const Coef& coef, double* dense) {
   EpiArgs ep{};
   ep.inst_mod = 1;
   ep.coef = coef;
@@ -779,7 +779,7 @@ hipError_t strip_pass(qn_ctx c, int axis, const void* in, void* out, const doubl
 // skip (device int, may be NULL): when set, every launch of the solve exits
 // at once (the quasi-Newton loop has stopped).  rhs: the caller's right-hand
 // side when it is not in W1 (interior() solves).
-hipError_t solve_ws(qn_ctx c, const double* coef, double* dense, int epi_last,
+hipError_t solve_ws(qn_ctx c, const Coef& coef, double* dense, int epi_last,
                     const int* skip = nullptr, const double* uscale = nullptr,
                     const double* rhs = nullptr) {
   EpiArgs ep = epi_args(c, coef, dense);
@@ -1130,8 +1130,6 @@ qn_status qn_setup(const qn_grid* grid, double beta, int32_t nonlinearity, const
   off += align256((size_t)c->max_blocks * 4 * sizeof(double));
   c->off_scal = off;
   off += align256(sizeof(DevScalars));
-  c->off_coef = off;
-  off += align256(2 * sizeof(double));
   c->off_cscale = off;  // Gray-Scott: per-component diffusion {D_A, D_S}
   off += align256(2 * sizeof(double));
   c->need = off;
@@ -1316,16 +1314,16 @@ qn_status qn_fdm_solve(qn_ctx c, const double* d_R, double scale, double shift, 
   if (scale * c->lam_min_sum + shift <= 0.0)
     return fail(QN_ERR_INVALID, "scale*lam_min(A_h) + shift = %g <= 0: singular or indefinite",
                 scale * c->lam_min_sum + shift);
-  double* coef = c->at<double>(c->off_coef);
-  hipError_t e = launch_set_coef(coef, scale, shift, c->stream);
-  if (e == hipSuccess && !c->interior())  // else the x pass reads d_R itself
+  hipError_t e = hipSuccess;
+  if (!c->interior())  // else the x pass reads d_R itself
     e = timed(c, K_PAD_COPY, [&] {
       return launch_pad_copy(d_R, c->ws + c->off_W1, transform_storage(c->prec), c->ncomp,
                              c->n[0], c->n[1], c->n[2], c->p[0], c->p[1], c->p[2], c->stream,
                              c->xfold ? c->hp[0] : 0);
     });
   if (e == hipSuccess)
-    e = solve_ws(c, coef, d_X, EPI_STORE_DENSE, nullptr, nullptr, c->interior() ? d_R : nullptr);
+    e = solve_ws(c, Coef{nullptr, 0, scale, shift}, d_X, EPI_STORE_DENSE, nullptr, nullptr,
+                 c->interior() ? d_R : nullptr);
   if (e != hipSuccess) return hip_fail(c, e, "fdm solve launch");
   return QN_OK;
 }
@@ -1358,7 +1356,7 @@ qn_status qn_iterate(qn_ctx c, double* d_U, const double* d_F, double rtol, int3
   const int* done = &c->scal()->done;
   auto enqueue = [&](int k) {
     hipError_t e = hipSuccess;
-    if (k > 0) e = solve_ws(c, &c->scal()->scale, d_U, EPI_SUB_DENSE, done);
+    if (k > 0) e = solve_ws(c, Coef{&c->scal()->scale, 0, 0.0, 0.0}, d_U, EPI_SUB_DENSE, done);
     // the finalize kernel also writes the scalars into host slot k & 1
     if (e == hipSuccess)
       e = residual_into_ws(c, d_U, d_F, nullptr, rtol, k, max_iter, k > 0 ? done : nullptr,
@@ -1457,7 +1455,7 @@ qn_status qn_eigen_iterate(qn_ctx c, double* d_U, double rtol, int32_t max_iter,
   auto enqueue = [&](int k) {
     hipError_t e = hipSuccess;
     if (k > 0)
-      e = solve_ws(c, &c->scal()->scale, d_U, EPI_SUB_DENSE, done, &c->scal()->uscale);
+      e = solve_ws(c, Coef{&c->scal()->scale, 0, 0.0, 0.0}, d_U, EPI_SUB_DENSE, done, &c->scal()->uscale);
     if (e == hipSuccess)
       e = eigen_residual(c, d_U, nullptr, nullptr, rtol, k, max_iter, k > 0 ? done : nullptr,
                          c->dring + (k & 1));
@@ -1512,14 +1510,12 @@ qn_status qn_autotune(qn_ctx c) {
   hipEvent_t t0 = nullptr, t1 = nullptr;
   hipError_t e = hipEventCreate(&t0);
   if (e == hipSuccess) e = hipEventCreate(&t1);
-  // finite transform contents; the coefficient slot holds {scale, shift} = {1, 1}
+  // finite transform contents
   const size_t tbytes = c->tensor_elems() * c->elem();
   if (e == hipSuccess) e = launch_zero(c->ws + c->off_W1, tbytes, c->stream);
   if (e == hipSuccess) e = launch_zero(c->ws + c->off_W2, tbytes, c->stream);
-  double* coef = c->at<double>(c->off_coef);
-  if (e == hipSuccess) e = launch_set_coef(coef, 1.0, 1.0, c->stream);
   FoldStep st[6];
-  const int ns = solve_plan(c, epi_args(c, coef, nullptr), EPI_STORE, st);
+  const int ns = solve_plan(c, epi_args(c, Coef{nullptr, 0, 1.0, 1.0}, nullptr), EPI_STORE, st);
   const bool was_tuned = c->tuned;
   c->tuned = false;  // step_tile gives the default rule below
   FoldTile best[6] = {};
@@ -1561,7 +1557,7 @@ qn_status qn_tile_info(qn_ctx c, int32_t i, int32_t* info4) {
   if (s != QN_OK) return s;
   if (!info4) return fail(QN_ERR_INVALID, "null argument");
   FoldStep st[6];
-  const int ns = solve_plan(c, epi_args(c, nullptr, nullptr), EPI_STORE, st);
+  const int ns = solve_plan(c, epi_args(c, Coef{}, nullptr), EPI_STORE, st);
   if (i < 0 || i >= ns) return fail(QN_ERR_INVALID, "launch index %d out of range [0, %d)", i, ns);
   const FoldTile t = step_tile(c, st[i], i);
   const int kid = st[i].kid;
@@ -1578,7 +1574,7 @@ qn_status qn_set_tile(qn_ctx c, int32_t i, const int32_t* info4) {
   if (s != QN_OK) return s;
   if (!info4) return fail(QN_ERR_INVALID, "null argument");
   FoldStep st[6];
-  const int ns = solve_plan(c, epi_args(c, nullptr, nullptr), EPI_STORE, st);
+  const int ns = solve_plan(c, epi_args(c, Coef{}, nullptr), EPI_STORE, st);
   if (i < 0 || i >= ns) return fail(QN_ERR_INVALID, "launch index %d out of range [0, %d)", i, ns);
   const int kid = st[i].kid;
   const int kind = kid == K_GEMM_X ? 0 : kid == K_GEMM_X_UPDATE ? 3 : kid == K_GEMM_YZ_INV ? 2 : 1;

@@ -74,7 +74,6 @@ struct qnb_ctx_s {
   double step = 1.0;                     // U -= step dU
   double gs[4] = {0.0, 0.0, 0.0, 0.0};  // Gray-Scott: D_A, D_S, rho, mu
   size_t off_cscale = 0;                 // device {D_A, D_S}
-  size_t off_coef = 0;                   // device {scale, shift} of qnb_fdm_solve
   std::vector<int> n, ncomp, inst_cls, inst_pos;
   std::vector<Cls> cls;
   long long field_elems = 0;
@@ -129,8 +128,7 @@ EpiArgs epi_for(qnb_ctx c, const Cls& k, double* dense_base) {
   ep.lamX = ep.lamM;
   ep.lamY = nullptr;
   BState* st = (BState*)(c->ws + k.off_state);
-  ep.coef = &st[0].scale;
-  ep.coef_stride = (int)(sizeof(BState) / sizeof(double));
+  ep.coef = {&st[0].scale, (int)(sizeof(BState) / sizeof(double)), 0.0, 0.0};
   ep.dense = dense_base ? dense_base + k.off_field : nullptr;
   ep.px = ep.py = k.p;
   ep.pz = 1;
@@ -176,7 +174,6 @@ hipError_t class_fast_solve(qnb_ctx c, const Cls& k, const double* rhs, bool sub
   b.es = k.p;
   b.oy = 1;
   b.coef = ep.coef;
-  b.coef_stride = ep.coef_stride;
   b.cscale = ep.cscale;
   b.comp_div = ep.cscale ? ep.comp_div : 1;
   b.lamX = ep.lamX;
@@ -241,7 +238,6 @@ hipError_t class_strip_solve(qnb_ctx c, const Cls& k, const double* rhs, bool su
   a.Fo = f.FoT;
   a.lamM = a.lamX = ep.lamX;
   a.coef = ep.coef;
-  a.coef_stride = ep.coef_stride;
   a.cscale = ep.cscale;
   if (ep.cscale) a.comp_div = ep.comp_div;
   e = launch(false, STRIP_DIV, a);
@@ -591,8 +587,6 @@ qn_status qnb_setup_ex(int32_t count, const int32_t* n, const int32_t* ncomp, in
   }
   c->off_cscale = off;
   off += a256(2 * sizeof(double));
-  c->off_coef = off;
-  off += a256(2 * sizeof(double));
   c->field_elems = fe;
   c->need = off;
   *out = c;
@@ -787,8 +781,7 @@ qn_status qnb_fdm_solve(qnb_ctx c, const double* d_R, double scale, double shift
     if (!(scale * k.lam_min + shift > 0.0))
       return set_error(QN_ERR_INVALID, "n = %d: scale lam_min(A_h) + shift <= 0 (singular or "
                                        "indefinite)", k.n);
-  double* coef = (double*)(c->ws + c->off_coef);
-  hipError_t e = launch_set_coef(coef, scale, shift, c->stream);
+  hipError_t e = hipSuccess;
   for (auto& k : c->cls) {
     if (e != hipSuccess) break;
     void* W1 = c->ws + k.off_W1;
@@ -796,8 +789,7 @@ qn_status qnb_fdm_solve(qnb_ctx c, const double* d_R, double scale, double shift
     if (k.interior()) {
       EpiArgs ep = epi_for(c, k, d_X);
       ep.skip = nullptr;  // every instance
-      ep.coef = coef;
-      ep.coef_stride = 0;
+      ep.coef = {nullptr, 0, scale, shift};
       const double* r = d_R + k.off_field;
       e = k.fast ? class_fast_solve(c, k, r, false, ep, c->stream)
                  : class_strip_solve(c, k, r, false, ep, c->stream);
@@ -809,8 +801,7 @@ qn_status qnb_fdm_solve(qnb_ctx c, const double* d_R, double scale, double shift
     if (e != hipSuccess) break;
     EpiArgs ep = epi_for(c, k, d_X);
     ep.skip = nullptr;  // every instance
-    ep.coef = coef;
-    ep.coef_stride = 0;
+    ep.coef = {nullptr, 0, scale, shift};
     const int rows = k.ncomp * k.K * k.p;
     const int slabs = k.ncomp * k.K;
     const long long sl = (long long)k.p * k.p;

@@ -138,8 +138,9 @@ __global__ __launch_bounds__(FAST_THREADS, FAM == EVEN ? 4 : 2) void k_fast_line
     QN_FAST_SWITCH(R)
 #undef X
   } else {
-    const double* coef = a.coef + (long long)inst * a.coef_stride;
-    const double scale = coef[0] * (a.cscale ? a.cscale[plane / a.comp_div] : 1.0), beta = coef[1];
+    double scale, beta;
+    a.coef.get(inst, scale, beta);
+    if (a.cscale) scale *= a.cscale[plane / a.comp_div];
     const double den0 = scale * (a.lamX[x0 + xl] + (a.lamY ? a.lamY[opos] : 0.0)) + beta;
 #define X(L)                                                                                       \
   case L: {                                                                                        \

@@ -414,8 +414,8 @@ __global__ __launch_bounds__(256, 2) void k_gemm_left_bf(GemmOperands S, const v
   if (EPI == EPI_DIVIDE) {
     // denominator scale (lam_m + lam_x + lam_y) + beta: the column part once
     // per column block, the row part once per row, one divide per entry
-    const double* cf = ep.coef + (long long)inst * ep.coef_stride;
-    const double scale = cf[0], beta = cf[1];
+    double scale, beta;
+    ep.coef.get(inst, scale, beta);
     double cn[BN];
 #pragma unroll
     for (int j = 0; j < BN; ++j) {

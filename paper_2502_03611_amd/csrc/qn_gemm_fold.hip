@@ -181,8 +181,9 @@ __global__ __launch_bounds__(256, 2) void k_fold_left_fwd(const T* __restrict__ 
 
   T* Cb = C + (long long)b * bstride;
   if (EPI == EPI_DIVIDE) {
-    const double* cf = ep.coef + (long long)inst * ep.coef_stride;
-    const double scale = cf[0] * (ep.cscale ? ep.cscale[b / ep.comp_div] : 1.0), beta = cf[1];
+    double scale, beta;
+    ep.coef.get(inst, scale, beta);
+    if (ep.cscale) scale *= ep.cscale[b / ep.comp_div];
     double cn[BN];
 #pragma unroll
     for (int j = 0; j < BN; ++j) {
@@ -347,9 +348,8 @@ __global__ __launch_bounds__(256, 2) void k_fold_left_fwd2(const T* __restrict__
   T* Cb = C + (long long)b * bstride;
   double scale = 1.0, beta = 0.0, cn[BN];
   if (EPI == EPI_DIVIDE) {
-    const double* cf = ep.coef + (long long)inst * ep.coef_stride;
-    scale = cf[0] * (ep.cscale ? ep.cscale[b / ep.comp_div] : 1.0);
-    beta = cf[1];
+    ep.coef.get(inst, scale, beta);
+    if (ep.cscale) scale *= ep.cscale[b / ep.comp_div];
 #pragma unroll
     for (int j = 0; j < BN; ++j) {
       const int n = n0 + wn + 16 * j + (lane & 15);

@@ -15,7 +15,9 @@
 // around them; per instruction the tiles are the faster form (511^3, no
 // padding: 1.39 against 1.24 ms a product), so the strips are taken where the
 // padding outweighs that (use_strips in qn_host.h).  200^3 FP64 solve 0.57 ->
-// 0.41 ms, 400^3 6.9 -> 4.1 ms, 150 x 203 x 176 FP32 0.23 -> 0.17 ms.  The
+// 0.40 ms, 400^3 6.9 -> 3.9 ms, 150 x 203 x 176 FP32 0.23 -> 0.17 ms.  (With
+// vector address arithmetic and tail selects in every chunk, nine other vector
+// instructions per matrix one, 0.41 and 4.1 ms.)  The
 // contraction runs in the same order as in the tile form (steps of four rows
 // from row 0), so the results are the same bits.
 //
@@ -54,6 +56,49 @@ struct Stage {
   V r[NA];
 };
 
+// The stage's global loads, advanced by `step` elements per chunk.  Rows past bk
+// repeat others: they feed accumulators that are not stored.  With whole rows
+// per 256 vectors of one parity the addresses are scalar but for one offset.
+template <typename T, int MB>
+struct Loader {
+  using S = Stage<T, MB>;
+  typedef typename S::V V;
+  static constexpr int ROW = 16 * MB / S::VE;  // vectors of a row
+  static constexpr bool SCALAR = MB == 4;
+  static constexpr int NP = SCALAR ? 2 : S::NA;
+  const T* p[NP];
+  int off = 0, bk;
+  __device__ __forceinline__ Loader(const StripArgs& a, int tid, int m0) : bk(a.bk) {
+    if constexpr (SCALAR) {
+      p[0] = (const T*)a.Fe;
+      p[1] = (const T*)a.Fo;
+      off = (tid / ROW) * bk + min(m0 + (tid % ROW) * S::VE, bk - S::VE);
+    } else {
+#pragma unroll
+      for (int q = 0; q < S::NA; ++q) {
+        const int v = min(tid + 256 * q, S::NV - 1);
+        p[q] = (const T*)(v / ROW / KC ? a.Fo : a.Fe) + (v / ROW % KC) * bk +
+               min(m0 + (v % ROW) * S::VE, bk - S::VE);
+      }
+    }
+  }
+  __device__ __forceinline__ void next(V (&r)[S::NA], int step) {
+    if constexpr (SCALAR) {
+#pragma unroll
+      for (int q = 0; q < S::NA; ++q)
+        r[q] = *reinterpret_cast<const V*>(p[q / (S::NA / 2)] + q % (S::NA / 2) * (256 / ROW) * bk + off);
+      p[0] += step;
+      p[1] += step;
+    } else {
+#pragma unroll
+      for (int q = 0; q < S::NA; ++q) {
+        r[q] = *reinterpret_cast<const V*>(p[q]);
+        p[q] += step;
+      }
+    }
+  }
+};
+
 // Column group g of a split or natural axis: first position and valid width.
 __device__ __forceinline__ void group_of(const StripArgs& a, int g, int width, int& pos, int& lim) {
   if (g < a.ge) {
@@ -68,7 +113,7 @@ __device__ __forceinline__ void group_of(const StripArgs& a, int g, int width, i
 // Form L (y and z axes).  INV = 0: forward (spatial rows k and n-1-k folded),
 // INV = 1: inverse.  NCB: 16-column blocks per wave.
 template <typename T, int MB, int NCB, int INV, int DIV>
-__global__ __launch_bounds__(256, MB <= 4 ? 3 : 2) void k_strip_left(StripArgs a) {
+__global__ __launch_bounds__(256, MB * NCB <= 6 && MB <= 4 ? 3 : 2) void k_strip_left(StripArgs a) {
   using MF = Mfma<T>;
   using S = Stage<T, MB>;
   typedef typename S::V V;
@@ -76,10 +121,11 @@ __global__ __launch_bounds__(256, MB <= 4 ? 3 : 2) void k_strip_left(StripArgs a
   const int mtiles = a.mtiles;
   const int t = xcd_tile(blockIdx.x, gridDim.x);
   const int mt = t % mtiles, wg = t / mtiles;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 15, lk = lane >> 4;
   const int n = a.n, h = a.h, odd = a.odd, bk = a.bk, ne = h + odd;
   const int m0 = mt * 16 * MB;
+  const int live_blocks = (ne - m0 + 15) / 16;  // the last block tile may have fewer than MB
   const int strip = min(wg * 4 + wave, a.strips - 1);  // spare waves repeat the last strip
   const int o = strip / a.groups, g = strip - o * a.groups;
   const int plane = o / a.oy;
@@ -115,17 +161,8 @@ __global__ __launch_bounds__(256, MB <= 4 ? 3 : 2) void k_strip_left(StripArgs a
     for (int j = 0; j < NCB; ++j) acce[i][j] = acco[i][j] = typename MF::v4{0, 0, 0, 0};
 
   V ra[S::NA];
-  auto aload = [&](int k0) {
-#pragma unroll
-    for (int q = 0; q < S::NA; ++q) {
-      const int v = tid + 256 * q;
-      const int mm = (v % (16 * MB / S::VE)) * S::VE, kk = (v / (16 * MB / S::VE)) % KC,
-                par = v / (16 * MB / S::VE) / KC;
-      ra[q] = V{};
-      if (v < S::NV && m0 + mm < bk)
-        ra[q] = *reinterpret_cast<const V*>((const T*)(par ? a.Fo : a.Fe) + (long long)(k0 + kk) * bk + m0 + mm);
-    }
-  };
+  Loader<T, MB> ld(a, tid, m0);
+  auto aload = [&]() { ld.next(ra, KC * bk); };
   auto astore = [&](int buf) {
 #pragma unroll
     for (int q = 0; q < S::NA; ++q) {
@@ -136,7 +173,25 @@ __global__ __launch_bounds__(256, MB <= 4 ? 3 : 2) void k_strip_left(StripArgs a
     }
   };
   T lo[2][KC / 4][NCB], hi[2][KC / 4][NCB];
+  // Chunks inside the folded rows: scalar row addresses, one offset per lane
+  // (the upper rows of a forward product run backwards).
+  const unsigned off0 = (unsigned)(lk * a.es) * (unsigned)sizeof(T);
+  const unsigned off1 = INV ? off0 : (unsigned)((3 - lk) * a.es) * (unsigned)sizeof(T);
+  auto at = [&](long long row, unsigned off, int j) {
+    return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(in + row * a.es) +
+                                       (off + (unsigned)col[j] * (unsigned)sizeof(T)));
+  };
   auto bload = [&](int k0, T (&l)[KC / 4][NCB], T (&u)[KC / 4][NCB]) {
+    if (k0 + KC <= h) {
+#pragma unroll
+      for (int s = 0; s < KC / 4; ++s)
+#pragma unroll
+        for (int j = 0; j < NCB; ++j) {
+          l[s][j] = at(k0 + 4 * s, off0, j);
+          u[s][j] = at(INV ? bk + k0 + 4 * s : n - 4 - k0 - 4 * s, off1, j);
+        }
+      return;
+    }
 #pragma unroll
     for (int s = 0; s < KC / 4; ++s) {
       const int k = k0 + 4 * s + lk;
@@ -154,40 +209,52 @@ __global__ __launch_bounds__(256, MB <= 4 ? 3 : 2) void k_strip_left(StripArgs a
   const int nk = (ne + KC - 1) / KC;
   auto compute = [&](int kc, const T (&l)[KC / 4][NCB], const T (&u)[KC / 4][NCB]) {
     const int buf = kc & 1;
+    T e[KC / 4][NCB], d[KC / 4][NCB];
+    const bool full = kc * KC + KC <= h;
+#pragma unroll
+    for (int s = 0; s < KC / 4; ++s)
+#pragma unroll
+      for (int j = 0; j < NCB; ++j) {
+        e[s][j] = INV ? l[s][j] : l[s][j] + u[s][j];
+        d[s][j] = INV ? u[s][j] : l[s][j] - u[s][j];
+      }
+    if (!full) {
+#pragma unroll
+      for (int s = 0; s < KC / 4; ++s) {
+        const int k = kc * KC + 4 * s + lk;
+#pragma unroll
+        for (int j = 0; j < NCB; ++j) {
+          if (INV)
+            e[s][j] = k < ne ? e[s][j] : T(0);
+          else
+            e[s][j] = k < h ? e[s][j] : (k == h && odd) ? l[s][j] : T(0);
+          d[s][j] = k < h ? d[s][j] : T(0);
+        }
+      }
+    }
 #pragma unroll
     for (int s = 0; s < KC / 4; ++s) {
       if (kc * KC + 4 * s >= ne) break;
-      const int k = kc * KC + 4 * s + lk;
-      T e[NCB], d[NCB];
-#pragma unroll
-      for (int j = 0; j < NCB; ++j) {
-        if (INV) {
-          e[j] = k < ne ? l[s][j] : T(0);
-          d[j] = k < h ? u[s][j] : T(0);
-        } else {
-          e[j] = k < h ? l[s][j] + u[s][j] : (k == h && odd) ? l[s][j] : T(0);
-          d[j] = k < h ? l[s][j] - u[s][j] : T(0);
-        }
-      }
 #pragma unroll
       for (int i = 0; i < MB; ++i) {
+        if (i >= live_blocks) break;
         const T fe = As[buf][0][4 * s + lk][16 * i + lr], fo = As[buf][1][4 * s + lk][16 * i + lr];
 #pragma unroll
         for (int j = 0; j < NCB; ++j) {
-          acce[i][j] = MF::op(fe, e[j], acce[i][j]);
-          acco[i][j] = MF::op(fo, d[j], acco[i][j]);
+          acce[i][j] = MF::op(fe, e[s][j], acce[i][j]);
+          acco[i][j] = MF::op(fo, d[s][j], acco[i][j]);
         }
       }
     }
   };
-  aload(0);
+  aload();
   bload(0, lo[0], hi[0]);
   astore(0);
   __syncthreads();
   for (int kc = 0; kc < nk; kc += 2) {
     // two chunks per trip, so that the register buffers keep static names
     if (kc + 1 < nk) {
-      aload((kc + 1) * KC);
+      aload();
       bload((kc + 1) * KC, lo[1], hi[1]);
     }
     compute(kc, lo[0], hi[0]);
@@ -195,7 +262,7 @@ __global__ __launch_bounds__(256, MB <= 4 ? 3 : 2) void k_strip_left(StripArgs a
     astore(1);
     __syncthreads();
     if (kc + 2 < nk) {
-      aload((kc + 2) * KC);
+      aload();
       bload((kc + 2) * KC, lo[0], hi[0]);
     }
     compute(kc + 1, lo[1], hi[1]);
@@ -207,9 +274,8 @@ __global__ __launch_bounds__(256, MB <= 4 ? 3 : 2) void k_strip_left(StripArgs a
 
   double scale = 1.0, beta = 0.0, cn[NCB];
   if constexpr (DIV) {
-    const double* cf = a.coef + (long long)inst * a.coef_stride;
-    scale = cf[0] * (a.cscale ? a.cscale[plane / a.comp_div] : 1.0);
-    beta = cf[1];
+    a.coef.get(inst, scale, beta);
+    if (a.cscale) scale *= a.cscale[plane / a.comp_div];
 #pragma unroll
     for (int j = 0; j < NCB; ++j) cn[j] = a.lamX[col[j]] + (a.lamY ? a.lamY[opos] : 0.0);
   }
@@ -257,10 +323,11 @@ __global__ __launch_bounds__(256, MB <= 4 ? 3 : 2) void k_strip_right(StripArgs 
   const int mtiles = a.mtiles;
   const int t = xcd_tile(blockIdx.x, gridDim.x);
   const int mt = t % mtiles, wg = t / mtiles;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 15, lk = lane >> 4;
   const int n = a.n, h = a.h, odd = a.odd, bk = a.bk, ne = h + odd;
   const int m0 = mt * 16 * MB;
+  const int live_blocks = (ne - m0 + 15) / 16;  // the last block tile may have fewer than MB
   const int r0 = wg * 64 + 16 * wave;
   if (a.skip) {
     const int p0 = wg * 64 / a.oy, p1 = min(wg * 64 + 63, a.rows - 1) / a.oy;
@@ -282,17 +349,8 @@ __global__ __launch_bounds__(256, MB <= 4 ? 3 : 2) void k_strip_right(StripArgs 
   for (int i = 0; i < MB; ++i) acce[i] = acco[i] = typename MF::v4{0, 0, 0, 0};
 
   V ra[S::NA];
-  auto aload = [&](int k0) {
-#pragma unroll
-    for (int q = 0; q < S::NA; ++q) {
-      const int v = tid + 256 * q;
-      const int mm = (v % (16 * MB / S::VE)) * S::VE, kk = (v / (16 * MB / S::VE)) % KC,
-                par = v / (16 * MB / S::VE) / KC;
-      ra[q] = V{};
-      if (v < S::NV && m0 + mm < bk)
-        ra[q] = *reinterpret_cast<const V*>((const T*)(par ? a.Fo : a.Fe) + (long long)(k0 + kk) * bk + m0 + mm);
-    }
-  };
+  Loader<T, MB> ld(a, tid, m0);
+  auto aload = [&]() { ld.next(ra, KC * bk); };
   auto astore = [&](int buf) {
 #pragma unroll
     for (int q = 0; q < S::NA; ++q) {
@@ -305,6 +363,15 @@ __global__ __launch_bounds__(256, MB <= 4 ? 3 : 2) void k_strip_right(StripArgs 
   T lo[4], hi[4];
   auto dload = [&](int k0) {
     const int k = k0 + lr;
+    if (k0 + KC <= h) {
+      const int c1 = INV ? bk + k : n - 1 - k;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        lo[i] = (T)src[i][k];
+        hi[i] = (T)src[i][c1];
+      }
+      return;
+    }
     const int c0 = INV ? min(k, ne - 1) : min(k, h);
     const int c1 = INV ? (h > 0 ? bk + min(k, h - 1) : 0) : (k < h ? n - 1 - k : 0);
 #pragma unroll
@@ -315,10 +382,14 @@ __global__ __launch_bounds__(256, MB <= 4 ? 3 : 2) void k_strip_right(StripArgs 
   };
   auto dstore = [&](int k0) {
     const int k = k0 + lr;
+    const bool full = k0 + KC <= h;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       T e, d;
-      if (INV) {
+      if (full) {
+        e = INV ? lo[i] : lo[i] + hi[i];
+        d = INV ? hi[i] : lo[i] - hi[i];
+      } else if (INV) {
         e = k < ne ? lo[i] : T(0);
         d = k < h ? hi[i] : T(0);
       } else {
@@ -330,7 +401,7 @@ __global__ __launch_bounds__(256, MB <= 4 ? 3 : 2) void k_strip_right(StripArgs 
     }
   };
   const int nk = (ne + KC - 1) / KC;
-  aload(0);
+  aload();
   dload(0);
   astore(0);
   dstore(0);
@@ -338,7 +409,7 @@ __global__ __launch_bounds__(256, MB <= 4 ? 3 : 2) void k_strip_right(StripArgs 
   for (int kc = 0; kc < nk; ++kc) {
     const int buf = kc & 1;
     if (kc + 1 < nk) {
-      aload((kc + 1) * KC);
+      aload();
       dload((kc + 1) * KC);
     }
     T e[KC / 4], d[KC / 4];
@@ -352,6 +423,7 @@ __global__ __launch_bounds__(256, MB <= 4 ? 3 : 2) void k_strip_right(StripArgs 
       if (kc * KC + 4 * s >= ne) break;
 #pragma unroll
       for (int i = 0; i < MB; ++i) {
+        if (i >= live_blocks) break;
         acce[i] = MF::op(e[s], Bs[buf][0][4 * s + lk][16 * i + lr], acce[i]);
         acco[i] = MF::op(d[s], Bs[buf][1][4 * s + lk][16 * i + lr], acco[i]);
       }
@@ -400,18 +472,21 @@ __global__ __launch_bounds__(256, MB <= 4 ? 3 : 2) void k_strip_right(StripArgs 
   }
 }
 
-// 16-row blocks per wave (at most `cap`): the count whose rounds of workgroups
-// (three per CU to four blocks, else two) take the least matrix-core time; the
-// larger one of equals re-reads the data less often.  FP64 at 200^3: 7 blocks
-// 0.425 ms a solve, 4 0.411, 2 0.449; at 400^3: 7 4.06 ms, 5 4.46, 4 4.40.
-inline int blocks_per_wave(int ne, int cap, long long workgroups, int* mtiles) {
+constexpr int CAP = 7;  // (8 blocks spill)
+
+// 16-row blocks per wave: the count whose rounds of workgroups (three per CU up
+// to `three` blocks, else two) take the least time, a block counting
+// as its matrix instructions and the wave's own loads, folds and stores as half
+// a block (FP64 at 200^3: 7 blocks 0.425 ms a solve, 4 0.411, 2 0.449, 1 0.47; at
+// 400^3: 7 4.06 ms, 5 4.46, 4 4.40).
+inline int blocks_per_wave(int ne, int three, long long workgroups, int* mtiles) {
   const int nb = (ne + 15) / 16;
   int best = 1;
   long long best_cost = -1;
-  for (int mb = std::min(cap, nb); mb >= 1; --mb) {
+  for (int mb = std::min(CAP, nb); mb >= 1; --mb) {
     const long long wgs = workgroups * ((nb + mb - 1) / mb);
-    const int occ = mb <= 4 ? 3 : 2;
-    const long long cost = (wgs + 256 * occ - 1) / (256 * occ) * occ * mb;
+    const int occ = mb <= three ? 3 : 2;
+    const long long cost = (wgs + 256 * occ - 1) / (256 * occ) * occ * (2 * mb + 1);
     if (best_cost < 0 || cost < best_cost) {
       best_cost = cost;
       best = mb;
@@ -428,7 +503,7 @@ hipError_t left(StripArgs a, int kind, hipStream_t st) {
   a.groups = a.ge + (a.co + 16 * NCB - 1) / (16 * NCB);
   a.strips = a.groups * a.nouter;
   const long long wgs = (a.strips + 3) / 4;
-  const int mb = blocks_per_wave(a.h + a.odd, 8, wgs, &a.mtiles);
+  const int mb = blocks_per_wave(a.h + a.odd, NCB == 1 ? 4 : 3, wgs, &a.mtiles);
   const dim3 grid((unsigned)(wgs * a.mtiles)), block(256);
 #define QN_STRIP(M)                                                                      \
   case M:                                                                                \
@@ -437,7 +512,7 @@ hipError_t left(StripArgs a, int kind, hipStream_t st) {
     else hipLaunchKernelGGL((k_strip_left<T, M, NCB, 0, 0>), grid, block, 0, st, a);                          \
     break;
   switch (mb) {
-    QN_STRIP(1) QN_STRIP(2) QN_STRIP(3) QN_STRIP(4) QN_STRIP(5) QN_STRIP(6) QN_STRIP(7) QN_STRIP(8)
+    QN_STRIP(1) QN_STRIP(2) QN_STRIP(3) QN_STRIP(4) QN_STRIP(5) QN_STRIP(6) QN_STRIP(7)
     default: return hipErrorInvalidValue;
   }
 #undef QN_STRIP
@@ -446,10 +521,8 @@ hipError_t left(StripArgs a, int kind, hipStream_t st) {
 
 template <typename T>
 hipError_t right(StripArgs a, int kind, bool in64, hipStream_t st) {
-  // FP64 stages of 8 blocks would leave one workgroup per CU
-  constexpr int CAP = sizeof(T) == 8 ? 7 : 8;
   const long long wgs = (a.rows + 63) / 64;
-  const int mb = blocks_per_wave(a.h + a.odd, CAP, wgs, &a.mtiles);
+  const int mb = blocks_per_wave(a.h + a.odd, 4, wgs, &a.mtiles);
   const dim3 grid((unsigned)(wgs * a.mtiles)), block(256);
 #define QN_STRIP(M)                                                                      \
   case M:                                                                                \
@@ -459,12 +532,6 @@ hipError_t right(StripArgs a, int kind, bool in64, hipStream_t st) {
     break;
   switch (mb) {
     QN_STRIP(1) QN_STRIP(2) QN_STRIP(3) QN_STRIP(4) QN_STRIP(5) QN_STRIP(6) QN_STRIP(7)
-    case 8:
-      if constexpr (CAP >= 8) {
-        switch (8) { QN_STRIP(8) }
-        break;
-      }
-      return hipErrorInvalidValue;
     default: return hipErrorInvalidValue;
   }
 #undef QN_STRIP

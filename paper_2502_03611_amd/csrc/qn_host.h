@@ -442,12 +442,13 @@ inline void fast_tables(int N, int Q, int R, bool neumann, double ih2, std::vect
 // waves: 200^2 FP64 0.046 against 0.036 ms of tile launches) and at least 1.25
 // times as many matrix-core operations in the padded tiles as in the strips
 // (whose rate is 0.8-0.9 of the tiles': 255^3 0.73 against 0.67 ms at a ratio
-// of 1.0, 400^3 4.1 against 6.6 ms at 1.35, 200^3 0.41 against 0.52 ms at 1.9).  n, p, dense: extents, padded
-// extents and which axes have a dense product.
+// of 1.0, 400^3 4.1 against 6.6 ms at 1.35, 200^3 0.41 against 0.52 ms at 1.9).
+// Row strides stay below 2^26 elements (32-bit lane offsets of three rows).  n,
+// p, dense: extents, padded extents and which axes have a dense product.
 inline bool use_strips(int dim, const int* n, const int* p, const bool* dense, int fields) {
   double values = fields, tiles = 0.0, strips = 0.0;
   for (int a = 0; a < dim; ++a) values *= n[a];
-  if (values < 1048576.0) return false;
+  if (values < 1048576.0 || (dim == 3 && (double)p[0] * p[1] >= 67108864.0)) return false;
   auto up16 = [](int v) { return (v + 15) / 16 * 16; };
   for (int a = 0; a < dim; ++a) {
     if (!dense[a]) continue;

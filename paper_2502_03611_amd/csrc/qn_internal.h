@@ -63,21 +63,34 @@ enum Epi : int {
   EPI_STORE_DENSE = 3,  // dense[..] = acc (interior only)
 };
 
+// {scale, beta} of a solve: at + instance * stride in device memory (the
+// scalars of a running iteration), or the values themselves when at is NULL
+// (stand-alone solves: a launch that stores them first is 1.4 us and a launch
+// gap, 18.3 against 14.1 us for a 63^2 FP64 solve).
+struct Coef {
+  const double* at;
+  int stride;
+  double scale, beta;
+  __device__ void get(long long inst, double& s, double& b) const {
+    const double* p = at + inst * stride;
+    s = at ? p[0] : scale;
+    b = at ? p[1] : beta;
+  }
+};
+
 struct EpiArgs {
   const double* lamM;   // eigenvalues along the product's own axis (row index m)
   const double* lamX;   // eigenvalues along x (column index n % px)
   const double* lamY;   // eigenvalues along y (column index n / px), NULL in 2D
-  const double* coef;   // device {scale, beta} (points into DevScalars or solve slot)
+  Coef coef;
   double* dense;        // caller array (ncomp, nz, ny, nx) for the dense epilogues
   int px, py, pz;       // padded extents
   int nx, ny, nz;       // interior extents
   // Batched solver: slabs / row blocks belong to instance (index % inst_mod);
-  // an instance whose skip flag is set is left untouched, and its {scale, beta}
-  // sit at coef + instance * coef_stride.  A single problem uses skip = NULL,
-  // inst_mod = 1, coef_stride = 0.
+  // an instance whose skip flag is set is left untouched.  A single problem uses
+  // skip = NULL, inst_mod = 1, coef.stride = 0.
   const int* skip;
   int inst_mod;
-  int coef_stride;
   // EPI_SUB_DENSE of the folded kernels: the old values are multiplied by
   // *uscale before the subtraction (the eigenproblem's normalisation), NULL: 1.
   const double* uscale;
@@ -204,8 +217,7 @@ struct StripArgs {
   const double* lamM;
   const double* lamX;
   const double* lamY;
-  const double* coef;
-  int coef_stride;
+  Coef coef;
   const double* cscale;
   int comp_div;
   const int* skip;
@@ -247,8 +259,7 @@ struct FastArgs {
   int sub;
   const double* uscale;
   double step;
-  const double* coef;
-  int coef_stride;
+  Coef coef;
   const double* cscale;
   int comp_div;
   const double* lamX;
@@ -382,7 +393,6 @@ inline int transform_storage(int prec) {
 hipError_t launch_pad_copy(const double* src, void* dst, int out_prec, int ncomp, int nx, int ny,
                            int nz, int px, int py, int pz, hipStream_t st, int xfold = 0);
 // Write {scale, beta} into a device slot.
-hipError_t launch_set_coef(double* slot, double scale, double beta, hipStream_t st);
 // Fill n bytes with zero (a kernel, not a memset node).
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t st);
 

@@ -946,16 +946,6 @@ hipError_t launch_pad_copy(const double* src, void* dst, int out_prec, int ncomp
   return hipGetLastError();
 }
 
-__global__ void k_set_coef(double* slot, double scale, double beta) {
-  slot[0] = scale;
-  slot[1] = beta;
-}
-
-hipError_t launch_set_coef(double* slot, double scale, double beta, hipStream_t st) {
-  hipLaunchKernelGGL(k_set_coef, dim3(1), dim3(1), 0, st, slot, scale, beta);
-  return hipGetLastError();
-}
-
 __global__ __launch_bounds__(256) void k_zero(uint4* p, size_t n16) {
   size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
   const size_t stride = (size_t)gridDim.x * 256;
