@@ -599,9 +599,16 @@ void choose_fast(qn_ctx c) {
     c->fast[a] = c->prec == QN_PREC_FP64 && c->sem_k == 0 && f.N >= 16 && fast_stages(f.N, &f.Q, &f.R) &&
                  (f.R / 2 + 1) * es + 64 < (1LL << 28);
     c->fx[a] = f;
-    c->any_fast = c->any_fast || c->fast[a];
     c->all_fast = c->all_fast && c->fast[a];
   }
+  // On a small grid a product over at most 32 contraction rows is a launch like
+  // a factored pass, which gains only as the last axis (divide and inverse in
+  // the same pass): 100 x 63 x 63 with both short axes factored 57, dense 53 us
+  // per iteration; 31 x 31 x 200, last axis short, 64 and 81.
+  const bool small = (double)c->ncomp * c->n[0] * c->n[1] * c->n[2] < 1048576.0;
+  if (small && !c->fast[c->dim - 1])
+    for (int a = 0; a < c->dim; ++a) c->fast[a] = c->fast[a] && c->n[a] > 64;
+  for (int a = 0; a < c->dim; ++a) c->any_fast = c->any_fast || c->fast[a];
   const bool dense[3] = {!c->fast[0], !c->fast[1], !c->fast[2]};
   c->strip = c->fold && use_strips(c->dim, c->n, c->p, dense, c->ncomp);
   // An odd number of 128-byte lines per plane, so that the z passes' strides do
@@ -776,15 +783,29 @@ hipError_t strip_pass(qn_ctx c, int axis, const void* in, void* out, const doubl
               : launch_strip32(false, kind, false, a, c->stream);
 }
 
+// Whether the first pass of a stand-alone solve reads the caller's right-hand
+// side.  Factored and strip x passes always do.  The tile form's does where that
+// beats the copy into the padded tensor: in FP64 everywhere (63^2 26.5 against
+// 20.7 us a solve, 511^3 8.32 and 8.18 ms); in FP32 every column tile would
+// fetch FP64 rows twice the size in 8-byte loads, which costs more than the copy
+// saves from long axes on (127^3 67 and 61 us, 511^2 40 and 38; but 255^3 363
+// and 371, 1023^2 103 and 146).
+bool direct_rhs(qn_ctx c) {
+  if (c->interior()) return true;
+  if (!c->fold || c->fast[0]) return false;
+  return c->prec == QN_PREC_FP64 || (c->p[0] <= 512 && c->tensor_elems() <= (1u << 22));
+}
+
 // skip (device int, may be NULL): when set, every launch of the solve exits
 // at once (the quasi-Newton loop has stopped).  rhs: the caller's right-hand
-// side when it is not in W1 (interior() solves).
+// side when the first pass reads it instead of W1.
 hipError_t solve_ws(qn_ctx c, const Coef& coef, double* dense, int epi_last,
                     const int* skip = nullptr, const double* uscale = nullptr,
                     const double* rhs = nullptr) {
   EpiArgs ep = epi_args(c, coef, dense);
   ep.skip = skip;
   ep.uscale = uscale;
+  if (!c->interior()) ep.src = rhs;
   FoldStep st[6];
   const int ns = solve_plan(c, ep, epi_last, st);
   if (c->any_fast || c->interior()) {
@@ -1315,7 +1336,8 @@ qn_status qn_fdm_solve(qn_ctx c, const double* d_R, double scale, double shift, 
     return fail(QN_ERR_INVALID, "scale*lam_min(A_h) + shift = %g <= 0: singular or indefinite",
                 scale * c->lam_min_sum + shift);
   hipError_t e = hipSuccess;
-  if (!c->interior())  // else the x pass reads d_R itself
+  const bool direct = direct_rhs(c);  // the first pass reads d_R itself
+  if (!direct)
     e = timed(c, K_PAD_COPY, [&] {
       return launch_pad_copy(d_R, c->ws + c->off_W1, transform_storage(c->prec), c->ncomp,
                              c->n[0], c->n[1], c->n[2], c->p[0], c->p[1], c->p[2], c->stream,
@@ -1323,7 +1345,7 @@ qn_status qn_fdm_solve(qn_ctx c, const double* d_R, double scale, double shift, 
     });
   if (e == hipSuccess)
     e = solve_ws(c, Coef{nullptr, 0, scale, shift}, d_X, EPI_STORE_DENSE, nullptr, nullptr,
-                 c->interior() ? d_R : nullptr);
+                 direct ? d_R : nullptr);
   if (e != hipSuccess) return hip_fail(c, e, "fdm solve launch");
   return QN_OK;
 }

@@ -292,9 +292,11 @@ hipError_t lines_launch(K kern, int lc, FastArgs a, int nouter, hipStream_t st) 
   const int qh = a.ax.Q / 2 + 1, rh = a.ax.R / 2 + 1;
   auto bytes = [&](int l) { return (size_t)qh * rh * sizeof(Pair<T>) << l; };
   while (lc > 2 && bytes(lc) > kLdsTarget) --lc;
-  // small grids: fewer lines per workgroup until every CU has two
+  // small grids: fewer lines per workgroup (shorter runs of a cache line) until
+  // half the CUs have one; per iteration, to 512 workgroups and to 128: 63^3 53
+  // and 48 us, 127 x 127 x 31 73 and 60, 1023^2 82 and 77
   auto tiles = [&](int cols, int l) { return (cols + (1 << l) - 1) >> l; };
-  while (lc > 2 && (long long)(tiles(a.ce, lc) + tiles(a.co, lc)) * nouter < 512) --lc;
+  while (lc > 2 && (long long)(tiles(a.ce, lc) + tiles(a.co, lc)) * nouter < 128) --lc;
   a.lc = lc;
   a.xsplit = tiles(a.ce, lc);
   a.xtiles = a.xsplit + tiles(a.co, lc);
@@ -311,8 +313,8 @@ hipError_t rows_launch(FastArgs a, hipStream_t st) {
   const size_t per = (size_t)qh * (rh | 1) * sizeof(Pair<T>);
   int lines = 256 / nb;
   lines = std::min<int>(lines, std::max<size_t>(1, kLdsTarget / per));
-  // small grids: fewer rows per workgroup (but a whole wave) until every CU has two
-  lines = std::min(lines, std::max(std::max(1, 64 / nb), a.rows / 512));
+  // small grids: fewer rows per workgroup (but a whole wave) until every CU has one
+  lines = std::min(lines, std::max(std::max(1, 64 / nb), a.rows / 256));
   a.lines = lines;
   auto kern = k_fast_rows<FAM, EPI>;
   hipError_t e = allow_lds(kern, per * lines);

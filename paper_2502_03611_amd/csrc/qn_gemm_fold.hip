@@ -158,6 +158,11 @@ __global__ __launch_bounds__(256, 2) void k_fold_left_fwd(const T* __restrict__ 
   const int kmax = ((h + ax.odd + TK - 1) / TK) * TK;
   const int nk = kmax / TK;
   gload(0);
+  double scale = 1.0, beta = 0.0;  // their loads overlap the first stage's
+  if (EPI == EPI_DIVIDE) {
+    ep.coef.get(inst, scale, beta);
+    if (ep.cscale) scale *= ep.cscale[b / ep.comp_div];
+  }
   lstore(0);
   __syncthreads();
   for (int kc = 0; kc < nk; ++kc) {
@@ -181,9 +186,6 @@ __global__ __launch_bounds__(256, 2) void k_fold_left_fwd(const T* __restrict__ 
 
   T* Cb = C + (long long)b * bstride;
   if (EPI == EPI_DIVIDE) {
-    double scale, beta;
-    ep.coef.get(inst, scale, beta);
-    if (ep.cscale) scale *= ep.cscale[b / ep.comp_div];
     double cn[BN];
 #pragma unroll
     for (int j = 0; j < BN; ++j) {
@@ -315,6 +317,11 @@ __global__ __launch_bounds__(256, 2) void k_fold_left_fwd2(const T* __restrict__
   const int kmax = ((h + ax.odd + TK - 1) / TK) * TK;
   const int nk = kmax / TK;
   gload(0);
+  double scale = 1.0, beta = 0.0;  // their loads overlap the first stage's
+  if (EPI == EPI_DIVIDE) {
+    ep.coef.get(inst, scale, beta);
+    if (ep.cscale) scale *= ep.cscale[b / ep.comp_div];
+  }
   lstore(0);
   __syncthreads();
   for (int kc = 0; kc < nk; ++kc) {
@@ -346,10 +353,8 @@ __global__ __launch_bounds__(256, 2) void k_fold_left_fwd2(const T* __restrict__
   }
 
   T* Cb = C + (long long)b * bstride;
-  double scale = 1.0, beta = 0.0, cn[BN];
+  double cn[BN];
   if (EPI == EPI_DIVIDE) {
-    ep.coef.get(inst, scale, beta);
-    if (ep.cscale) scale *= ep.cscale[b / ep.comp_div];
 #pragma unroll
     for (int j = 0; j < BN; ++j) {
       const int n = n0 + wn + 16 * j + (lane & 15);
@@ -521,7 +526,11 @@ __global__ __launch_bounds__(256, 2) void k_fold_left_inv(const T* __restrict__ 
 
 // Forward along x (contraction over the columns of A's rows):
 // C[r][m] = sum_{k<bk} fold_blk(A[r])[k] F^T_blk[k][i], blk = m / bk, i = m % bk.
-template <typename T, int TM, int TN, int TKS>
+// SRC: the rows come from the caller's FP64 interior array ep.src (any 8-byte
+// alignment, padding rows zero) instead of the padded tensor: a stand-alone
+// solve without the copy into it (63^2 FP32 29.1 -> 20.8 us, 255^2 28.2 -> 24.8;
+// where, see direct_rhs in qn_api.cpp).
+template <typename T, int TM, int TN, int TKS, int SRC>
 __global__ __launch_bounds__(256, 2) void k_fold_right_fwd(const T* __restrict__ A,
                                                            const T* __restrict__ FeT,
                                                            const T* __restrict__ FoT,
@@ -558,6 +567,16 @@ __global__ __launch_bounds__(256, 2) void k_fold_right_fwd(const T* __restrict__
   // happens at the LDS store so the loads overlap the MFMA phase.
   V rlo[NA], rhi[NA], rb[NB];
   int kpre = 0;
+  const double* drow[SRC ? NA : 1];  // rows of ep.src, NULL: padding
+  if constexpr (SRC) {
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+      const int r = r0 + min((tid + 256 * i) / (TK / VE), TM - 1);
+      const int p = r / ep.py, y = r - p * ep.py, c = p / ep.pz, z = p - c * ep.pz;
+      drow[i] = y < ep.ny && z < ep.nz
+                    ? ep.src + (((long long)c * ep.nz + z) * ep.ny + y) * ep.nx : nullptr;
+    }
+  }
   auto gload = [&](int k0) {
     kpre = k0;
 #pragma unroll
@@ -565,6 +584,18 @@ __global__ __launch_bounds__(256, 2) void k_fold_right_fwd(const T* __restrict__
       const int v = tid + 256 * i;
       if (v < TM * TK / VE) {
         const int row = v / (TK / VE), kv = (v % (TK / VE)) * VE;
+        if constexpr (SRC) {
+#pragma unroll
+          for (int e = 0; e < VE; ++e) {
+            const int k = k0 + kv + e;
+            rlo[i][e] = rhi[i][e] = T(0);
+            if (drow[i]) {
+              rlo[i][e] = (T)drow[i][min(k, na - 1)];
+              rhi[i][e] = (T)drow[i][k < h ? na - 1 - k : 0];
+            }
+          }
+          continue;
+        }
         const T* src = A + (long long)(r0 + row) * P2;
         rlo[i] = *reinterpret_cast<const V*>(src + k0 + kv);
 #pragma unroll
@@ -916,8 +947,12 @@ hipError_t rfwd(const FoldOperands& f, const T* A, T* C, const FoldAxis& ax, int
 #define QN_RFWD(TM_, TN_, TK_)                                                                   \
   if (t.tm == TM_ && t.tn == TN_ && t.tk == TK_) {                                               \
     const unsigned g = (unsigned)((long long)(rows / TM_) * (2 * ax.bk / TN_));                  \
-    hipLaunchKernelGGL((k_fold_right_fwd<T, TM_, TN_, TK_>), dim3(g), dim3(256), 0, st, A, FeT, \
-                       FoT, C, ax, rows, ep);                                                    \
+    if (ep.src)                                                                                  \
+      hipLaunchKernelGGL((k_fold_right_fwd<T, TM_, TN_, TK_, 1>), dim3(g), dim3(256), 0, st, A,  \
+                         FeT, FoT, C, ax, rows, ep);                                             \
+    else                                                                                         \
+      hipLaunchKernelGGL((k_fold_right_fwd<T, TM_, TN_, TK_, 0>), dim3(g), dim3(256), 0, st, A,  \
+                         FeT, FoT, C, ax, rows, ep);                                             \
     return hipGetLastError();                                                                    \
   }
   QN_RFWD(128, 128, 0)

@@ -72,9 +72,13 @@ struct Coef {
   int stride;
   double scale, beta;
   __device__ void get(long long inst, double& s, double& b) const {
-    const double* p = at + inst * stride;
-    s = at ? p[0] : scale;
-    b = at ? p[1] : beta;
+    s = scale;
+    b = beta;
+    if (at) {
+      const double* p = at + inst * stride;
+      s = p[0];
+      b = p[1];
+    }
   }
 };
 
@@ -84,6 +88,8 @@ struct EpiArgs {
   const double* lamY;   // eigenvalues along y (column index n / px), NULL in 2D
   Coef coef;
   double* dense;        // caller array (ncomp, nz, ny, nx) for the dense epilogues
+  const double* src;    // folded forward x product: caller array (ncomp, nz, ny, nx) read instead
+                        // of the padded tensor, or NULL
   int px, py, pz;       // padded extents
   int nx, ny, nz;       // interior extents
   // Batched solver: slabs / row blocks belong to instance (index % inst_mod);
