@@ -118,7 +118,12 @@ dim3 sem_grid(int ox, int oy, int oz) {
 // halo strips (the x and y bands), its own values written from the window, so
 // each node of U is fetched from global memory about once plus the halo
 // share.  Tiles are dealt to the XCDs in contiguous ranges (x fastest), so the
-// halo lines a tile shares with its neighbours meet in one L2.
+// halo lines a tile shares with its neighbours meet in one L2.  The loads of
+// the next plane are in flight while one is computed, the staged plane is
+// double-buffered (one barrier per plane) and for short bands the thread's own x
+// and y coefficients stay in registers: 255^3, K = 2: 127 us, 153 with the
+// loads, two barriers and coefficient reads in the plane itself (24 bytes a
+// point at the copy rate: 82).
 constexpr int TX = 64, TY = 8;
 
 template <int K, typename TO>
@@ -126,7 +131,8 @@ __global__ __launch_bounds__(TX * TY) void k_sem_residual3(ResidualArgs a) {
   constexpr int W = 2 * K + 1;
   constexpr int NH = 2 * K * TY + 2 * K * TX;           // halo cells per plane
   constexpr int NS = (NH + TX * TY - 1) / (TX * TY);    // halo slots per thread
-  __shared__ double tile[TY + 2 * K][TX + 2 * K];
+  constexpr bool REG = K <= 4;                          // x and y bands of the thread in registers
+  __shared__ double tile[2][TY + 2 * K][TX + 2 * K];
   __shared__ double cx[TX][W], cy[TY][W];               // x and y bands of the tile
   __shared__ double red[TX * TY / 64][4];
   if (a.stop && *a.stop) return;
@@ -178,39 +184,64 @@ __global__ __launch_bounds__(TX * TY) void k_sem_residual3(ResidualArgs a) {
       if (gxh >= 0 && gxh < nx && gyh >= 0 && gyh < ny) ho[j] = (long long)gyh * nx + gxh;
     }
   }
+  // plane z + 1's halo, source and potential and plane z + 1 + K of the column
+  // are in flight while plane z is computed
+  auto at = [&](const double* p, int z) {
+    return (col && z < z1 && z < nz) ? p[(long long)z * plane + c] : 0.0;
+  };
+  double halo[NS], f, pv, wn = 0.0;
+  auto fetch = [&](int z) {
+#pragma unroll
+    for (int j = 0; j < NS; ++j)
+      halo[j] = (z < z1 && z < nz && ho[j] >= 0) ? a.U[(long long)z * plane + ho[j]] : 0.0;
+    f = at(a.F, z);
+    pv = a.pot ? at(a.pot, z) : 0.0;
+  };
+  fetch(z0);
+  __syncthreads();  // the bands
+  double bx_[REG ? W : 1], by_[REG ? W : 1];
+  if constexpr (REG) {
+#pragma unroll
+    for (int d = 0; d < W; ++d) {
+      bx_[d] = cx[tx][d];
+      by_[d] = cy[ty][d];
+    }
+  }
   double s_r = 0.0, s_f = 0.0, mn = DBL_MAX, mx = -DBL_MAX;
   for (int z = z0; z < z1; ++z) {
     const bool zin = z < nz;
-    tile[ty + K][tx + K] = win[K];
+    double (&tl)[TY + 2 * K][TX + 2 * K] = tile[(z - z0) & 1];
+    tl[ty + K][tx + K] = win[K];
 #pragma unroll
     for (int j = 0; j < NS; ++j)
-      if (hs[j] >= 0)
-        (&tile[0][0])[hs[j]] = (zin && ho[j] >= 0) ? a.U[(long long)z * plane + ho[j]] : 0.0;
-    __syncthreads();
+      if (hs[j] >= 0) (&tl[0][0])[hs[j]] = halo[j];
+    __syncthreads();  // (the other buffer is read by no wave from here on)
+    const double fz = f, pz = pv;
+    wn = ld(z + 1 + K);
+    fetch(z + 1);
     const long long o = (long long)z * a.r_zstride + (long long)y * a.r_ystride + x;
     if (col && zin) {
-      const long long i = (long long)z * plane + c;
       const double* hz = a.hb[2] + (long long)z * W;  // uniform over the workgroup
       double lap = 0.0;
 #pragma unroll
       for (int d = 0; d < W; ++d)
-        lap += cx[tx][d] * tile[ty + K][tx + d] + cy[ty][d] * tile[ty + d][tx + K] + hz[d] * win[d];
-      const double u = win[K], f = a.F[i];
-      const double m = a.lin + (a.pot ? a.pot[i] : 0.0);
-      const double r = lap + a.cub * (u * u * u) + a.quad * (u * u) + m * u - f;
+        lap += (REG ? bx_[REG ? d : 0] : cx[tx][d]) * tl[ty + K][tx + d] +
+               (REG ? by_[REG ? d : 0] : cy[ty][d]) * tl[ty + d][tx + K] + hz[d] * win[d];
+      const double u = win[K];
+      const double m = a.lin + pz;
+      const double r = lap + a.cub * (u * u * u) + a.quad * (u * u) + m * u - fz;
       const double fu = 3.0 * a.cub * (u * u) + 2.0 * a.quad * u + m;
       s_r += r * r;
-      s_f += f * f;
+      s_f += fz * fz;
       mn = fmin(mn, fu);
       mx = fmax(mx, fu);
       reinterpret_cast<TO*>(a.R)[o] = (TO)r;
     } else if (x < a.ox && y < a.oy) {
       reinterpret_cast<TO*>(a.R)[o] = (TO)0.0;
     }
-    __syncthreads();  // the tile is restaged for the next plane
 #pragma unroll
     for (int d = 0; d < W - 1; ++d) win[d] = win[d + 1];
-    win[W - 1] = ld(z + 1 + K);
+    win[W - 1] = wn;
   }
   const int lane = tid & 63, wv = tid >> 6;
   s_r = wsum(s_r);
