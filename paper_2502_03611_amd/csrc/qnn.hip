@@ -201,9 +201,12 @@ __global__ __launch_bounds__(512) void k_conv32(const float* __restrict__ in,
 // blockIdx + gridDim, ...; the next tile's input is loaded into registers
 // while the matrix cores work on the current one, and each A fragment serves
 // both halves of the output channels.  k_conv32 stages every tile twice (once
-// per half) with nothing else resident on the CU to cover it.  Same
-// accumulation order, so the same bits.  16 x 255^2: MODE 0 0.37 -> 0.25 ms,
-// MODE 1 0.44 -> 0.30 ms (FP32 matrix-core floor 0.12 ms).
+// per half) with nothing else resident on the CU to cover it.  A tile's outputs
+// (GELU or its derivative) are formed and stored an eighth per tap of the next
+// tile, beside the other waves' matrix instructions (at the end of the tile:
+// step 2.80 against 2.75 ms).  Same accumulation order, so the same bits.
+// 16 x 255^2: MODE 0 0.37 -> 0.25 ms, MODE 1 0.44 -> 0.28 ms (FP32 matrix-core
+// floor 0.12 ms).
 template <int MODE>
 __global__ __launch_bounds__(512) void k_conv32_tiles(const float* __restrict__ in,
                                                       const float* __restrict__ wk,
@@ -233,7 +236,38 @@ __global__ __launch_bounds__(512) void k_conv32_tiles(const float* __restrict__ 
   };
   const int lane = tid & 63, wave = tid >> 6;
   const int lr = lane & 15, lk = lane >> 4;
-  int t = blockIdx.x;
+  // Outputs of tile t: part k = 0 .. 7 is the 16 pixels of row block k / 2 in
+  // the channels 16 (k % 2) + lr; its zprev values are loaded a part ahead.
+  f4v acc[4][2], done[4][2];
+  float zp[2][4];
+  auto place = [&](int t, int k, int q) {
+    const int tx = t % tiles_x, ty = (t / tiles_x) % tiles_y, b = t / (tiles_x * tiles_y);
+    const int y = ty * CT_Y + 2 * wave + (k >> 2), x = tx * CT_X + ((k >> 1) & 1) * 16 + 4 * lk + q;
+    return y < H && x < W ? (((long long)b * H + y) * W + x) * 32 + 16 * (k & 1) + lr : -1LL;
+  };
+  auto zload = [&](int t, int k) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const long long o = place(t, k, q);
+      zp[k & 1][q] = o >= 0 ? zprev[o] : 0.f;
+    }
+  };
+  auto emit = [&](int t, int k) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const long long o = place(t, k, q);
+      if (o < 0) continue;
+      const float v = done[k >> 1][k & 1][q];
+      if (MODE == 0) {
+        const float z = v + bias[16 * (k & 1) + lr];
+        if (out0) out0[o] = z;
+        out1[o] = gelu(z);
+      } else {
+        out0[o] = v * gelu_grad(zp[k & 1][q]);
+      }
+    }
+  };
+  int t = blockIdx.x, prev = -1;
   if (t < ntiles) gload(t);
   for (; t < ntiles; t += gridDim.x) {
     __syncthreads();  // every wave is done with the previous tile
@@ -244,13 +278,13 @@ __global__ __launch_bounds__(512) void k_conv32_tiles(const float* __restrict__ 
     }
     __syncthreads();
     if (t + (int)gridDim.x < ntiles) gload(t + gridDim.x);
-    const int tx = t % tiles_x, ty = (t / tiles_x) % tiles_y, b = t / (tiles_x * tiles_y);
-    const int y0 = ty * CT_Y, x0 = tx * CT_X;
-    f4v acc[4][2];
+    if (MODE == 1 && prev >= 0) zload(prev, 0);
 #pragma unroll
     for (int i = 0; i < 4; ++i) acc[i][0] = acc[i][1] = f4v{0, 0, 0, 0};
+#pragma unroll
     for (int tap = 0; tap < 9; ++tap) {
       const int dy = tap / 3, dx = tap % 3;
+      if (MODE == 1 && tap < 7 && prev >= 0) zload(prev, tap + 1);
 #pragma unroll
       for (int c0 = 0; c0 < 32; c0 += 4) {
         const float* bw = &s_w[(tap * 32 + c0 + lk) * 32 + lr];
@@ -263,29 +297,22 @@ __global__ __launch_bounds__(512) void k_conv32_tiles(const float* __restrict__ 
           acc[mb][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b1, acc[mb][1], 0, 0, 0);
         }
       }
+      // an eighth of the previous tile's outputs, beside the other waves'
+      // matrix instructions
+      if (tap < 8 && prev >= 0) emit(prev, tap);
     }
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb) {
-      const int y = y0 + 2 * wave + (mb >> 1);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int x = x0 + (mb & 1) * 16 + 4 * lk + q;
-        if (y >= H || x >= W) continue;
-        const long long base = (((long long)b * H + y) * W + x) * 32;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const int c = 16 * h + lr;
-          const float v = acc[mb][h][q];
-          if (MODE == 0) {
-            const float z = v + bias[c];
-            if (out0) out0[base + c] = z;
-            out1[base + c] = gelu(z);
-          } else {
-            out0[base + c] = v * gelu_grad(zprev[base + c]);
-          }
-        }
-      }
+    for (int i = 0; i < 4; ++i) {
+      done[i][0] = acc[i][0];
+      done[i][1] = acc[i][1];
     }
+    prev = t;
+  }
+  if (prev < 0) return;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    if (MODE == 1) zload(prev, k);
+    emit(prev, k);
   }
 }
 
