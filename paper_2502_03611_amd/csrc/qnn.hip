@@ -202,13 +202,15 @@ __global__ __launch_bounds__(512) void k_conv32(const float* __restrict__ in,
 // while the matrix cores work on the current one, and each A fragment serves
 // both halves of the output channels.  k_conv32 stages every tile twice (once
 // per half) with nothing else resident on the CU to cover it.  A tile's outputs
-// (GELU or its derivative) are formed and stored an eighth per tap of the next
-// tile, beside the other waves' matrix instructions (at the end of the tile:
-// step 2.80 against 2.75 ms).  Same accumulation order, so the same bits.
-// 16 x 255^2: MODE 0 0.37 -> 0.25 ms, MODE 1 0.44 -> 0.28 ms (FP32 matrix-core
-// floor 0.12 ms).
+// (GELU or its derivative) are formed and stored a quarter per two taps of the
+// next tile, beside the other waves' matrix instructions (at the end of the
+// tile: step 2.80 against 2.75 ms), and four waves per SIMD cover one another's
+// waits (eight waves of two rows: step 2.75 against 2.58 ms).  Same accumulation
+// order, so the same bits.  16 x 255^2: MODE 0 0.37 -> 0.23 ms, MODE 1 0.44 ->
+// 0.25 ms (FP32 matrix-core floor 0.12 ms).
+constexpr int CT_THREADS = 1024;  // 16 waves: one row of the tile each
 template <int MODE>
-__global__ __launch_bounds__(512) void k_conv32_tiles(const float* __restrict__ in,
+__global__ __launch_bounds__(CT_THREADS) void k_conv32_tiles(const float* __restrict__ in,
                                                       const float* __restrict__ wk,
                                                       const float* __restrict__ bias,
                                                       const float* __restrict__ zprev,
@@ -217,9 +219,9 @@ __global__ __launch_bounds__(512) void k_conv32_tiles(const float* __restrict__ 
                                                       int tiles_x, int tiles_y, int ntiles) {
   __shared__ __attribute__((aligned(16))) float s_in[HY * HX * CP];
   __shared__ __attribute__((aligned(16))) float s_w[288 * 32];
-  constexpr int NI = (HY * HX * 8 + 511) / 512;  // float4 per thread and tile
+  constexpr int NI = (HY * HX * 8 + CT_THREADS - 1) / CT_THREADS;  // float4 per thread and tile
   const int tid = threadIdx.x;
-  for (int i = tid; i < 288 * 8; i += 512)
+  for (int i = tid; i < 288 * 8; i += CT_THREADS)
     reinterpret_cast<float4*>(s_w)[i] = reinterpret_cast<const float4*>(wk)[i];
   float4 ri[NI];
   auto gload = [&](int t) {
@@ -227,7 +229,7 @@ __global__ __launch_bounds__(512) void k_conv32_tiles(const float* __restrict__ 
     const int y0 = ty * CT_Y, x0 = tx * CT_X;
 #pragma unroll
     for (int n = 0; n < NI; ++n) {
-      const int i = tid + n * 512, c4 = i & 7, pix = i >> 3;
+      const int i = tid + n * CT_THREADS, c4 = i & 7, pix = i >> 3;
       const int yy = y0 + pix / HX - 1, xx = x0 + pix % HX - 1;
       ri[n] = make_float4(0.f, 0.f, 0.f, 0.f);
       if (pix < HY * HX && yy >= 0 && yy < H && xx >= 0 && xx < W)
@@ -236,13 +238,13 @@ __global__ __launch_bounds__(512) void k_conv32_tiles(const float* __restrict__ 
   };
   const int lane = tid & 63, wave = tid >> 6;
   const int lr = lane & 15, lk = lane >> 4;
-  // Outputs of tile t: part k = 0 .. 7 is the 16 pixels of row block k / 2 in
+  // Outputs of tile t: part k = 0 .. 3 is the 16 pixels of row block k / 2 in
   // the channels 16 (k % 2) + lr; its zprev values are loaded a part ahead.
-  f4v acc[4][2], done[4][2];
+  f4v acc[2][2], done[2][2];
   float zp[2][4];
   auto place = [&](int t, int k, int q) {
     const int tx = t % tiles_x, ty = (t / tiles_x) % tiles_y, b = t / (tiles_x * tiles_y);
-    const int y = ty * CT_Y + 2 * wave + (k >> 2), x = tx * CT_X + ((k >> 1) & 1) * 16 + 4 * lk + q;
+    const int y = ty * CT_Y + wave, x = tx * CT_X + (k >> 1) * 16 + 4 * lk + q;
     return y < H && x < W ? (((long long)b * H + y) * W + x) * 32 + 16 * (k & 1) + lr : -1LL;
   };
   auto zload = [&](int t, int k) {
@@ -273,36 +275,35 @@ __global__ __launch_bounds__(512) void k_conv32_tiles(const float* __restrict__ 
     __syncthreads();  // every wave is done with the previous tile
 #pragma unroll
     for (int n = 0; n < NI; ++n) {
-      const int i = tid + n * 512;
+      const int i = tid + n * CT_THREADS;
       if (i < HY * HX * 8) *reinterpret_cast<float4*>(&s_in[(i >> 3) * CP + (i & 7) * 4]) = ri[n];
     }
     __syncthreads();
     if (t + (int)gridDim.x < ntiles) gload(t + gridDim.x);
     if (MODE == 1 && prev >= 0) zload(prev, 0);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) acc[i][0] = acc[i][1] = f4v{0, 0, 0, 0};
+    for (int i = 0; i < 2; ++i) acc[i][0] = acc[i][1] = f4v{0, 0, 0, 0};
 #pragma unroll
     for (int tap = 0; tap < 9; ++tap) {
       const int dy = tap / 3, dx = tap % 3;
-      if (MODE == 1 && tap < 7 && prev >= 0) zload(prev, tap + 1);
+      if (MODE == 1 && tap % 2 == 0 && tap < 6 && prev >= 0) zload(prev, tap / 2 + 1);
 #pragma unroll
       for (int c0 = 0; c0 < 32; c0 += 4) {
         const float* bw = &s_w[(tap * 32 + c0 + lk) * 32 + lr];
         const float b0 = bw[0], b1 = bw[16];
 #pragma unroll
-        for (int mb = 0; mb < 4; ++mb) {
-          const int r = 2 * wave + (mb >> 1), xh = (mb & 1) * 16;
-          const float a = s_in[((r + dy) * HX + xh + lr + dx) * CP + c0 + lk];
+        for (int mb = 0; mb < 2; ++mb) {
+          const float a = s_in[((wave + dy) * HX + 16 * mb + lr + dx) * CP + c0 + lk];
           acc[mb][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b0, acc[mb][0], 0, 0, 0);
           acc[mb][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b1, acc[mb][1], 0, 0, 0);
         }
       }
-      // an eighth of the previous tile's outputs, beside the other waves'
+      // a quarter of the previous tile's outputs, beside the other waves'
       // matrix instructions
-      if (tap < 8 && prev >= 0) emit(prev, tap);
+      if (tap % 2 == 0 && tap < 8 && prev >= 0) emit(prev, tap / 2);
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < 2; ++i) {
       done[i][0] = acc[i][0];
       done[i][1] = acc[i][1];
     }
@@ -310,7 +311,7 @@ __global__ __launch_bounds__(512) void k_conv32_tiles(const float* __restrict__ 
   }
   if (prev < 0) return;
 #pragma unroll
-  for (int k = 0; k < 8; ++k) {
+  for (int k = 0; k < 4; ++k) {
     if (MODE == 1) zload(prev, k);
     emit(prev, k);
   }
@@ -318,12 +319,12 @@ __global__ __launch_bounds__(512) void k_conv32_tiles(const float* __restrict__ 
 
 constexpr int GT_Y = 8, GT_X = 32;            // weight-gradient pixel tile
 constexpr int GHY = GT_Y + 2, GHX = GT_X + 2;  // with halo
-constexpr int DS = 48;                         // LDS stride of the dz tile
+constexpr int DS = 48;                         // LDS pixel stride of its tiles (four pixels on distinct banks)
 
 // Weight gradient of a 32 -> 32 layer over 8 x 32 pixel tiles:
 // part[co*288 + ci*9 + tap] = sum_p dz[p][co] * act[p + tap][ci] and
 // part[9216 + co] = sum_p dz[p][co].  GEMM M = 32 (co) x N = 288 (tap, ci) x
-// K = 256 pixels per tile.  One workgroup per CU (98 KB of LDS) walks the
+// K = 256 pixels per tile.  One workgroup per CU (114 KB of LDS) walks the
 // tiles blockIdx, blockIdx + gridDim, ...: the next tile's loads are in
 // registers while the matrix cores work on the current one, each tile's FP32
 // sums are added to FP64 accumulators, and only one partial per half
@@ -336,7 +337,7 @@ __global__ __launch_bounds__(WG_THREADS) void k_conv32_wgrad(const float* __rest
                                                              const float* __restrict__ dz,
                                                              double* __restrict__ part, int H, int W,
                                                              int tiles_x, int tiles_y, int ntiles) {
-  __shared__ __attribute__((aligned(16))) float s_a[GHY * GHX * CP];
+  __shared__ __attribute__((aligned(16))) float s_a[GHY * GHX * DS];
   __shared__ __attribute__((aligned(16))) float s_d[GT_Y * GT_X * DS];
   constexpr int NA = (GHY * GHX * 8 + WG_THREADS - 1) / WG_THREADS;  // float4 per thread and tile
   constexpr int ND = GT_Y * GT_X * 8 / WG_THREADS;
@@ -378,7 +379,7 @@ __global__ __launch_bounds__(WG_THREADS) void k_conv32_wgrad(const float* __rest
 #pragma unroll
     for (int n = 0; n < NA; ++n) {
       const int i = tid + n * WG_THREADS;
-      if (i < GHY * GHX * 8) *reinterpret_cast<float4*>(&s_a[(i >> 3) * CP + (i & 7) * 4]) = ra[n];
+      if (i < GHY * GHX * 8) *reinterpret_cast<float4*>(&s_a[(i >> 3) * DS + (i & 7) * 4]) = ra[n];
     }
 #pragma unroll
     for (int n = 0; n < ND; ++n) {
@@ -390,16 +391,17 @@ __global__ __launch_bounds__(WG_THREADS) void k_conv32_wgrad(const float* __rest
     f4v acc[9];
 #pragma unroll
     for (int i = 0; i < 9; ++i) acc[i] = f4v{0, 0, 0, 0};
-    for (int kp = 128 * grp; kp < 128 * grp + 128; kp += 4) {
-      const int p = kp + lk;
-      const int py = p / GT_X, px = p % GT_X;
-      const float a = s_d[p * DS + mb * 16 + lr];
+    for (int py = 4 * grp; py < 4 * grp + 4; ++py) {
+      const float* pd = &s_d[(py * GT_X + lk) * DS + mb * 16 + lr];
+      const float* pa = &s_a[(py * GHX + lk) * DS + (wave >> 1) * 16 + lr];
 #pragma unroll
-      for (int i = 0; i < 9; ++i) {
-        const int nb = (wave >> 1) + 2 * i;
-        const int tap = nb >> 1, ci = (nb & 1) * 16 + lr;
-        const float bv = s_a[((py + tap / 3) * GHX + px + tap % 3) * CP + ci];
-        acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, bv, acc[i], 0, 0, 0);
+      for (int px = 0; px < GT_X; px += 4) {
+        const float a = pd[px * DS];
+#pragma unroll
+        for (int tap = 0; tap < 9; ++tap) {
+          const float bv = pa[((tap / 3) * GHX + px + tap % 3) * DS];
+          acc[tap] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, bv, acc[tap], 0, 0, 0);
+        }
       }
     }
 #pragma unroll
@@ -715,7 +717,7 @@ static void launch_conv32(const float* in, const float* wk, const float* bias, c
   // at least two tiles per CU keep the tile loop's loads ahead of its
   // arithmetic; below that the split over output-channel halves fills the chip
   if ((long long)tx * ty * batch >= 512) {
-    hipLaunchKernelGGL((k_conv32_tiles<MODE>), dim3(256), dim3(512), 0, st, in, wk, bias, zprev, out0,
+    hipLaunchKernelGGL((k_conv32_tiles<MODE>), dim3(256), dim3(CT_THREADS), 0, st, in, wk, bias, zprev, out0,
                        out1, H, W, tx, ty, tx * ty * batch);
     return;
   }
