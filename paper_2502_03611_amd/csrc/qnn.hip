@@ -47,11 +47,13 @@ __device__ inline float gelu_grad(float x) {
 // ---------------------------------------------------------------- layer 1
 
 // Layer 1: x0 = (f / 50, v0); z1 = b1 + W1 * x0; a1 = gelu(z1).  One thread
-// per pixel computes all 32 channels; the weights (32, 2, 3, 3) are staged in
-// LDS and read at wave-uniform addresses (broadcast).  The 128 x 32 outputs
-// of a workgroup go through LDS (row stride 33: conflict-free columns) so that
-// the stores are one contiguous 16 KB run.  TRAIN also keeps x0 and z1 for the
-// backward pass.
+// per pixel computes all 32 channels; the weights (32, 2, 3, 3) are read at
+// uniform addresses into scalar registers (from LDS they were one broadcast read
+// per multiply-add).  The 128 x 32 values of z1 of a workgroup go through LDS
+// (row stride 33: conflict-free columns) so that the stores are one contiguous
+// 16 KB run, and GELU is applied on the way out.  TRAIN also keeps x0 and z1 for
+// the backward pass.  Bound by those stores: 16 x 255^2 76 us (from 124, 64-bit
+// index divisions included), 54 at the copy rate.
 constexpr int L1_PX = 128;
 template <bool TRAIN>
 __global__ __launch_bounds__(L1_PX) void k_in_fwd(const double* __restrict__ f,
@@ -60,16 +62,13 @@ __global__ __launch_bounds__(L1_PX) void k_in_fwd(const double* __restrict__ f,
                                                   float* __restrict__ x0, float* __restrict__ z1,
                                                   float* __restrict__ a1, int H, int W,
                                                   long long npix) {
-  __shared__ float sw[L1_SIZE];
-  __shared__ float sz[TRAIN ? L1_PX * 33 : 1];
-  __shared__ float sa[L1_PX * 33];
+  __shared__ float sz[L1_PX * 33];
   const int l = threadIdx.x;
-  for (int i = l; i < L1_SIZE; i += L1_PX) sw[i] = p1[i];
-  __syncthreads();
   const long long p0 = (long long)blockIdx.x * L1_PX, p = p0 + l;
   if (p < npix) {
-    const int x = (int)(p % W), y = (int)((p / W) % H);
-    const long long b = p / ((long long)W * H);
+    const unsigned row = (unsigned)p / W;  // (npix is an int)
+    const int x = (int)((unsigned)p - row * W), y = (int)(row % H);
+    const long long b = row / H;
     float nb[CIN0][9];
 #pragma unroll
     for (int t = 0; t < 9; ++t) {
@@ -85,13 +84,12 @@ __global__ __launch_bounds__(L1_PX) void k_in_fwd(const double* __restrict__ f,
     }
 #pragma unroll 4
     for (int c = 0; c < 32; ++c) {
-      float s = sw[32 * CIN0 * 9 + c];
+      float s = p1[32 * CIN0 * 9 + c];
 #pragma unroll
       for (int ci = 0; ci < CIN0; ++ci)
 #pragma unroll
-        for (int t = 0; t < 9; ++t) s += sw[(c * CIN0 + ci) * 9 + t] * nb[ci][t];
-      if (TRAIN) sz[l * 33 + c] = s;
-      sa[l * 33 + c] = gelu(s);
+        for (int t = 0; t < 9; ++t) s += p1[(c * CIN0 + ci) * 9 + t] * nb[ci][t];
+      sz[l * 33 + c] = s;
     }
   }
   __syncthreads();
@@ -100,8 +98,9 @@ __global__ __launch_bounds__(L1_PX) void k_in_fwd(const double* __restrict__ f,
   for (int j = 0; j < 32; ++j) {
     const int idx = j * L1_PX + l, px = idx >> 5, c = idx & 31;
     if (px < np) {
-      if (TRAIN) z1[(p0 + px) * 32 + c] = sz[px * 33 + c];
-      a1[(p0 + px) * 32 + c] = sa[px * 33 + c];
+      const float z = sz[px * 33 + c];
+      if (TRAIN) z1[(p0 + px) * 32 + c] = z;
+      a1[(p0 + px) * 32 + c] = gelu(z);
     }
   }
 }
@@ -463,12 +462,13 @@ __global__ __launch_bounds__(256) void k_out_fwd(const float* __restrict__ a4,
 #pragma unroll
     for (int t = 0; t < 9; ++t) w[j][t] = sw[(4 * c4 + j) * 9 + t];
   const float bias = sw[288];
-  const long long stride = (long long)gridDim.x * 32;
+  const unsigned stride = gridDim.x * 32;
   // The trip count is uniform across each group of eight lanes, so the
   // shuffles below always find their partners.
-  for (long long p = ((long long)blockIdx.x * 256 + threadIdx.x) >> 3; p < npix; p += stride) {
-    const int x = (int)(p % W), y = (int)((p / W) % H);
-    const long long b = p / ((long long)W * H);
+  for (unsigned p = (blockIdx.x * 256 + threadIdx.x) >> 3; p < (unsigned)npix; p += stride) {
+    const unsigned row = p / W;
+    const int x = (int)(p - row * W), y = (int)(row % H);
+    const long long b = row / H;
     float s = 0.f;
 #pragma unroll
     for (int t = 0; t < 9; ++t) {
