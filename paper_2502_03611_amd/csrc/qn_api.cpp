@@ -606,11 +606,16 @@ void choose_fast(qn_ctx c) {
   // the same pass): 100 x 63 x 63 with both short axes factored 57, dense 53 us
   // per iteration; 31 x 31 x 200, last axis short, 64 and 81.
   const bool small = (double)c->ncomp * c->n[0] * c->n[1] * c->n[2] < 1048576.0;
-  if (small && !c->fast[c->dim - 1])
+  auto strips = [&] {
+    const bool dense[3] = {!c->fast[0], !c->fast[1], !c->fast[2]};
+    return c->fold && use_strips(c->dim, c->n, c->p, dense, c->ncomp, c->prec == QN_PREC_FP32);
+  };
+  c->strip = strips();
+  if (!c->strip && small && !c->fast[c->dim - 1]) {
     for (int a = 0; a < c->dim; ++a) c->fast[a] = c->fast[a] && c->n[a] > 64;
+    c->strip = strips();
+  }
   for (int a = 0; a < c->dim; ++a) c->any_fast = c->any_fast || c->fast[a];
-  const bool dense[3] = {!c->fast[0], !c->fast[1], !c->fast[2]};
-  c->strip = c->fold && use_strips(c->dim, c->n, c->p, dense, c->ncomp);
   // An odd number of 128-byte lines per plane, so that the z passes' strides do
   // not return to the same memory channels (511^3 factored: plane stride 2 MiB
   // 0.82 ms for the z pass, 2 MiB - 4 KiB 0.70, odd 0.69; the y passes 0.47 and

@@ -540,7 +540,7 @@ qn_status qnb_setup_ex(int32_t count, const int32_t* n, const int32_t* ncomp, in
     }
     const int ext[2] = {k.n, k.n}, pad[2] = {k.p, k.p};
     const bool dense[2] = {true, true};
-    k.strip = c->fold && !k.fast && use_strips(2, ext, pad, dense, k.ncomp * k.K);
+    k.strip = c->fold && !k.fast && use_strips(2, ext, pad, dense, k.ncomp * k.K, c->prec == QN_PREC_FP32);
     const int ex = k.interior() ? k.n : k.p;
     k.bpi = residual_max_blocks(ex, ex, 1, RESIDUAL_PLANAR_ROWS, true);
     k.off_part = off;

@@ -438,17 +438,24 @@ inline void fast_tables(int N, int Q, int R, bool neumann, double ih2, std::vect
 }
 
 // Whether the dense products of a solve take the strip form (qn_gemm_strip.h):
-// at least 2^20 values (below that a strip launch leaves the chip to too few
-// waves: 200^2 FP64 0.046 against 0.036 ms of tile launches) and at least 1.25
-// times as many matrix-core operations in the padded tiles as in the strips
-// (whose rate is 0.8-0.9 of the tiles': 255^3 0.73 against 0.67 ms at a ratio
-// of 1.0, 400^3 4.1 against 6.6 ms at 1.35, 200^3 0.41 against 0.52 ms at 1.9).
+// when the padded tiles do enough more matrix-core operations than the strips,
+// whose rate is 0.8-0.9 of the tiles' (255^3 0.73 against 0.67 ms at a ratio of
+// 1.0; 400^3 3.9 and 6.6 ms at 1.35, 200^3 0.40 and 0.52 ms at 1.9).  On smaller
+// grids a strip launch leaves the chip to too few waves and the ratio has to be
+// larger: from 2^20 to 2^22 values 1.5 in FP32 (127 x 127 x 66, 1.39: 93 against
+// 87 us an iteration), in 3D from 2^18 to 2^20 2.1 (60 x 70 x 64, 1.8: 60 and 54 us;
+// 66 x 31 x 200, 4.7: 72 and 126; 66^3, 5.1: 67 and 114), below that and in small
+// 2D never (52^3 35 against 29 us a solve, 200^2 46 and 36, 390^2 58 and 51).
 // Row strides stay below 2^26 elements (32-bit lane offsets of three rows).  n,
 // p, dense: extents, padded extents and which axes have a dense product.
-inline bool use_strips(int dim, const int* n, const int* p, const bool* dense, int fields) {
+inline bool use_strips(int dim, const int* n, const int* p, const bool* dense, int fields,
+                       bool fp32) {
   double values = fields, tiles = 0.0, strips = 0.0;
   for (int a = 0; a < dim; ++a) values *= n[a];
-  if (values < 1048576.0 || (dim == 3 && (double)p[0] * p[1] >= 67108864.0)) return false;
+  double least = 1.25;
+  if (values < 1048576.0) least = 2.1;
+  else if (values < 4194304.0 && fp32) least = 1.5;
+  if (values < (dim == 3 ? 262144.0 : 1048576.0) || (dim == 3 && (double)p[0] * p[1] >= 67108864.0)) return false;
   auto up16 = [](int v) { return (v + 15) / 16 * 16; };
   for (int a = 0; a < dim; ++a) {
     if (!dense[a]) continue;
@@ -462,7 +469,7 @@ inline bool use_strips(int dim, const int* n, const int* p, const bool* dense, i
     tiles += t;
     strips += s;
   }
-  return tiles > 1.25 * strips;
+  return tiles > least * strips;
 }
 
 }  // namespace qn

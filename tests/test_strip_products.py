@@ -31,6 +31,9 @@ def _pinned(s):
     ("cubic", (137, 138, 63), {}),                # FP64: x factored
     ("cubic", (200, 66, 90), {"boundary": "neumann", "lin": 1.0}),
     ("cubic", (133, 89, 101), {"discretization": "sem", "sem_order": 2}),
+    ("cubic", (66, 66, 66), {}),                  # below 2^20 values: padding of 128 about 66
+    ("system", (34, 37, 130), {}),
+    ("cubic", (31, 82, 127), {}),                 # FP64: z and x factored
 ])
 def test_strips_give_the_tiles_bits(problem, shape, kw, prec):
     if kw.get("discretization") == "sem":
