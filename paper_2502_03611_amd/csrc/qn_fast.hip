@@ -267,9 +267,10 @@ __global__ __launch_bounds__(FAST_THREADS, FAM == EVEN && EPI == 0 ? 4 : 2) void
 #undef X
 }
 
-// Kernels of more than 64 KB of LDS need the limit raised once per device.
-template <typename K>
-hipError_t allow_lds(K kernel, size_t bytes) {
+// A kernel's limit of 64 KB of LDS is raised the first time it needs more, once
+// per kernel and device (the kernels share one type, so Kern is a value).
+template <auto Kern>
+hipError_t allow_lds(size_t bytes) {
   static std::atomic<unsigned long long> done{0};  // one bit per device
   if (bytes <= 64 * 1024) return hipSuccess;
   int dev = 0;
@@ -277,7 +278,7 @@ hipError_t allow_lds(K kernel, size_t bytes) {
   if (e != hipSuccess) return e;
   const unsigned long long bit = 1ull << (dev & 63);
   if (done.load(std::memory_order_relaxed) & bit) return hipSuccess;
-  e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+  e = hipFuncSetAttribute(reinterpret_cast<const void*>(Kern),
                           hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   if (e == hipSuccess) done.fetch_or(bit, std::memory_order_relaxed);
   return e;
@@ -287,8 +288,10 @@ constexpr size_t kLdsTarget = 80 * 1024;  // two workgroups per CU
 
 int round64(int v) { return (v + 63) & ~63; }
 
-template <typename K>
-hipError_t lines_launch(K kern, int lc, FastArgs a, int nouter, hipStream_t st) {
+template <int FAM, int DIV>
+hipError_t lines_launch(FastArgs a, int nouter, hipStream_t st) {
+  constexpr auto kern = k_fast_lines<FAM, DIV>;
+  int lc = FAM == BIG ? 3 : 4;
   const int qh = a.ax.Q / 2 + 1, rh = a.ax.R / 2 + 1;
   auto bytes = [&](int l) { return (size_t)qh * rh * sizeof(Pair<T>) << l; };
   while (lc > 2 && bytes(lc) > kLdsTarget) --lc;
@@ -301,7 +304,7 @@ hipError_t lines_launch(K kern, int lc, FastArgs a, int nouter, hipStream_t st) 
   a.xsplit = tiles(a.ce, lc);
   a.xtiles = a.xsplit + tiles(a.co, lc);
   const int nt = round64(std::max(qh, rh) << lc);
-  hipError_t e = allow_lds(kern, bytes(lc));
+  hipError_t e = allow_lds<kern>(bytes(lc));
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3((unsigned)a.xtiles * nouter), dim3(nt), bytes(lc), st, a);
   return hipGetLastError();
@@ -316,8 +319,8 @@ hipError_t rows_launch(FastArgs a, hipStream_t st) {
   // small grids: fewer rows per workgroup (but a whole wave) until every CU has one
   lines = std::min(lines, std::max(std::max(1, 64 / nb), a.rows / 256));
   a.lines = lines;
-  auto kern = k_fast_rows<FAM, EPI>;
-  hipError_t e = allow_lds(kern, per * lines);
+  constexpr auto kern = k_fast_rows<FAM, EPI>;
+  hipError_t e = allow_lds<kern>(per * lines);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3((a.rows + lines - 1) / lines), dim3(round64(lines * nb)),
                      per * lines, st, a);
@@ -334,15 +337,9 @@ int family(const FastAxis& ax) {
 
 hipError_t launch_fast_lines(const FastArgs& a, int nouter, bool divide, hipStream_t st) {
   switch (family(a.ax)) {
-    case EVEN:
-      return divide ? lines_launch(k_fast_lines<EVEN, 1>, 4, a, nouter, st)
-                    : lines_launch(k_fast_lines<EVEN, 0>, 4, a, nouter, st);
-    case ANY:
-      return divide ? lines_launch(k_fast_lines<ANY, 1>, 4, a, nouter, st)
-                    : lines_launch(k_fast_lines<ANY, 0>, 4, a, nouter, st);
-    default:
-      return divide ? lines_launch(k_fast_lines<BIG, 1>, 3, a, nouter, st)
-                    : lines_launch(k_fast_lines<BIG, 0>, 3, a, nouter, st);
+    case EVEN: return divide ? lines_launch<EVEN, 1>(a, nouter, st) : lines_launch<EVEN, 0>(a, nouter, st);
+    case ANY: return divide ? lines_launch<ANY, 1>(a, nouter, st) : lines_launch<ANY, 0>(a, nouter, st);
+    default: return divide ? lines_launch<BIG, 1>(a, nouter, st) : lines_launch<BIG, 0>(a, nouter, st);
   }
 }
 

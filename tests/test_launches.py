@@ -1,0 +1,38 @@
+"""Launches read on the CPU (launch_trace.py): which form each mode product
+takes and whether its launch is one that the device accepts."""
+
+import os
+
+import pytest
+
+from launch_trace import CLANG, forms, trace
+
+pytestmark = pytest.mark.skipif(not os.path.exists(CLANG), reason="needs the ROCm host compiler")
+
+KB64, KB160 = 64 * 1024, 160 * 1024
+
+
+def test_every_launch_fits_the_device():
+    """Kernels of more than 64 KB of dynamic LDS have had their limit raised, each
+    of them and on each device; the limits of a workgroup and of a launch hold;
+    a factored pass keeps a workgroup's rows within its 32-bit byte offsets."""
+    long_axes = [(511, 511, 511), (639, 33), (33, 639), (1023, 95), (2047, 17), (17, 2047), (15, 799, 63),
+                 (799, 15, 31), (31, 15, 799), (399, 399, 399), (95, 95, 95), (255, 255)]
+    calls = [{"shape": s, "do": ["solve", "iterate", ["device", 3], "solve", "iterate"]} for s in long_axes]
+    calls += [{"shape": [n + 2 for n in s], "boundary": "neumann", "do": ["solve"]} for s in long_axes]
+    # the widest gap between the components of a padded tensor
+    calls += [{"shape": (65, 4093, 2047), "problem": "system", "do": ["solve", "iterate"]}]
+    calls += [{"sizes": [255] * 8 + [1023] * 2 + [799, 63], "ncomp": [1] * 11 + [2], "precision": "fp64"}]
+    raised, large = set(), set()
+    for rows in trace(calls):
+        for r in rows:
+            if r["kind"] == "raise":
+                raised.add((r["device"], r["name"]))
+                continue
+            assert 0 < r["block"] <= 1024 and r["lds"] <= KB160, r
+            assert 0 < r["grid"] and r["grid"] * r["block"] < 2 ** 32, r
+            assert 0 <= r["span"] < 2 ** 32 - 8 * 4096, r
+            if r["lds"] > KB64:
+                assert (r["device"], r["name"]) in raised, r
+                large.add(r["name"])
+    assert len(large) >= 4, large
