@@ -378,7 +378,9 @@ qn_status qn_tile_info(qn_ctx ctx, int32_t i, int32_t* info4);
 /* Pin launch i to the tile info4 (same encoding as qn_tile_info), e.g. one
  * that qn_autotune chose for another context of the same grid.  The shape must
  * be instantiated and admissible for the launch (QN_ERR_INVALID otherwise);
- * the other launches keep their current tiles.  Host only. */
+ * the other launches keep their current tiles.  On a launch that is not issued
+ * because its axis runs factored (see qn_autotune) the tile is recorded for
+ * qn_tile_info and changes nothing else.  Host only. */
 qn_status qn_set_tile(qn_ctx ctx, int32_t i, const int32_t* info4);
 
 /* Kernel timing (contexts created with options.timing != 0).  qn_timing_read

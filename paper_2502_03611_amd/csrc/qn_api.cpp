@@ -109,8 +109,9 @@ struct qn_ctx_s {
   hipStream_t stream = nullptr;
   bool fold = true;       // reflection-folded transforms (FP64/FP32); dense for split-bf16
   FoldAxis ax[3] = {};
-  FoldTile tile[6] = {};  // per mode-product launch of the folded solve (after qn_autotune)
-  bool tuned = false;
+  FoldTile tile[6] = {};  // chosen tile of launch i of the solve, where bit i of pins is set
+  unsigned pins = 0;
+  bool tuned = false;     // a launch that is issued has one (those of factored axes are not)
   std::vector<double> hS[3], hlam[3];  // dense S or folded FeT|FoT|Fe|Fo; lam (split if folded)
   // 3D split-bf16 solves with folded forward y and z products: half extents
   // of the folded layouts and the forward operands (bf16 parts) of y and z
@@ -569,9 +570,9 @@ int step_candidates(qn_ctx c, const FoldStep& f, FoldTile* out) {
   return n;
 }
 
-// Tile of launch i of the plan: the autotuned one, else the default rule.
+// Tile of launch i of the plan: the pinned or autotuned one, else the default rule.
 FoldTile step_tile(qn_ctx c, const FoldStep& f, int i) {
-  if (c->tuned) return c->tile[i];
+  if (c->pins >> i & 1) return c->tile[i];
   if (!c->fold) {
     long long mext, next;
     dense_extents(f, &mext, &next);
@@ -1532,6 +1533,7 @@ qn_status qn_autotune(qn_ctx c) {
   if (s != QN_OK) return s;
   if (c->all_fast || c->strip) {  // no tiled launch is issued: drop pinned tiles
     c->tuned = false;
+    c->pins = 0;
     return QN_OK;
   }
   hipEvent_t t0 = nullptr, t1 = nullptr;
@@ -1543,8 +1545,8 @@ qn_status qn_autotune(qn_ctx c) {
   if (e == hipSuccess) e = launch_zero(c->ws + c->off_W2, tbytes, c->stream);
   FoldStep st[6];
   const int ns = solve_plan(c, epi_args(c, Coef{nullptr, 0, 1.0, 1.0}, nullptr), EPI_STORE, st);
-  const bool was_tuned = c->tuned;
-  c->tuned = false;  // step_tile gives the default rule below
+  const unsigned pins = c->pins;
+  c->pins = 0;  // step_tile gives the default rule below
   FoldTile best[6] = {};
   for (int i = 0; i < ns && e == hipSuccess; ++i) {
     const FoldStep& f = st[i];
@@ -1571,10 +1573,11 @@ qn_status qn_autotune(qn_ctx c) {
   if (t0) (void)hipEventDestroy(t0);
   if (t1) (void)hipEventDestroy(t1);
   if (e != hipSuccess) {
-    c->tuned = was_tuned;
+    c->pins = pins;
     return hip_fail(c, e, "autotune");
   }
   for (int i = 0; i < 6; ++i) c->tile[i] = best[i];
+  c->pins = 63;
   c->tuned = true;
   return QN_OK;
 }
@@ -1613,10 +1616,10 @@ qn_status qn_set_tile(qn_ctx c, int32_t i, const int32_t* info4) {
     const FoldTile& t = cand[k];
     const int flags = kind + (t.paired ? 4 : 0) + t.tk;
     if (flags == info4[0] && t.tm == info4[2] && t.tn == info4[3]) {
-      if (!c->tuned)
-        for (int j = 0; j < ns; ++j) c->tile[j] = step_tile(c, st[j], j);
       c->tile[i] = t;
-      c->tuned = true;
+      c->pins |= 1u << i;
+      // (a factored axis runs as before, and so do the others)
+      if (!c->fast[st[i].axis]) c->tuned = true;
       return QN_OK;
     }
   }

@@ -36,3 +36,20 @@ def test_every_launch_fits_the_device():
                 assert (r["device"], r["name"]) in raised, r
                 large.add(r["name"])
     assert len(large) >= 4, large
+
+
+@pytest.mark.parametrize("shape,launch,want", [
+    ((102, 63, 201), 0, "TFTTFT"),   # x of a grid in strips with y factored: the dense axes run tiled
+    ((102, 63, 201), 1, "SFSSFS"),   # its y launches are not issued
+    ((102, 63, 201), 4, "SFSSFS"),
+    ((63, 137, 138), 2, "SFFFS"),    # z, in a grid with y and z factored
+    ((255, 255), 0, "FFF"),
+    ((255, 255), 2, "FFF"),
+    ((40, 127, 127), 3, "FFTTFF"),   # tiled beside factored axes already
+])
+def test_pinning_a_tile_moves_issued_launches_only(shape, launch, want):
+    rows, = trace([{"shape": shape, "do": [["pin", launch], "solve"]}])
+    assert forms(rows) == want
+    rows, = trace([{"shape": shape, "do": [["pin", launch], "autotune", "solve"]}])
+    before, = trace([{"shape": shape, "do": ["solve"]}])
+    assert forms(rows) == forms(before)  # autotune drops it
