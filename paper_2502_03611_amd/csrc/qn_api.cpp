@@ -325,10 +325,16 @@ ResidualArgs residual_args(qn_ctx c, const double* U, const double* F, double* R
   a.bc = c->bc;
   a.partials = c->at<double>(c->off_part);
   a.xfold = (!R_caller && c->xfold) ? c->hp[0] : 0;  // the x product reads it folded
-  if (!R_caller && c->interior()) {
+  // Interior extents also where tiles are pinned on a grid of strips, so that the
+  // partial sums, and with them the iteration's bits, do not depend on the pins;
+  // the padding is left as it is, since a fold product's padded rows and columns
+  // reach padded ones only (the contraction is masked past the extent).
+  if (!R_caller && (c->interior() || c->strip)) {
     a.ox = c->n[0];
     a.oy = c->n[1];
     a.oz = c->n[2];
+  }
+  if (!R_caller && c->interior()) {
     a.r_ystride = (int)c->fs[0];
     a.r_zstride = (int)c->fs[1];
     a.r_cstride = c->fs[2];

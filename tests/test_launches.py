@@ -53,3 +53,19 @@ def test_pinning_a_tile_moves_issued_launches_only(shape, launch, want):
     rows, = trace([{"shape": shape, "do": [["pin", launch], "autotune", "solve"]}])
     before, = trace([{"shape": shape, "do": ["solve"]}])
     assert forms(rows) == forms(before)  # autotune drops it
+
+
+@pytest.mark.parametrize("call", [
+    {"shape": (100, 110, 106)}, {"shape": (66, 134, 229), "precision": "fp32"},
+    {"shape": (34, 37, 130), "problem": "system"}, {"shape": (102, 63, 201)},
+    {"shape": (133, 89, 101), "sem_order": 2},
+])
+def test_pinned_tiles_keep_the_residual_launch(call):
+    """The residual's workgroups, and so the grouping of its partial sums, are the
+    same beside strips and beside pinned tiles."""
+    free, pinned = trace([dict(call, do=["iterate"]), dict(call, do=[["pin", 0], "iterate"])])
+    assert "S" in forms(free) and "S" not in forms(pinned)
+
+    def residual(rows):
+        return [(r["name"], r["grid"], r["block"]) for r in rows if "residual" in r.get("name", "")]
+    assert residual(free) and residual(free) == residual(pinned)
