@@ -595,8 +595,7 @@ FoldTile step_tile(qn_ctx c, const FoldStep& f, int i) {
 // (closer to the exact solve, 2e-7 against 5e-7), and callers of a single
 // reduced-precision solve would see other results.
 void choose_fast(qn_ctx c) {
-  c->any_fast = false;
-  c->all_fast = true;
+  double chain[3] = {0.0, 0.0, 0.0};
   for (int a = 0; a < c->dim; ++a) {
     const int off = c->bc == QN_BC_NEUMANN ? 0 : 1;
     FastAxis f{};
@@ -606,7 +605,6 @@ void choose_fast(qn_ctx c) {
     c->fast[a] = c->prec == QN_PREC_FP64 && c->sem_k == 0 && f.N >= 16 && fast_stages(f.N, &f.Q, &f.R) &&
                  (f.R / 2 + 1) * es + 64 < (1LL << 28);
     c->fx[a] = f;
-    c->all_fast = c->all_fast && c->fast[a];
   }
   // On a small grid a product over at most 32 contraction rows is a launch like
   // a factored pass, which gains only as the last axis (divide and inverse in
@@ -622,7 +620,18 @@ void choose_fast(qn_ctx c) {
     for (int a = 0; a < c->dim; ++a) c->fast[a] = c->fast[a] && c->n[a] > 64;
     c->strip = strips();
   }
-  for (int a = 0; a < c->dim; ++a) c->any_fast = c->any_fast || c->fast[a];
+  for (int a = 0; a < c->dim; ++a)
+    if (c->fast[a]) chain[a] = fast_work(c->fx[a].Q) + fast_work(c->fx[a].R);
+  if (!fast_pays(c->dim, c->n, c->p, chain, c->ncomp)) {
+    for (bool& f : c->fast) f = false;
+    c->strip = strips();
+  }
+  c->any_fast = false;
+  c->all_fast = true;
+  for (int a = 0; a < c->dim; ++a) {
+    c->any_fast = c->any_fast || c->fast[a];
+    c->all_fast = c->all_fast && c->fast[a];
+  }
   // An odd number of 128-byte lines per plane, so that the z passes' strides do
   // not return to the same memory channels (511^3 factored: plane stride 2 MiB
   // 0.82 ms for the z pass, 2 MiB - 4 KiB 0.70, odd 0.69; the y passes 0.47 and

@@ -385,18 +385,20 @@ inline float bf16_value(uint16_t h) {
   return f;
 }
 
+// Multiply-adds of an unrolled stage of the factored transforms (qn_fast.h):
+// even lengths halve, odd ones are contracted.
+inline double fast_work(int q) {
+  double w = 0.0;
+  for (; q > 2 && q % 2 == 0; q /= 2) w += q * q / 8.0 + 1.5 * q;
+  return w + (q > 2 ? q * q / 2.0 + q : q);
+}
+
 // Stage lengths of the factored transform of an axis of N intervals
 // (qn_fast.hip): 2N = Q R, both instantiated, with the fewest multiply-adds
 // per point; false when 2N has no such factorisation.
 inline bool fast_stages(int N, int* Qo, int* Ro) {
   static const int big[] = {20, 24, 28, 30, 32, 36, 40, 44, 48, 50, 52, 56, 60, 64};
   auto is_big = [](int q) { return std::find(std::begin(big), std::end(big), q) != std::end(big); };
-  // multiply-adds of an unrolled stage: even lengths halve, odd ones are contracted
-  auto work = [](int q) {
-    double w = 0.0;
-    for (; q > 2 && q % 2 == 0; q /= 2) w += q * q / 8.0 + 1.5 * q;
-    return w + (q > 2 ? q * q / 2.0 + q : q);
-  };
   double best = 1e300;
   for (int q = 4; q <= 64; ++q) {
     if ((2 * N) % q != 0) continue;
@@ -405,7 +407,7 @@ inline bool fast_stages(int N, int* Qo, int* Ro) {
     if (!small && !(is_big(q) && is_big(r))) continue;
     // two even lengths, then any to 32, then the longer ones: fewer registers
     // per thread, so more waves in flight
-    const double w = work(q) / q + work(r) / r + (!small ? 1e6 : ((q | r) & 1) ? 1e3 : 0.0);
+    const double w = fast_work(q) / q + fast_work(r) / r + (!small ? 1e6 : ((q | r) & 1) ? 1e3 : 0.0);
     if (w < best) {
       best = w;
       *Qo = q;
@@ -435,6 +437,53 @@ inline void fast_tables(int N, int Q, int R, bool neumann, double ih2, std::vect
   }
   if (!neumann) lam[0] = lam[N] = lam[N - 1];
   for (int k = N + 1; k < 2 * N; ++k) lam[k] = lam[2 * N - k];
+}
+
+// Whether the factored axes of a small grid stay factored (else every axis takes
+// its dense product).  A thread walks the two stages of its class alone, a chain
+// of work(Q) + work(R) multiply-adds; where a dense product is a single launch of
+// few tiles, that chain is the longer one for prime-like stages (4 x 23, 4 x 29,
+// 4 x 31, 5 x 26).  chain: its length per factored axis, 0 for dense ones.  The
+// lines lie where an iteration takes as long either way, dense and factored:
+//   2D, at most two tiles per axis, both factored: 51^2 (chains of 462 in all)
+//   29.2 and 29.6 us, 45^2 (596) 29.4 and 31.0, 61^2 (1044) 29.3 and 34.5; 86^2
+//   (940) 33.5 and 33.6, 92^2 (1064) 33.6 and 34.6.  Only y, which saves a launch:
+//   57 x 72 (460) 35.8 and 35.1, 61 x 58 (522) 33.6 and 34.3.  Only x, which saves
+//   none: 100 x 127 (172) 36.8 and 36.8, 100 x 123 (542) 37.2 and 39.1.
+//   3D, one tile per axis: 50^3 (546) 43.2 and 42.9, 37^3 (630) 42.8 and 43.3, 64^3
+//   (714) 43.4 and 45.4, 61^3 (1566) 43.4 and 51.2; 61 x 58 x 58 with z alone 47.9
+//   and 45.2; two fields, where the dense launches carry twice the padding: 51^3
+//   (693) 49.4 and 47.4, 64^3 50.7 and 52.8.  One axis of two tiles: 127 x 61 x 31
+//   (754) 52.6 and 48.4, 127 x 61 x 61 (1216) 54.5 and 56.5.
+inline bool fast_pays(int dim, const int* n, const int* p, const double* chain, int fields) {
+  double sum = 0.0, values = 1.0, padded = 1.0;
+  int count = 0, tiles = 0, most = 0, sides = 0;
+  for (int a = 0; a < dim; ++a) {
+    sum += chain[a];
+    count += chain[a] > 0.0;
+    values *= n[a];
+    padded *= p[a];
+    tiles += p[a] / 64;
+    most = std::max(most, p[a]);
+    if (chain[a] > 0.0) sides += p[a];
+  }
+  if (count == 0 || most > 128 || tiles > 4) return true;
+  if (dim == 2) {
+    if (count == 2) return sum <= 3.75 * sides;
+    return chain[1] > 0.0 && sum <= 7.3 * sides;
+  }
+  if (count == 1) return true;
+  if (fields > 1) sum *= values / padded;
+  return sum <= (tiles == 3 ? 600.0 : 1024.0);
+}
+
+// The same for the classes of a batch, n^2 points an instance and `values` in
+// all, which fill the chip: the factored passes' arithmetic counts, over n^2
+// points of the 64^2 that a dense tile pads to.  61^2 (chain of 522) x 1127
+// instances 196 us an iteration dense and 243 factored, x 70 57 and 56; 64^2 (238)
+// x 1024 177 and 194; 56^2 (220) x 1337 223 and 226, 62^2 (148) x 1091 193 and 193.
+inline bool fast_pays_batched(int n, double chain, double values) {
+  return n > 64 || values < 262144.0 || chain * n * n <= 180.0 * 4096.0;
 }
 
 // Whether the dense products of a solve take the strip form (qn_gemm_strip.h):
