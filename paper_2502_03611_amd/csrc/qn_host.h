@@ -491,25 +491,30 @@ inline bool fast_pays_batched(int n, double chain, double values) {
 // whose rate is 0.8-0.9 of the tiles' (255^3 0.73 against 0.67 ms at a ratio of
 // 1.0; 400^3 3.9 and 6.6 ms at 1.35, 200^3 0.40 and 0.52 ms at 1.9).  On smaller
 // grids a strip launch leaves the chip to too few waves and the ratio has to be
-// larger: from 2^20 to 2^22 values 1.5 in FP32 (127 x 127 x 66, 1.39: 93 against
-// 87 us an iteration), in 3D from 2^18 to 2^20 2.1 (60 x 70 x 64, 1.8: 60 and 54 us;
-// 66 x 31 x 200, 4.7: 72 and 126; 66^3, 5.1: 67 and 114), below that and in small
-// 2D never (52^3 35 against 29 us a solve, 200^2 46 and 36, 390^2 58 and 51).
+// larger.  3D from 2^18 to 2^20 values: 2.1 in FP64 (60 x 70 x 64, 1.8: 60 and 54
+// us an iteration; 66 x 31 x 200, 4.7: 72 and 126; 66^3, 5.1: 67 and 114); in FP32,
+// whose tiles are faster, only from 2^27 operations of the tiles on (60 x 35 x 66
+// of two fields, 0.87 of that, 2.7: 63 and 60; 164 x 31 x 63, 0.84, 2.3: 66 and
+// 57.5; 66 x 36 x 127, 1.1, 3.2: 64 and 66), at a ratio of 2.4 up to 2^28 (217 x 63 x
+// 31, 2.25: 70 and 65; 274 x 63 x 31, 2.26: 82 and 74; 96 x 66 x 31 of two fields,
+// 4.7: 66 and 84) and 2.1 beyond (66 x 109 x 63 of two fields, 2.1: 78 and 85).
+// From 2^20 to 2^22 values in FP32 1.75 where x pads to the tile's 128 (63 x 214 x
+// 72 of two fields, 1.64: 128 and 123; 127 x 198 x 89, 1.69: 131 and 126; 44 x 240 x
+// 153, 1.8: 115 and 124), else 1.5 (275 x 44 x 175, 1.67: 0.83 of the tiles' time).
+// Below 2^18 values, in 2D below 2^20, never (52^3 35 against 29 us a solve, 200^2 46
+// and 36, 390^2 58 and 51).
 // Row strides stay below 2^26 elements (32-bit lane offsets of three rows).  n,
 // p, dense: extents, padded extents and which axes have a dense product.
 inline bool use_strips(int dim, const int* n, const int* p, const bool* dense, int fields,
                        bool fp32) {
   double values = fields, tiles = 0.0, strips = 0.0;
   for (int a = 0; a < dim; ++a) values *= n[a];
-  double least = 1.25;
-  if (values < 1048576.0) least = 2.1;
-  else if (values < 4194304.0 && fp32) least = 1.5;
   if (values < (dim == 3 ? 262144.0 : 1048576.0) || (dim == 3 && (double)p[0] * p[1] >= 67108864.0)) return false;
   auto up16 = [](int v) { return (v + 15) / 16 * 16; };
   for (int a = 0; a < dim; ++a) {
     if (!dense[a]) continue;
     const int ne = (n[a] + 1) / 2;
-    double t = (double)p[a] * up16(ne), s = 2.0 * up16(ne) * (ne + 3);
+    double t = (double)fields * p[a] * up16(ne), s = 2.0 * fields * up16(ne) * (ne + 3);
     for (int b = 0; b < dim; ++b)
       if (b != a) {
         t *= p[b];
@@ -517,6 +522,13 @@ inline bool use_strips(int dim, const int* n, const int* p, const bool* dense, i
       }
     tiles += t;
     strips += s;
+  }
+  double least = 1.25;
+  if (values < 1048576.0) {
+    if (fp32 && tiles < 134217728.0) return false;
+    least = fp32 && tiles < 268435456.0 ? 2.4 : 2.1;
+  } else if (values < 4194304.0 && fp32) {
+    least = p[0] % 128 == 0 ? 1.75 : 1.5;
   }
   return tiles > least * strips;
 }

@@ -93,3 +93,17 @@ def test_factored_classes_of_batches():
     sizes = [61] * 300 + [57] * 20 + [63] * 700 + [127] * 40
     rows, = trace([{"sizes": sizes, "ncomp": [1] * len(sizes), "precision": "fp64"}])
     assert sorted(forms(rows)) == sorted("TTTT" + "FFF" + "FFF" + "FFF")
+
+
+@pytest.mark.parametrize("shape,problem,want", [
+    # too little tile work, or too little padding, for strips to gain in FP32: tiles
+    ((164, 31, 63), "cubic", "T"), ((60, 35, 66), "system", "T"), ((62, 108, 31), "system", "T"),
+    ((217, 63, 31), "cubic", "T"), ((274, 63, 31), "cubic", "T"), ((63, 214, 72), "system", "T"),
+    ((127, 198, 89), "cubic", "T"), ((31, 31, 31), "cubic", "T"),
+    ((66, 66, 66), "cubic", "S"), ((66, 36, 127), "cubic", "S"), ((96, 66, 31), "system", "S"),
+    ((66, 109, 63), "system", "S"), ((44, 240, 153), "cubic", "S"), ((275, 44, 175), "cubic", "S"),
+    ((150, 203, 176), "system", "S"),
+])
+def test_strips_of_small_fp32_grids(shape, problem, want):
+    rows, = trace([{"shape": shape, "problem": problem, "precision": "fp32", "do": ["solve"]}])
+    assert forms(rows) == 6 * want
