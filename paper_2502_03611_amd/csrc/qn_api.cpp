@@ -826,9 +826,12 @@ hipError_t solve_ws(qn_ctx c, const Coef& coef, double* dense, int epi_last,
   EpiArgs ep = epi_args(c, coef, dense);
   ep.skip = skip;
   ep.uscale = uscale;
-  if (!c->interior()) ep.src = rhs;
   FoldStep st[6];
   const int ns = solve_plan(c, ep, epi_last, st);
+  if (rhs && !c->interior()) {
+    st[0].in = rhs;
+    st[0].epi = EPI_FROM_DENSE;
+  }
   if (c->any_fast || c->interior()) {
     // the plan's launches in order, factored axes in place on the current
     // tensor, the others into the other tensor; the last forward axis, when
@@ -846,7 +849,7 @@ hipError_t solve_ws(qn_ctx c, const Coef& coef, double* dense, int epi_last,
         if (c->fast[axis]) return fast_pass(c, axis, (double*)cur, r, inverse, divide, epi_last, ep);
         if (c->interior()) return strip_pass(c, axis, cur, other, r, inverse, divide, epi_last, ep);
         FoldStep f = st[i];
-        f.in = cur;
+        f.in = r ? (const void*)r : cur;
         f.out = other;
         return run_step(c, f, step_tile(c, f, i));
       });
@@ -1365,7 +1368,7 @@ qn_status qn_fdm_solve(qn_ctx c, const double* d_R, double scale, double shift, 
                              c->xfold ? c->hp[0] : 0);
     });
   if (e == hipSuccess)
-    e = solve_ws(c, Coef{nullptr, 0, scale, shift}, d_X, EPI_STORE_DENSE, nullptr, nullptr,
+    e = solve_ws(c, Coef::values(scale, shift), d_X, EPI_STORE_DENSE, nullptr, nullptr,
                  direct ? d_R : nullptr);
   if (e != hipSuccess) return hip_fail(c, e, "fdm solve launch");
   return QN_OK;
@@ -1399,7 +1402,7 @@ qn_status qn_iterate(qn_ctx c, double* d_U, const double* d_F, double rtol, int3
   const int* done = &c->scal()->done;
   auto enqueue = [&](int k) {
     hipError_t e = hipSuccess;
-    if (k > 0) e = solve_ws(c, Coef{&c->scal()->scale, 0, 0.0, 0.0}, d_U, EPI_SUB_DENSE, done);
+    if (k > 0) e = solve_ws(c, Coef::memory(&c->scal()->scale, 0), d_U, EPI_SUB_DENSE, done);
     // the finalize kernel also writes the scalars into host slot k & 1
     if (e == hipSuccess)
       e = residual_into_ws(c, d_U, d_F, nullptr, rtol, k, max_iter, k > 0 ? done : nullptr,
@@ -1498,7 +1501,7 @@ qn_status qn_eigen_iterate(qn_ctx c, double* d_U, double rtol, int32_t max_iter,
   auto enqueue = [&](int k) {
     hipError_t e = hipSuccess;
     if (k > 0)
-      e = solve_ws(c, Coef{&c->scal()->scale, 0, 0.0, 0.0}, d_U, EPI_SUB_DENSE, done, &c->scal()->uscale);
+      e = solve_ws(c, Coef::memory(&c->scal()->scale, 0), d_U, EPI_SUB_DENSE, done, &c->scal()->uscale);
     if (e == hipSuccess)
       e = eigen_residual(c, d_U, nullptr, nullptr, rtol, k, max_iter, k > 0 ? done : nullptr,
                          c->dring + (k & 1));
@@ -1559,7 +1562,7 @@ qn_status qn_autotune(qn_ctx c) {
   if (e == hipSuccess) e = launch_zero(c->ws + c->off_W1, tbytes, c->stream);
   if (e == hipSuccess) e = launch_zero(c->ws + c->off_W2, tbytes, c->stream);
   FoldStep st[6];
-  const int ns = solve_plan(c, epi_args(c, Coef{nullptr, 0, 1.0, 1.0}, nullptr), EPI_STORE, st);
+  const int ns = solve_plan(c, epi_args(c, Coef::values(1.0, 1.0), nullptr), EPI_STORE, st);
   const unsigned pins = c->pins;
   c->pins = 0;  // step_tile gives the default rule below
   FoldTile best[6] = {};

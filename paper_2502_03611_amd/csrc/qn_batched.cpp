@@ -128,7 +128,7 @@ EpiArgs epi_for(qnb_ctx c, const Cls& k, double* dense_base) {
   ep.lamX = ep.lamM;
   ep.lamY = nullptr;
   BState* st = (BState*)(c->ws + k.off_state);
-  ep.coef = {&st[0].scale, (int)(sizeof(BState) / sizeof(double)), 0.0, 0.0};
+  ep.coef = Coef::memory(&st[0].scale, sizeof(BState) / sizeof(double));
   ep.dense = dense_base ? dense_base + k.off_field : nullptr;
   ep.px = ep.py = k.p;
   ep.pz = 1;
@@ -791,7 +791,7 @@ qn_status qnb_fdm_solve(qnb_ctx c, const double* d_R, double scale, double shift
     if (k.interior()) {
       EpiArgs ep = epi_for(c, k, d_X);
       ep.skip = nullptr;  // every instance
-      ep.coef = {nullptr, 0, scale, shift};
+      ep.coef = Coef::values(scale, shift);
       const double* r = d_R + k.off_field;
       e = k.fast ? class_fast_solve(c, k, r, false, ep, c->stream)
                  : class_strip_solve(c, k, r, false, ep, c->stream);
@@ -803,7 +803,7 @@ qn_status qnb_fdm_solve(qnb_ctx c, const double* d_R, double scale, double shift
     if (e != hipSuccess) break;
     EpiArgs ep = epi_for(c, k, d_X);
     ep.skip = nullptr;  // every instance
-    ep.coef = {nullptr, 0, scale, shift};
+    ep.coef = Coef::values(scale, shift);
     const int rows = k.ncomp * k.K * k.p;
     const int slabs = k.ncomp * k.K;
     const long long sl = (long long)k.p * k.p;

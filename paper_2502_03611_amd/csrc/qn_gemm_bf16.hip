@@ -296,6 +296,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_left_bf(GemmOperands S, const v
         for (int i = 0; i < BM; ++i) acc[i][j] = mfma_split<NP>(a[i], bj[j], acc[i][j]);
     }
   };
+  double scale = 1.0, beta = 0.0;  // their loads overlap the first chunk's
   const int nk = K / BTK;
   if constexpr (PS) {
     const __bf16* Bh = (const __bf16*)Bv + (long long)b * bstride;
@@ -318,6 +319,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_left_bf(GemmOperands S, const v
       }
     };
     dload(0, 0);
+    if (EPI == EPI_DIVIDE) ep.coef.get(inst, scale, beta);
     for (int kc = 0; kc < nk; ++kc) {
       const int buf = kc & 1;
       // this chunk's loads have landed and every wave is done reading the
@@ -389,6 +391,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_left_bf(GemmOperands S, const v
     };
 
     gload(0);
+    if (EPI == EPI_DIVIDE) ep.coef.get(inst, scale, beta);
     lstore(0);
     __syncthreads();
     for (int kc = 0; kc < nk; ++kc) {
@@ -414,8 +417,6 @@ __global__ __launch_bounds__(256, 2) void k_gemm_left_bf(GemmOperands S, const v
   if (EPI == EPI_DIVIDE) {
     // denominator scale (lam_m + lam_x + lam_y) + beta: the column part once
     // per column block, the row part once per row, one divide per entry
-    double scale, beta;
-    ep.coef.get(inst, scale, beta);
     double cn[BN];
 #pragma unroll
     for (int j = 0; j < BN; ++j) {

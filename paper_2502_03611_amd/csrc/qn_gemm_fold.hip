@@ -526,7 +526,7 @@ __global__ __launch_bounds__(256, 2) void k_fold_left_inv(const T* __restrict__ 
 
 // Forward along x (contraction over the columns of A's rows):
 // C[r][m] = sum_{k<bk} fold_blk(A[r])[k] F^T_blk[k][i], blk = m / bk, i = m % bk.
-// SRC: the rows come from the caller's FP64 interior array ep.src (any 8-byte
+// SRC: the rows come from A as the caller's FP64 interior array (any 8-byte
 // alignment, padding rows zero) instead of the padded tensor: a stand-alone
 // solve without the copy into it (63^2 FP32 29.1 -> 20.8 us, 255^2 28.2 -> 24.8;
 // where, see direct_rhs in qn_api.cpp).
@@ -567,14 +567,15 @@ __global__ __launch_bounds__(256, 2) void k_fold_right_fwd(const T* __restrict__
   // happens at the LDS store so the loads overlap the MFMA phase.
   V rlo[NA], rhi[NA], rb[NB];
   int kpre = 0;
-  const double* drow[SRC ? NA : 1];  // rows of ep.src, NULL: padding
+  const double* drow[SRC ? NA : 1];  // the array's rows, NULL: padding
   if constexpr (SRC) {
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
       const int r = r0 + min((tid + 256 * i) / (TK / VE), TM - 1);
       const int p = r / ep.py, y = r - p * ep.py, c = p / ep.pz, z = p - c * ep.pz;
       drow[i] = y < ep.ny && z < ep.nz
-                    ? ep.src + (((long long)c * ep.nz + z) * ep.ny + y) * ep.nx : nullptr;
+                    ? reinterpret_cast<const double*>(A) + (((long long)c * ep.nz + z) * ep.ny + y) * ep.nx
+                    : nullptr;
     }
   }
   auto gload = [&](int k0) {
@@ -941,13 +942,13 @@ hipError_t linv(const FoldOperands& f, const T* Y, T* C, const FoldAxis& ax, int
 
 template <typename T>
 hipError_t rfwd(const FoldOperands& f, const T* A, T* C, const FoldAxis& ax, int rows,
-                const EpiArgs& ep, const FoldTile& t, hipStream_t st) {
+                bool from_dense, const EpiArgs& ep, const FoldTile& t, hipStream_t st) {
   const T* FeT = (const T*)f.FeT;
   const T* FoT = (const T*)f.FoT;
 #define QN_RFWD(TM_, TN_, TK_)                                                                   \
   if (t.tm == TM_ && t.tn == TN_ && t.tk == TK_) {                                               \
     const unsigned g = (unsigned)((long long)(rows / TM_) * (2 * ax.bk / TN_));                  \
-    if (ep.src)                                                                                  \
+    if (from_dense)                                                                              \
       hipLaunchKernelGGL((k_fold_right_fwd<T, TM_, TN_, TK_, 1>), dim3(g), dim3(256), 0, st, A,  \
                          FeT, FoT, C, ax, rows, ep);                                             \
     else                                                                                         \
@@ -1005,7 +1006,7 @@ hipError_t fold_typed(int kind, const FoldOperands& f, const void* in, void* out
   const T* src = (const T*)in;
   T* dst = (T*)out;
   switch (kind) {
-    case FK_RFWD: return rfwd<T>(f, src, dst, ax, rows, ep, t, st);
+    case FK_RFWD: return rfwd<T>(f, src, dst, ax, rows, epi == EPI_FROM_DENSE, ep, t, st);
     case FK_LFWD:
       if (t.paired) return lfwd2<T>(f, src, dst, ax, ncols, batch, bstride, epi, ep, t, st);
       return lfwd<T>(f, src, dst, ax, ncols, batch, bstride, epi, ep, t, st);

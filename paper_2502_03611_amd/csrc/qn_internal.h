@@ -61,20 +61,41 @@ enum Epi : int {
   EPI_DIVIDE = 1,       // padded store of acc / (scale * (lamM + lamX + lamY) + beta)
   EPI_SUB_DENSE = 2,    // dense[..] -= acc (interior only)
   EPI_STORE_DENSE = 3,  // dense[..] = acc (interior only)
+  EPI_FROM_DENSE = 4,   // folded forward x product: padded store; the input is the caller's FP64
+                        // array (ncomp, nz, ny, nx) instead of the padded tensor
 };
 
 // {scale, beta} of a solve: at + instance * stride in device memory (the
-// scalars of a running iteration), or the values themselves when at is NULL
-// (stand-alone solves: a launch that stores them first is 1.4 us and a launch
-// gap, 18.3 against 14.1 us for a 63^2 FP64 solve).
+// scalars of a running iteration), or the values themselves (stand-alone solves:
+// a launch that stores them first is 1.4 us and a launch gap, 18.3 against
+// 14.1 us for a 63^2 FP64 solve).
 struct Coef {
-  const double* at;
-  int stride;
-  double scale, beta;
+  union {
+    const double* at;
+    double scale;
+  };
+  union {
+    long long stride;
+    double beta;
+  };
+  int stored;  // at and stride hold
+  static Coef memory(const double* at, long long stride) {
+    Coef c{};
+    c.at = at;
+    c.stride = stride;
+    c.stored = 1;
+    return c;
+  }
+  static Coef values(double scale, double beta) {
+    Coef c{};
+    c.scale = scale;
+    c.beta = beta;
+    return c;
+  }
   __device__ void get(long long inst, double& s, double& b) const {
     s = scale;
     b = beta;
-    if (at) {
+    if (stored) {
       const double* p = at + inst * stride;
       s = p[0];
       b = p[1];
@@ -82,21 +103,23 @@ struct Coef {
   }
 };
 
+// Copied into every mode-product launch, hence kept small: where the host bounds
+// the launches, an iteration of six of them on 58 x 31 points takes 34.2 us with
+// 120 bytes, 35.2 with 128 and 35.5 with 152.
 struct EpiArgs {
   const double* lamM;   // eigenvalues along the product's own axis (row index m)
   const double* lamX;   // eigenvalues along x (column index n % px)
   const double* lamY;   // eigenvalues along y (column index n / px), NULL in 2D
   Coef coef;
   double* dense;        // caller array (ncomp, nz, ny, nx) for the dense epilogues
-  const double* src;    // folded forward x product: caller array (ncomp, nz, ny, nx) read instead
-                        // of the padded tensor, or NULL
-  int px, py, pz;       // padded extents
-  int nx, ny, nz;       // interior extents
+  unsigned short px, py, pz;  // padded extents
+  unsigned short nx, ny, nz;  // interior extents
   // Batched solver: slabs / row blocks belong to instance (index % inst_mod);
   // an instance whose skip flag is set is left untouched.  A single problem uses
   // skip = NULL, inst_mod = 1, coef.stride = 0.
   const int* skip;
   int inst_mod;
+  int comp_div;  // of cscale
   // EPI_SUB_DENSE of the folded kernels: the old values are multiplied by
   // *uscale before the subtraction (the eigenproblem's normalisation), NULL: 1.
   const double* uscale;
@@ -104,7 +127,6 @@ struct EpiArgs {
   // = slab index / comp_div), NULL: 1 (the Gray-Scott system's diffusion
   // coefficients: (D_c A + beta I)^-1 per component).
   const double* cscale;
-  int comp_div;
   // EPI_SUB_DENSE of the folded kernels: dense = old - step * acc (the damped
   // step of the Gray-Scott system; 1 otherwise).
   double step;
@@ -112,6 +134,8 @@ struct EpiArgs {
   // b % pz: the z mode of a y product batched over z), NULL: none.
   const double* lamB;
 };
+
+static_assert(sizeof(EpiArgs) <= 120, "every launch copies it");
 
 // Dense split-bf16 mode products (qn_gemm_bf16.hip), FP32 tensors.  All
 // launchers take an explicit stream and return the launch status.

@@ -53,6 +53,7 @@ extern "C" {
 const char* trace_text() { return text.c_str(); }
 void trace_clear() { text.clear(); }
 void trace_device(int d) { device = d; }
+int trace_argument_bytes() { return sizeof(qn::EpiArgs); }
 
 void** __hipRegisterFatBinary(const void*) {
   static void* module;

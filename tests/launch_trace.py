@@ -55,6 +55,11 @@ def trace(calls, lib=None):
     return res
 
 
+def argument_bytes():
+    """Bytes of the struct that every mode-product launch copies."""
+    return ctypes.CDLL(_stand_in()).trace_argument_bytes()
+
+
 FORMS = {"k_fast": "F", "k_strip": "S", "k_fold": "T", "k_gemm": "D"}
 
 

@@ -5,7 +5,7 @@ import os
 
 import pytest
 
-from launch_trace import CLANG, forms, trace
+from launch_trace import CLANG, argument_bytes, forms, trace
 
 pytestmark = pytest.mark.skipif(not os.path.exists(CLANG), reason="needs the ROCm host compiler")
 
@@ -107,3 +107,8 @@ def test_factored_classes_of_batches():
 def test_strips_of_small_fp32_grids(shape, problem, want):
     rows, = trace([{"shape": shape, "problem": problem, "precision": "fp32", "do": ["solve"]}])
     assert forms(rows) == 6 * want
+
+
+def test_launch_arguments_stay_small():
+    """Launches bound by the host slow down with the bytes they copy."""
+    assert argument_bytes() <= 120
