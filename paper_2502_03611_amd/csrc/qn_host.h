@@ -500,7 +500,10 @@ inline bool fast_pays_batched(int n, double chain, double values) {
 // 4.7: 66 and 84) and 2.1 beyond (66 x 109 x 63 of two fields, 2.1: 78 and 85).
 // From 2^20 to 2^22 values in FP32 1.75 where x pads to the tile's 128 (63 x 214 x
 // 72 of two fields, 1.64: 128 and 123; 127 x 198 x 89, 1.69: 131 and 126; 44 x 240 x
-// 153, 1.8: 115 and 124), else 1.5 (275 x 44 x 175, 1.67: 0.83 of the tiles' time).
+// 153, 1.8: 115 and 124), else 1.5 (275 x 44 x 175, 1.67: 0.83 of the tiles' time);
+// from there to 2^24 1.4 and 1.27 (254 x 254 x 66, 1.38: 239 and 214; 254 x 130 x 127
+// of two fields, 1.44: 271 and 288; 127 x 313 x 130, 1.26: 242 and 234; 280 x 63 x 277,
+// 1.27: 210 and 226).
 // Below 2^18 values, in 2D below 2^20, never (52^3 35 against 29 us a solve, 200^2 46
 // and 36, 390^2 58 and 51).
 // Row strides stay below 2^26 elements (32-bit lane offsets of three rows).  n,
@@ -527,8 +530,9 @@ inline bool use_strips(int dim, const int* n, const int* p, const bool* dense, i
   if (values < 1048576.0) {
     if (fp32 && tiles < 134217728.0) return false;
     least = fp32 && tiles < 268435456.0 ? 2.4 : 2.1;
-  } else if (values < 4194304.0 && fp32) {
-    least = p[0] % 128 == 0 ? 1.75 : 1.5;
+  } else if (values < 16777216.0 && fp32) {
+    const bool full = p[0] % 128 == 0;
+    least = values < 4194304.0 ? (full ? 1.75 : 1.5) : (full ? 1.4 : 1.27);
   }
   return tiles > least * strips;
 }

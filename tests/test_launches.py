@@ -100,9 +100,12 @@ def test_factored_classes_of_batches():
     ((164, 31, 63), "cubic", "T"), ((60, 35, 66), "system", "T"), ((62, 108, 31), "system", "T"),
     ((217, 63, 31), "cubic", "T"), ((274, 63, 31), "cubic", "T"), ((63, 214, 72), "system", "T"),
     ((127, 198, 89), "cubic", "T"), ((31, 31, 31), "cubic", "T"),
+    ((254, 254, 66), "cubic", "T"), ((127, 254, 66), "system", "T"), ((254, 200, 254), "cubic", "T"),
+    ((196, 63, 254), "system", "T"), ((127, 313, 130), "cubic", "T"),
     ((66, 66, 66), "cubic", "S"), ((66, 36, 127), "cubic", "S"), ((96, 66, 31), "system", "S"),
     ((66, 109, 63), "system", "S"), ((44, 240, 153), "cubic", "S"), ((275, 44, 175), "cubic", "S"),
-    ((150, 203, 176), "system", "S"),
+    ((150, 203, 176), "system", "S"), ((254, 130, 127), "system", "S"), ((280, 63, 277), "cubic", "S"),
+    ((270, 270, 510), "cubic", "S"),
 ])
 def test_strips_of_small_fp32_grids(shape, problem, want):
     rows, = trace([{"shape": shape, "problem": problem, "precision": "fp32", "do": ["solve"]}])
