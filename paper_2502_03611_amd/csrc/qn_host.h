@@ -498,12 +498,14 @@ inline bool fast_pays_batched(int n, double chain, double values) {
 // 57.5; 66 x 36 x 127, 1.1, 3.2: 64 and 66), at a ratio of 2.4 up to 2^28 (217 x 63 x
 // 31, 2.25: 70 and 65; 274 x 63 x 31, 2.26: 82 and 74; 96 x 66 x 31 of two fields,
 // 4.7: 66 and 84) and 2.1 beyond (66 x 109 x 63 of two fields, 2.1: 78 and 85).
-// From 2^20 to 2^22 values in FP32 1.75 where x pads to the tile's 128 (63 x 214 x
-// 72 of two fields, 1.64: 128 and 123; 127 x 198 x 89, 1.69: 131 and 126; 44 x 240 x
-// 153, 1.8: 115 and 124), else 1.5 (275 x 44 x 175, 1.67: 0.83 of the tiles' time);
-// from there to 2^24 1.4 and 1.27 (254 x 254 x 66, 1.38: 239 and 214; 254 x 130 x 127
-// of two fields, 1.44: 271 and 288; 127 x 313 x 130, 1.26: 242 and 234; 280 x 63 x 277,
-// 1.27: 210 and 226).
+// From 2^20 to 2^22 values in FP32 1.75 in 3D where x pads to the tile's 128 (63 x
+// 214 x 72 of two fields, 1.64: 128 and 123; 127 x 198 x 89, 1.69: 131 and 126; 66 x
+// 127 x 127, 1.84: 88 and 92), else 1.5 (275 x 44 x 175, 1.67: 0.83 of the tiles'
+// time; batches of 95^2 x 132, 1.68: 79 and 87, 194^2 x 31, 1.57: 89 and 93, x 92: 147
+// and 143 but 100 and 105 a solve).  From there to 2^24 1.4 and 1.27 (254 x 254 x 66,
+// 1.38: 239 and 214; 254 x 130 x 127 of two fields, 1.44: 271 and 288; 127 x 313 x 130,
+// 1.26: 242 and 234; 280 x 63 x 277, 1.27: 210 and 226), 1.33 in 2D (batches of 222^2 x
+// 121, 1.29: 185 and 170, 210^2 x 136, 1.4: 194 and 210).
 // Below 2^18 values, in 2D below 2^20, never (52^3 35 against 29 us a solve, 200^2 46
 // and 36, 390^2 58 and 51).
 // Row strides stay below 2^26 elements (32-bit lane offsets of three rows).  n,
@@ -531,8 +533,8 @@ inline bool use_strips(int dim, const int* n, const int* p, const bool* dense, i
     if (fp32 && tiles < 134217728.0) return false;
     least = fp32 && tiles < 268435456.0 ? 2.4 : 2.1;
   } else if (values < 16777216.0 && fp32) {
-    const bool full = p[0] % 128 == 0;
-    least = values < 4194304.0 ? (full ? 1.75 : 1.5) : (full ? 1.4 : 1.27);
+    const bool full = dim == 3 && p[0] % 128 == 0;
+    least = values < 4194304.0 ? (full ? 1.75 : 1.5) : full ? 1.4 : dim == 3 ? 1.27 : 1.33;
   }
   return tiles > least * strips;
 }

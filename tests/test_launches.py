@@ -112,6 +112,12 @@ def test_strips_of_small_fp32_grids(shape, problem, want):
     assert forms(rows) == 6 * want
 
 
+def test_strips_of_fp32_batches():
+    for n, count, want in ((95, 132, "S"), (72, 231, "S"), (140, 61, "S"), (210, 136, "S"), (222, 121, "T")):
+        rows, = trace([{"sizes": [n] * count, "ncomp": [1] * count, "precision": "fp32"}])
+        assert forms(rows) == 4 * want, n
+
+
 def test_launch_arguments_stay_small():
     """Launches bound by the host slow down with the bytes they copy."""
     assert argument_bytes() <= 120
