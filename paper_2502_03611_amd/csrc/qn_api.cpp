@@ -1368,7 +1368,7 @@ qn_status qn_fdm_solve(qn_ctx c, const double* d_R, double scale, double shift, 
                              c->xfold ? c->hp[0] : 0);
     });
   if (e == hipSuccess)
-    e = solve_ws(c, Coef::values(scale, shift), d_X, EPI_STORE_DENSE, nullptr, nullptr,
+    e = solve_ws(c, Coef{nullptr, scale, shift}, d_X, EPI_STORE_DENSE, nullptr, nullptr,
                  direct ? d_R : nullptr);
   if (e != hipSuccess) return hip_fail(c, e, "fdm solve launch");
   return QN_OK;
@@ -1402,7 +1402,7 @@ qn_status qn_iterate(qn_ctx c, double* d_U, const double* d_F, double rtol, int3
   const int* done = &c->scal()->done;
   auto enqueue = [&](int k) {
     hipError_t e = hipSuccess;
-    if (k > 0) e = solve_ws(c, Coef::memory(&c->scal()->scale, 0), d_U, EPI_SUB_DENSE, done);
+    if (k > 0) e = solve_ws(c, Coef{&c->scal()->scale, 0.0, 0.0}, d_U, EPI_SUB_DENSE, done);
     // the finalize kernel also writes the scalars into host slot k & 1
     if (e == hipSuccess)
       e = residual_into_ws(c, d_U, d_F, nullptr, rtol, k, max_iter, k > 0 ? done : nullptr,
@@ -1501,7 +1501,7 @@ qn_status qn_eigen_iterate(qn_ctx c, double* d_U, double rtol, int32_t max_iter,
   auto enqueue = [&](int k) {
     hipError_t e = hipSuccess;
     if (k > 0)
-      e = solve_ws(c, Coef::memory(&c->scal()->scale, 0), d_U, EPI_SUB_DENSE, done, &c->scal()->uscale);
+      e = solve_ws(c, Coef{&c->scal()->scale, 0.0, 0.0}, d_U, EPI_SUB_DENSE, done, &c->scal()->uscale);
     if (e == hipSuccess)
       e = eigen_residual(c, d_U, nullptr, nullptr, rtol, k, max_iter, k > 0 ? done : nullptr,
                          c->dring + (k & 1));
@@ -1562,7 +1562,7 @@ qn_status qn_autotune(qn_ctx c) {
   if (e == hipSuccess) e = launch_zero(c->ws + c->off_W1, tbytes, c->stream);
   if (e == hipSuccess) e = launch_zero(c->ws + c->off_W2, tbytes, c->stream);
   FoldStep st[6];
-  const int ns = solve_plan(c, epi_args(c, Coef::values(1.0, 1.0), nullptr), EPI_STORE, st);
+  const int ns = solve_plan(c, epi_args(c, Coef{nullptr, 1.0, 1.0}, nullptr), EPI_STORE, st);
   const unsigned pins = c->pins;
   c->pins = 0;  // step_tile gives the default rule below
   FoldTile best[6] = {};

@@ -128,7 +128,8 @@ EpiArgs epi_for(qnb_ctx c, const Cls& k, double* dense_base) {
   ep.lamX = ep.lamM;
   ep.lamY = nullptr;
   BState* st = (BState*)(c->ws + k.off_state);
-  ep.coef = Coef::memory(&st[0].scale, sizeof(BState) / sizeof(double));
+  ep.coef = {&st[0].scale, 0.0, 0.0};
+  ep.coef_stride = (int)(sizeof(BState) / sizeof(double));
   ep.dense = dense_base ? dense_base + k.off_field : nullptr;
   ep.px = ep.py = k.p;
   ep.pz = 1;
@@ -174,6 +175,7 @@ hipError_t class_fast_solve(qnb_ctx c, const Cls& k, const double* rhs, bool sub
   b.es = k.p;
   b.oy = 1;
   b.coef = ep.coef;
+  b.coef_stride = ep.coef_stride;
   b.cscale = ep.cscale;
   b.comp_div = ep.cscale ? ep.comp_div : 1;
   b.lamX = ep.lamX;
@@ -238,6 +240,7 @@ hipError_t class_strip_solve(qnb_ctx c, const Cls& k, const double* rhs, bool su
   a.Fo = f.FoT;
   a.lamM = a.lamX = ep.lamX;
   a.coef = ep.coef;
+  a.coef_stride = ep.coef_stride;
   a.cscale = ep.cscale;
   if (ep.cscale) a.comp_div = ep.comp_div;
   e = launch(false, STRIP_DIV, a);
@@ -791,7 +794,7 @@ qn_status qnb_fdm_solve(qnb_ctx c, const double* d_R, double scale, double shift
     if (k.interior()) {
       EpiArgs ep = epi_for(c, k, d_X);
       ep.skip = nullptr;  // every instance
-      ep.coef = Coef::values(scale, shift);
+      ep.coef = {nullptr, scale, shift};
       const double* r = d_R + k.off_field;
       e = k.fast ? class_fast_solve(c, k, r, false, ep, c->stream)
                  : class_strip_solve(c, k, r, false, ep, c->stream);
@@ -803,7 +806,7 @@ qn_status qnb_fdm_solve(qnb_ctx c, const double* d_R, double scale, double shift
     if (e != hipSuccess) break;
     EpiArgs ep = epi_for(c, k, d_X);
     ep.skip = nullptr;  // every instance
-    ep.coef = Coef::values(scale, shift);
+    ep.coef = {nullptr, scale, shift};
     const int rows = k.ncomp * k.K * k.p;
     const int slabs = k.ncomp * k.K;
     const long long sl = (long long)k.p * k.p;

@@ -139,7 +139,7 @@ __global__ __launch_bounds__(FAST_THREADS, FAM == EVEN ? 4 : 2) void k_fast_line
 #undef X
   } else {
     double scale, beta;
-    a.coef.get(inst, scale, beta);
+    a.coef.get((long long)inst * a.coef_stride, scale, beta);
     if (a.cscale) scale *= a.cscale[plane / a.comp_div];
     const double den0 = scale * (a.lamX[x0 + xl] + (a.lamY ? a.lamY[opos] : 0.0)) + beta;
 #define X(L)                                                                                       \

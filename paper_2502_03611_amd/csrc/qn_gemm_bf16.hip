@@ -319,7 +319,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_left_bf(GemmOperands S, const v
       }
     };
     dload(0, 0);
-    if (EPI == EPI_DIVIDE) ep.coef.get(inst, scale, beta);
+    if (EPI == EPI_DIVIDE) ep.coef.get((long long)inst * ep.coef_stride, scale, beta);
     for (int kc = 0; kc < nk; ++kc) {
       const int buf = kc & 1;
       // this chunk's loads have landed and every wave is done reading the
@@ -391,7 +391,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_left_bf(GemmOperands S, const v
     };
 
     gload(0);
-    if (EPI == EPI_DIVIDE) ep.coef.get(inst, scale, beta);
+    if (EPI == EPI_DIVIDE) ep.coef.get((long long)inst * ep.coef_stride, scale, beta);
     lstore(0);
     __syncthreads();
     for (int kc = 0; kc < nk; ++kc) {

@@ -160,7 +160,7 @@ __global__ __launch_bounds__(256, 2) void k_fold_left_fwd(const T* __restrict__ 
   gload(0);
   double scale = 1.0, beta = 0.0;  // their loads overlap the first stage's
   if (EPI == EPI_DIVIDE) {
-    ep.coef.get(inst, scale, beta);
+    ep.coef.get((long long)inst * ep.coef_stride, scale, beta);
     if (ep.cscale) scale *= ep.cscale[b / ep.comp_div];
   }
   lstore(0);
@@ -319,7 +319,7 @@ __global__ __launch_bounds__(256, 2) void k_fold_left_fwd2(const T* __restrict__
   gload(0);
   double scale = 1.0, beta = 0.0;  // their loads overlap the first stage's
   if (EPI == EPI_DIVIDE) {
-    ep.coef.get(inst, scale, beta);
+    ep.coef.get((long long)inst * ep.coef_stride, scale, beta);
     if (ep.cscale) scale *= ep.cscale[b / ep.comp_div];
   }
   lstore(0);

@@ -274,7 +274,7 @@ __global__ __launch_bounds__(256, MB * NCB <= 6 && MB <= 4 ? 3 : 2) void k_strip
 
   double scale = 1.0, beta = 0.0, cn[NCB];
   if constexpr (DIV) {
-    a.coef.get(inst, scale, beta);
+    a.coef.get((long long)inst * a.coef_stride, scale, beta);
     if (a.cscale) scale *= a.cscale[plane / a.comp_div];
 #pragma unroll
     for (int j = 0; j < NCB; ++j) cn[j] = a.lamX[col[j]] + (a.lamY ? a.lamY[opos] : 0.0);

@@ -65,38 +65,19 @@ enum Epi : int {
                         // array (ncomp, nz, ny, nx) instead of the padded tensor
 };
 
-// {scale, beta} of a solve: at + instance * stride in device memory (the
-// scalars of a running iteration), or the values themselves (stand-alone solves:
-// a launch that stores them first is 1.4 us and a launch gap, 18.3 against
-// 14.1 us for a 63^2 FP64 solve).
+// {scale, beta} of a solve: in device memory at `at` plus an instance's offset
+// (the scalars of a running iteration), or the values themselves when at is NULL
+// (stand-alone solves: a launch that stores them first is 1.4 us and a launch
+// gap, 18.3 against 14.1 us for a 63^2 FP64 solve).  (A union of the two forms
+// makes the kernels that select between them spill to scratch memory.)
 struct Coef {
-  union {
-    const double* at;
-    double scale;
-  };
-  union {
-    long long stride;
-    double beta;
-  };
-  int stored;  // at and stride hold
-  static Coef memory(const double* at, long long stride) {
-    Coef c{};
-    c.at = at;
-    c.stride = stride;
-    c.stored = 1;
-    return c;
-  }
-  static Coef values(double scale, double beta) {
-    Coef c{};
-    c.scale = scale;
-    c.beta = beta;
-    return c;
-  }
-  __device__ void get(long long inst, double& s, double& b) const {
+  const double* at;
+  double scale, beta;
+  __device__ void get(long long offset, double& s, double& b) const {
     s = scale;
     b = beta;
-    if (stored) {
-      const double* p = at + inst * stride;
+    if (at) {
+      const double* p = at + offset;
       s = p[0];
       b = p[1];
     }
@@ -114,9 +95,10 @@ struct EpiArgs {
   double* dense;        // caller array (ncomp, nz, ny, nx) for the dense epilogues
   unsigned short px, py, pz;  // padded extents
   unsigned short nx, ny, nz;  // interior extents
+  int coef_stride;            // doubles between the coefficients of two instances
   // Batched solver: slabs / row blocks belong to instance (index % inst_mod);
   // an instance whose skip flag is set is left untouched.  A single problem uses
-  // skip = NULL, inst_mod = 1, coef.stride = 0.
+  // skip = NULL, inst_mod = 1, coef_stride = 0.
   const int* skip;
   int inst_mod;
   int comp_div;  // of cscale
@@ -249,7 +231,7 @@ struct StripArgs {
   const double* lamY;
   Coef coef;
   const double* cscale;
-  int comp_div;
+  int comp_div, coef_stride;
   const int* skip;
   int inst_mod;
   int ge, groups, strips, mtiles;  // filled by the launchers
@@ -291,7 +273,7 @@ struct FastArgs {
   double step;
   Coef coef;
   const double* cscale;
-  int comp_div;
+  int comp_div, coef_stride;
   const double* lamX;
   const double* lamY;
   const int* skip;

@@ -2,10 +2,14 @@
 takes and whether its launch is one that the device accepts."""
 
 import os
+import re
+import shutil
+import subprocess
 
 import pytest
 
 from launch_trace import CLANG, argument_bytes, forms, trace
+from paper_2502_03611_amd import LIB_PATH
 
 pytestmark = pytest.mark.skipif(not os.path.exists(CLANG), reason="needs the ROCm host compiler")
 
@@ -121,3 +125,20 @@ def test_strips_of_fp32_batches():
 def test_launch_arguments_stay_small():
     """Launches bound by the host slow down with the bytes they copy."""
     assert argument_bytes() <= 120
+
+
+def test_mode_products_use_no_scratch_memory(tmp_path):
+    """The library's own code objects: no mode product spills (a selection between
+    two forms of the coefficients has made the strips do so)."""
+    so = shutil.copy(LIB_PATH, tmp_path)
+    tool = os.path.join(os.path.dirname(CLANG), "llvm-objdump")
+    subprocess.run([tool, "--offloading", so], check=True, capture_output=True, cwd=tmp_path)
+    seen = 0
+    for f in tmp_path.glob("*gfx950"):
+        notes = subprocess.run([os.path.join(os.path.dirname(CLANG), "llvm-readelf"), "--notes", str(f)],
+                               check=True, capture_output=True, text=True).stdout
+        for name, size in re.findall(r"\.name:\s+(_Z\S+)\n(?:.*\n)*?\s+\.private_segment_fixed_size:\s+(\d+)", notes):
+            if re.search(r"k_(strip|fold|fast|gemm)_", name):
+                seen += 1
+                assert size == "0", name
+    assert seen > 200
