@@ -88,7 +88,7 @@ __device__ __forceinline__ void stage2_lds(const Pair<T>* lds, int bs, T (&out)[
 // One transform (DIV = 0) or forward transform, divide and inverse transform
 // (DIV = 1) of the lines of C consecutive x positions, in place.
 template <int FAM, int DIV>
-__global__ __launch_bounds__(FAST_THREADS, FAM == EVEN ? 4 : 2) void k_fast_lines(FastArgs a) {
+__global__ __launch_bounds__(FAST_THREADS, FAM == EVEN ? 4 : 2) void k_fast_lines(LineArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   Pair<T>* lds = reinterpret_cast<Pair<T>*>(smem);
   const int C = 1 << a.lc;
@@ -96,7 +96,7 @@ __global__ __launch_bounds__(FAST_THREADS, FAM == EVEN ? 4 : 2) void k_fast_line
   const int plane = o / a.oy;
   const int inst = plane % a.inst_mod;
   if (a.skip && a.skip[inst]) return;
-  const int N = a.ax.N, Q = a.ax.Q, R = a.ax.R, off = a.ax.off;
+  const int N = a.N, Q = a.Q, R = a.R, off = a.off;
   const T sg = off ? T(-1) : T(1);
   const int t = threadIdx.x, line = t & (C - 1), c = t >> a.lc;
   const bool lower = xt < a.xsplit;  // even and odd modes of a dense x axis, or all of a natural one
@@ -106,7 +106,7 @@ __global__ __launch_bounds__(FAST_THREADS, FAM == EVEN ? 4 : 2) void k_fast_line
   const int oi = o % a.om, opos = oi < a.oe ? oi : a.obk + oi - a.oe;
   T* base = a.out + (long long)(o / a.om) * a.s1 + (long long)opos * a.s0 + x0;
   const unsigned eb = (unsigned)a.es * 8, lb = line * 8, xb = xl * 8;  // bytes: axis stride, line
-  const Pair<T>* tw = (const Pair<T>*)a.ax.tw;
+  const Pair<T>* tw = (const Pair<T>*)a.tw;
   const int rh = R >> 1, qh = Q >> 1;
   const bool in1 = c <= rh, in2 = c <= qh;
 
@@ -149,7 +149,7 @@ __global__ __launch_bounds__(FAST_THREADS, FAM == EVEN ? 4 : 2) void k_fast_line
       stage2_lds<L, T>(lds + (((rh + 1) * c) << a.lc) + line, C, v);                                   \
       const unsigned cb = c * 8; /* lam[k], k = 0 .. 2N - 1: continued evenly */                   \
       _Pragma("unroll") for (int k2 = 0; k2 < L; ++k2) {                                           \
-        v[k2] = quotient(v[k2], __builtin_fma(scale, ld(a.ax.lam + Q * k2, cb), den0));            \
+        v[k2] = quotient(v[k2], __builtin_fma(scale, ld(a.lam + Q * k2, cb), den0));            \
       }                                                                                            \
       if (off) { /* the modes k = 0 and k = N do not exist */                                      \
         if (c == 0) {                                                                              \
@@ -189,10 +189,10 @@ __global__ __launch_bounds__(FAST_THREADS, FAM == EVEN ? 4 : 2) void k_fast_line
 // per workgroup.  EPI 0: into a.out (padded layout); EPI 1: into the caller's
 // array a.dense (interior layout), stored or subtracted.
 template <int FAM, int EPI>
-__global__ __launch_bounds__(FAST_THREADS, FAM == EVEN && EPI == 0 ? 4 : 2) void k_fast_rows(FastArgs a) {
+__global__ __launch_bounds__(FAST_THREADS, FAM == EVEN && EPI == 0 ? 4 : 2) void k_fast_rows(RowArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   Pair<T>* lds = reinterpret_cast<Pair<T>*>(smem);
-  const int N = a.ax.N, Q = a.ax.Q, R = a.ax.R, off = a.ax.off;
+  const int N = a.N, Q = a.Q, R = a.R, off = a.off;
   const T sg = off ? T(-1) : T(1);
   const int rh = R >> 1, qh = Q >> 1;
   const int t = threadIdx.x;
@@ -204,9 +204,8 @@ __global__ __launch_bounds__(FAST_THREADS, FAM == EVEN && EPI == 0 ? 4 : 2) void
     for (int pl = pl0; pl <= pl1; ++pl) any = any || !a.skip[pl % a.inst_mod];
     if (!any) return;
   }
-  const Pair<T>* tw = (const Pair<T>*)a.ax.tw;
-  // offset of row r from the tensor's start, in the padded (in, out) or
-  // interior (dense) layout
+  const Pair<T>* tw = (const Pair<T>*)a.tw;
+  // offset of row r from the array's start
   auto row_off = [&](int r, long long s1, long long s0, long long ys) {
     const int pl = r / a.oy;
     return (long long)(pl / a.om) * s1 + (long long)(pl % a.om) * s0 + (long long)(r - pl * a.oy) * ys;
@@ -235,12 +234,9 @@ __global__ __launch_bounds__(FAST_THREADS, FAM == EVEN && EPI == 0 ? 4 : 2) void
   __syncthreads();
   if (!in2) return;
   if (a.skip && a.skip[(row2 / a.oy) % a.inst_mod]) return;
-  T* o = EPI == 0 ? a.out : a.dense;
-  const long long os1 = EPI == 0 ? a.s1 : a.om * a.ds0, os0 = EPI == 0 ? a.s0 : a.ds0,
-                  oys = EPI == 0 ? a.ys : a.dys;
-  const long long o0 = row_off(r0, os1, os0, oys);
-  o += o0;
-  const unsigned ro = 8 * (unsigned)(row_off(row2, os1, os0, oys) - o0);
+  const long long o0 = row_off(r0, a.s1, a.s0, a.ys);
+  T* o = a.out + o0;
+  const unsigned ro = 8 * (unsigned)(row_off(row2, a.s1, a.s0, a.ys) - o0);
   const unsigned vo = ro + 8 * c2, mo = ro + 8 * (qh - c2);
   const bool sub = EPI == 1 && a.sub != 0;  // a stored solve reads no old values
   const double us = sub && a.uscale ? *a.uscale : 1.0, sp = a.step;
@@ -289,10 +285,36 @@ constexpr size_t kLdsTarget = 80 * 1024;  // two workgroups per CU
 int round64(int v) { return (v + 63) & ~63; }
 
 template <int FAM, int DIV>
-hipError_t lines_launch(FastArgs a, int nouter, hipStream_t st) {
+hipError_t lines_launch(const FastArgs& f, int nouter, hipStream_t st) {
   constexpr auto kern = k_fast_lines<FAM, DIV>;
+  LineArgs a{};
+  a.tw = f.ax.tw;
+  a.lam = f.ax.lam;
+  a.out = f.out;
+  a.s1 = f.s1;
+  a.s0 = f.s0;
+  a.es = f.es;
+  a.lamX = f.lamX;
+  a.lamY = f.lamY;
+  a.coef = f.coef;
+  a.cscale = f.cscale;
+  a.skip = f.skip;
+  a.ce = f.ce;
+  a.cbk = f.cbk;
+  a.co = f.co;
+  a.oy = f.oy;
+  a.om = f.om;
+  a.oe = f.oe;
+  a.obk = f.obk;
+  a.inst_mod = f.inst_mod;
+  a.comp_div = f.comp_div;
+  a.coef_stride = f.coef_stride;
+  a.N = (short)f.ax.N;
+  a.Q = (short)f.ax.Q;
+  a.R = (short)f.ax.R;
+  a.off = (short)f.ax.off;
   int lc = FAM == BIG ? 3 : 4;
-  const int qh = a.ax.Q / 2 + 1, rh = a.ax.R / 2 + 1;
+  const int qh = a.Q / 2 + 1, rh = a.R / 2 + 1;
   auto bytes = [&](int l) { return (size_t)qh * rh * sizeof(Pair<T>) << l; };
   while (lc > 2 && bytes(lc) > kLdsTarget) --lc;
   // small grids: fewer lines per workgroup (shorter runs of a cache line) until
@@ -300,7 +322,7 @@ hipError_t lines_launch(FastArgs a, int nouter, hipStream_t st) {
   // and 48 us, 127 x 127 x 31 73 and 60, 1023^2 82 and 77
   auto tiles = [&](int cols, int l) { return (cols + (1 << l) - 1) >> l; };
   while (lc > 2 && (long long)(tiles(a.ce, lc) + tiles(a.co, lc)) * nouter < 128) --lc;
-  a.lc = lc;
+  a.lc = (short)lc;
   a.xsplit = tiles(a.ce, lc);
   a.xtiles = a.xsplit + tiles(a.co, lc);
   const int nt = round64(std::max(qh, rh) << lc);
@@ -311,14 +333,36 @@ hipError_t lines_launch(FastArgs a, int nouter, hipStream_t st) {
 }
 
 template <int FAM, int EPI>
-hipError_t rows_launch(FastArgs a, hipStream_t st) {
-  const int qh = a.ax.Q / 2 + 1, rh = a.ax.R / 2 + 1, nb = std::max(qh, rh);
+hipError_t rows_launch(const FastArgs& f, hipStream_t st) {
+  RowArgs a{};
+  a.tw = f.ax.tw;
+  a.in = f.in;
+  a.out = EPI ? f.dense : f.out;
+  a.is1 = f.is1;
+  a.is0 = f.is0;
+  a.s1 = EPI ? f.om * f.ds0 : f.s1;
+  a.s0 = EPI ? f.ds0 : f.s0;
+  a.uscale = f.uscale;
+  a.step = f.step;
+  a.skip = f.skip;
+  a.iys = f.iys;
+  a.ys = EPI ? f.dys : f.ys;
+  a.rows = f.rows;
+  a.oy = f.oy;
+  a.om = f.om;
+  a.inst_mod = f.inst_mod;
+  a.N = (short)f.ax.N;
+  a.Q = (short)f.ax.Q;
+  a.R = (short)f.ax.R;
+  a.off = (short)f.ax.off;
+  a.sub = f.sub != 0;
+  const int qh = a.Q / 2 + 1, rh = a.R / 2 + 1, nb = std::max(qh, rh);
   const size_t per = (size_t)qh * (rh | 1) * sizeof(Pair<T>);
   int lines = 256 / nb;
   lines = std::min<int>(lines, std::max<size_t>(1, kLdsTarget / per));
   // small grids: fewer rows per workgroup (but a whole wave) until every CU has one
   lines = std::min(lines, std::max(std::max(1, 64 / nb), a.rows / 256));
-  a.lines = lines;
+  a.lines = (short)lines;
   constexpr auto kern = k_fast_rows<FAM, EPI>;
   hipError_t e = allow_lds<kern>(per * lines);
   if (e != hipSuccess) return e;

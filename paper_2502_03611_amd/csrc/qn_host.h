@@ -446,11 +446,11 @@ inline void fast_tables(int N, int Q, int R, bool neumann, double ih2, std::vect
 // 4 x 31, 5 x 26).  chain: its length per factored axis, 0 for dense ones.  The
 // lines lie where an iteration takes as long either way, dense and factored:
 //   2D, at most two tiles per axis, both factored: 51^2 (chains of 462 in all)
-//   29.2 and 29.6 us, 45^2 (596) 29.4 and 31.0, 61^2 (1044) 29.3 and 34.5; 86^2
-//   (940) 33.5 and 33.6, 92^2 (1064) 33.6 and 34.6.  Only y, which saves a launch:
+//   29.4 and 29.4 us, 45^2 (596) 29.4 and 31.0, 61^2 (1044) 29.3 and 34.5; 86^2
+//   (940) 33.9 and 33.0, 92^2 (1064) 33.6 and 34.6.  Only y, which saves a launch:
 //   57 x 72 (460) 35.8 and 35.1, 61 x 58 (522) 33.6 and 34.3.  Only x, which saves
 //   none: 100 x 127 (172) 36.8 and 36.8, 100 x 123 (542) 37.2 and 39.1.
-//   3D, one tile per axis: 50^3 (546) 43.2 and 42.9, 37^3 (630) 42.8 and 43.3, 64^3
+//   3D, one tile per axis: 50^3 (546) 43.4 and 42.0, 37^3 (630) 42.8 and 43.3, 64^3
 //   (714) 43.4 and 45.4, 61^3 (1566) 43.4 and 51.2; 61 x 58 x 58 with z alone 47.9
 //   and 45.2; two fields, where the dense launches carry twice the padding: 51^3
 //   (693) 49.4 and 47.4, 64^3 50.7 and 52.8.  One axis of two tiles: 127 x 61 x 31

@@ -32,7 +32,7 @@ const std::string& name_of(const void* f) {
   return it == names.end() ? unknown : it->second;
 }
 
-long long rows_span(const qn::FastArgs& a, bool dense) {
+long long rows_span(const qn::RowArgs& a) {
   auto off = [&](int r, long long s1, long long s0, long long ys) {
     const int pl = r / a.oy;
     return (pl / a.om) * s1 + (pl % a.om) * s0 + (r - pl * (long long)a.oy) * ys;
@@ -41,8 +41,7 @@ long long rows_span(const qn::FastArgs& a, bool dense) {
   for (int r0 = 0; r0 < a.rows; r0 += a.lines) {
     const int r1 = std::min(r0 + a.lines, a.rows) - 1;
     const long long in = off(r1, a.is1, a.is0, a.iys) - off(r0, a.is1, a.is0, a.iys);
-    const long long out = dense ? off(r1, a.om * a.ds0, a.ds0, a.dys) - off(r0, a.om * a.ds0, a.ds0, a.dys)
-                                : off(r1, a.s1, a.s0, a.ys) - off(r0, a.s1, a.s0, a.ys);
+    const long long out = off(r1, a.s1, a.s0, a.ys) - off(r0, a.s1, a.s0, a.ys);
     span = std::max({span, 8 * in, 8 * out});
   }
   return span;
@@ -53,7 +52,9 @@ extern "C" {
 const char* trace_text() { return text.c_str(); }
 void trace_clear() { text.clear(); }
 void trace_device(int d) { device = d; }
-int trace_argument_bytes() { return sizeof(qn::EpiArgs); }
+int trace_argument_bytes(int kind) {
+  return kind == 0 ? sizeof(qn::EpiArgs) : kind == 1 ? sizeof(qn::LineArgs) : sizeof(qn::RowArgs);
+}
 
 void** __hipRegisterFatBinary(const void*) {
   static void* module;
@@ -83,7 +84,7 @@ hipError_t hipLaunchKernel(const void* f, dim3 g, dim3 b, void** args, size_t ld
   const std::string& n = name_of(f);
   long long span = 0;
   if (n.find("k_fast_rows<") != std::string::npos)
-    span = rows_span(*static_cast<const qn::FastArgs*>(args[0]), n.find(", 1>") != std::string::npos);
+    span = rows_span(*static_cast<const qn::RowArgs*>(args[0]));
   char buf[160];
   std::snprintf(buf, sizeof buf, "launch %d %lld %d %zu %lld ", device,
                 (long long)g.x * g.y * g.z, (int)(b.x * b.y * b.z), lds, span);

@@ -56,8 +56,8 @@ def trace(calls, lib=None):
 
 
 def argument_bytes():
-    """Bytes of the struct that every mode-product launch copies."""
-    return ctypes.CDLL(_stand_in()).trace_argument_bytes()
+    """Bytes of the structs that the launches of dense, line and row passes copy."""
+    return [ctypes.CDLL(_stand_in()).trace_argument_bytes(k) for k in range(3)]
 
 
 FORMS = {"k_fast": "F", "k_strip": "S", "k_fold": "T", "k_gemm": "D"}
