@@ -42,20 +42,22 @@ PEAK_HBM_GBS = 8000.0
 # HBM bytes per launch (read, write) from rocprofv3 FETCH_SIZE / WRITE_SIZE at
 # 511^3, the read counter scaled x2.0 and the write counter x1.0 (both
 # calibrated on a plain 1 GiB device copy), keyed by kernel.  Each figure is
-# valid only while the source file it was taken on is unchanged.
-TRAFFIC_SOURCES = {"fast": ("paper_2502_03611_amd/csrc/qn_fast.hip", "52338aaaa8e96554"),
-                   "pointwise": ("paper_2502_03611_amd/csrc/qn_pointwise.hip", "83e7e6dc37950a6a"),
-                   "bf16": ("paper_2502_03611_amd/csrc/qn_gemm_bf16.hip", "d8d0088ec7509d55")}
-TRAFFIC = {"k_fast_rows<0,0>": ("fast", 1.1455e+09, 1.0730e+09),
+# valid only while the source files it was taken on (those that issue the
+# kernel's loads and stores) are unchanged.
+TRAFFIC_SOURCES = {"fast": (("paper_2502_03611_amd/csrc/qn_fast.hip", "paper_2502_03611_amd/csrc/qn_fast.h"),
+                            "deea7fd6615b9b5e"),
+                   "pointwise": (("paper_2502_03611_amd/csrc/qn_pointwise.hip",), "83e7e6dc37950a6a"),
+                   "bf16": (("paper_2502_03611_amd/csrc/qn_gemm_bf16.hip",), "7a6573e2a8a2cbb3")}
+TRAFFIC = {"k_fast_rows<0,0>": ("fast", 1.1359e+09, 1.0729e+09),
            "k_fast_lines<0,0>": ("fast", 1.0700e+09, 1.0696e+09),
            "k_fast_lines<0,1>": ("fast", 1.0704e+09, 1.0696e+09),
-           "k_fast_rows<0,1>": ("fast", 2.2496e+09, 1.1154e+09),
-           "k_residual<QUASILIN,double>": ("pointwise", 2.3817e+09, 1.0696e+09),
-           "k_gemm_right_bf<2,128,128,EPI_STORE,false,2>": ("bf16", 5.6129e+08, 7.5414e+08),
-           "k_gemm_left_bf<2,128,128,EPI_STORE,false,2>": ("bf16", 5.5573e+08, 5.3800e+08),
-           "k_gemm_left_bf<2,128,128,EPI_DIVIDE,false,1>": ("bf16", 5.6513e+08, 5.3688e+08),
-           "k_gemm_left_bf<2,128,128,EPI_STORE,true,0>": ("bf16", 5.7200e+08, 5.3692e+08),
-           "k_gemm_right_bf<2,128,128,EPI_SUB_DENSE,true,0>": ("bf16", 1.6666e+09, 1.0954e+09)}
+           "k_fast_rows<0,1>": ("fast", 2.2392e+09, 1.1017e+09),
+           "k_residual<QUASILIN,double>": ("pointwise", 2.4003e+09, 1.0696e+09),
+           "k_gemm_right_bf<2,128,128,EPI_STORE,false,2>": ("bf16", 5.6402e+08, 7.2304e+08),
+           "k_gemm_left_bf<2,128,128,EPI_STORE,false,2>": ("bf16", 5.5412e+08, 5.3795e+08),
+           "k_gemm_left_bf<2,128,128,EPI_DIVIDE,false,1>": ("bf16", 5.6580e+08, 5.3688e+08),
+           "k_gemm_left_bf<2,128,128,EPI_STORE,true,0>": ("bf16", 5.7408e+08, 5.3692e+08),
+           "k_gemm_right_bf<2,64,128,EPI_SUB_DENSE,true,0>": ("bf16", 1.6760e+09, 1.1237e+09)}
 
 
 def traffic_if_current(kernel, n):
@@ -66,10 +68,12 @@ def traffic_if_current(kernel, n):
     if n != 511 or kernel not in TRAFFIC:
         return None
     src, rd, wr = TRAFFIC[kernel]
-    path, sha_ref = TRAFFIC_SOURCES[src]
-    with open(os.path.join(ROOT, path), "rb") as fh:
-        sha = hashlib.sha256(fh.read()).hexdigest()[:16]
-    return rd + wr if sha == sha_ref else None
+    paths, sha_ref = TRAFFIC_SOURCES[src]
+    sha = hashlib.sha256()
+    for path in paths:
+        with open(os.path.join(ROOT, path), "rb") as fh:
+            sha.update(fh.read())
+    return rd + wr if sha.hexdigest()[:16] == sha_ref else None
 
 
 def stream_reference(n):
