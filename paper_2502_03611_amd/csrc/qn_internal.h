@@ -432,7 +432,6 @@ inline int transform_storage(int prec) {
 // residual's xfold output.
 hipError_t launch_pad_copy(const double* src, void* dst, int out_prec, int ncomp, int nx, int ny,
                            int nz, int px, int py, int pz, hipStream_t st, int xfold = 0);
-// Write {scale, beta} into a device slot.
 // Fill n bytes with zero (a kernel, not a memset node).
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t st);
 

@@ -330,7 +330,8 @@ constexpr int DS = 48;                         // LDS pixel stride of its tiles 
 // workgroup leaves the chip (one per tile: 151 MB per layer at 16 images of
 // 255^2).  Two wave groups take the two halves of a tile's pixels, so every
 // SIMD holds two waves; wave w of a group owns row block w&1 and column
-// blocks (w>>1) + 2i.  16 x 255^2: 0.47 -> 0.26 ms.
+// blocks (w>>1) + 2i.  16 x 255^2: 0.47 -> 0.216 ms (0.26 with offsets computed at
+// run time and rows 36 apart).
 constexpr int WG_THREADS = 512;
 __global__ __launch_bounds__(WG_THREADS) void k_conv32_wgrad(const float* __restrict__ act,
                                                              const float* __restrict__ dz,
