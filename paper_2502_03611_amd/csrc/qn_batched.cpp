@@ -488,7 +488,7 @@ qn_status qnb_setup_ex(int32_t count, const int32_t* n, const int32_t* ncomp, in
     k.fx.off = foff;
     k.fast = precision == QN_PREC_FP64 && k.fx.N >= 16 && fast_stages(k.fx.N, &k.fx.Q, &k.fx.R) &&
              fast_pays_batched(k.n, fast_work(k.fx.Q) + fast_work(k.fx.R),
-                               (double)k.ncomp * k.K * k.n * k.n);
+                               (double)k.ncomp * k.K);
     if (k.fast) {  // modes in order; no dense operand
       fast_tables(k.fx.N, k.fx.Q, k.fx.R, foff == 0, k.ih2, k.htw, k.hlx);
       k.hlam.assign((size_t)k.p, k.hlx[k.fx.N - 1]);

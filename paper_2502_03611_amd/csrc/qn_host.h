@@ -444,17 +444,20 @@ inline void fast_tables(int N, int Q, int R, bool neumann, double ih2, std::vect
 // of work(Q) + work(R) multiply-adds; where a dense product is a single launch of
 // few tiles, that chain is the longer one for prime-like stages (4 x 23, 4 x 29,
 // 4 x 31, 5 x 26).  chain: its length per factored axis, 0 for dense ones.  The
-// lines lie where an iteration takes as long either way, dense and factored:
-//   2D, at most two tiles per axis, both factored: 51^2 (chains of 462 in all)
-//   29.4 and 29.4 us, 45^2 (596) 29.4 and 31.0, 61^2 (1044) 29.3 and 34.5; 86^2
-//   (940) 33.9 and 33.0, 92^2 (1064) 33.6 and 34.6.  Only y, which saves a launch:
-//   57 x 72 (460) 35.8 and 35.1, 61 x 58 (522) 33.6 and 34.3.  Only x, which saves
-//   none: 100 x 127 (172) 36.8 and 36.8, 100 x 123 (542) 37.2 and 39.1.
-//   3D, one tile per axis: 50^3 (546) 43.4 and 42.0, 37^3 (630) 42.8 and 43.3, 64^3
-//   (714) 43.4 and 45.4, 61^3 (1566) 43.4 and 51.2; 61 x 58 x 58 with z alone 47.9
-//   and 45.2; two fields, where the dense launches carry twice the padding: 51^3
-//   (693) 49.4 and 47.4, 64^3 50.7 and 52.8.  One axis of two tiles: 127 x 61 x 31
-//   (754) 52.6 and 48.4, 127 x 61 x 61 (1216) 54.5 and 56.5.
+// lines lie where an iteration bound by the GPU takes as long either way (us,
+// dense and factored; where the host bounds the launches a factored solve saves
+// one more of them, 45^2 33 and 33):
+//   2D, at most two tiles per axis, both factored: 57 x 63 (chains of 576 in all)
+//   29.2 and 29.3, 45^2 (596) 29.2 and 30.0, 61^2 (1044) 29.4 and 33.4; 92^2 (1064)
+//   34.0 and 34.1.  Only y, which saves a launch: 57 x 72 (460) 33.1 and 33.0, 61 x 58
+//   (522) 29.4 and 30.5.  Only x, which saves none: 100 x 127 (172) 33.9 and 32.0, 100 x
+//   123 (542) 34.0 and 34.4, a solve 20.4 and 22.6.
+//   3D, one tile per axis: 51^3 (693) 43.4 and 43.7, 64^3 (714) 43.5 and 44.6, 61 x 63 x
+//   63 (754) 43.7 and 45.1, 57^3 (1380) 43.5 and 49.0; 61 x 58 x 58 with z alone 47.9 and
+//   45.2, two factored axes have two thirds of the limit (61 x 61 x 58, 1044: 43.5 and
+//   45.8; 63 x 63 x 58, 232: 47.6 and 45.9); two fields, where the dense launches carry twice the padding: 45^3 (894)
+//   46.6 and 46.4, 64^3 51.0 and 52.0.  One axis of two tiles: 127 x 61 x 31 (754) 52.6
+//   and 48.4, 127 x 61 x 61 (1216) 53.4 and 54.7.
 inline bool fast_pays(int dim, const int* n, const int* p, const double* chain, int fields) {
   double sum = 0.0, values = 1.0, padded = 1.0;
   int count = 0, tiles = 0, most = 0, sides = 0;
@@ -468,22 +471,21 @@ inline bool fast_pays(int dim, const int* n, const int* p, const double* chain, 
     if (chain[a] > 0.0) sides += p[a];
   }
   if (count == 0 || most > 128 || tiles > 4) return true;
-  if (dim == 2) {
-    if (count == 2) return sum <= 3.75 * sides;
-    return chain[1] > 0.0 && sum <= 7.3 * sides;
-  }
+  if (dim == 2) return sum <= (count == 2 ? 4.55 : chain[1] > 0.0 ? 7.3 : 3.0) * sides;
   if (count == 1) return true;
   if (fields > 1) sum *= values / padded;
-  return sum <= (tiles == 3 ? 600.0 : 1024.0);
+  return sum <= (tiles == 3 ? 700.0 : 1024.0) * count / 3.0;
 }
 
-// The same for the classes of a batch, n^2 points an instance and `values` in
-// all, which fill the chip: the factored passes' arithmetic counts, over n^2
-// points of the 64^2 that a dense tile pads to.  61^2 (chain of 522) x 1127
-// instances 196 us an iteration dense and 243 factored, x 70 57 and 56; 64^2 (238)
-// x 1024 177 and 194; 56^2 (220) x 1337 223 and 226, 62^2 (148) x 1091 193 and 193.
-inline bool fast_pays_batched(int n, double chain, double values) {
-  return n > 64 || values < 262144.0 || chain * n * n <= 180.0 * 4096.0;
+// The same for the classes of a batch, `planes` fields of n^2 points in all.  While
+// a line pass is one round of workgroups with room to spare (two per CU, 16 lines
+// each) it is a launch that its chain is part of: 61^2 (chain of 522) x 80 instances
+// 50 us an iteration both ways, 64^2 (238) x 100 52 and 49.  Beyond, the factored
+// passes' arithmetic counts, over n^2 points of the 64^2 that a dense tile pads to:
+// 61^2 x 128 51 dense and 54 factored, x 1127 196 and 243, 64^2 x 180 57 and 64; 56^2
+// (220) x 1024 155 and 162, 62^2 (148) x 1091 193 and 193.
+inline bool fast_pays_batched(int n, double chain, double planes) {
+  return n > 64 || planes * ((n + 15) / 16) <= 448.0 || chain * n * n <= 165.0 * 4096.0;
 }
 
 // Whether the dense products of a solve take the strip form (qn_gemm_strip.h):

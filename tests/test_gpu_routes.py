@@ -133,3 +133,29 @@ def test_every_fp64_tile_of_dense_axes_gives_the_same_bits(shape, sem):
     s.iterate(u, f, rtol=0.0, max_iter=3)
     Solver(shape, "cubic", beta=1.0, **opt).iterate(v, f, rtol=0.0, max_iter=3)
     assert torch.equal(u, v) and torch.equal(s.fdm_solve(f, 1.5, 0.25), want)
+
+
+@pytest.mark.parametrize("shape,prec", [
+    ((95, 1023), "fp64"), ((15, 1023, 31), "fp64"), ((511, 511, 31), "fp64"),  # more than 64 KB of LDS
+    ((66, 134, 229), "fp32"), ((63, 106), "fp64"), ((63, 63, 63), "bf16x3"),
+])
+def test_a_first_solve_can_be_captured(shape, prec):
+    """A solver's first solve, in a graph: the limits that its kernels need are
+    raised outside the stream; replays on new inputs equal eager solves."""
+    print(f"capture {shape} {prec}", flush=True)
+    s, e = (Solver(shape, "cubic", beta=1.0, precision=prec) for _ in range(2))
+    R = torch.from_numpy(synth.random_field((1,) + shape, 5)).cuda()
+    X = torch.empty_like(R)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side), torch.cuda.graph(graph, stream=side):
+        s.fdm_solve(R, 1.1, 0.7, X=X)
+    torch.cuda.synchronize()
+    for i in range(3):
+        R.mul_(0.5 - i)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(X, e.fdm_solve(R, 1.1, 0.7)), i
+        torch.cuda.synchronize()

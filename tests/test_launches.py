@@ -77,15 +77,16 @@ def test_pinned_tiles_keep_the_residual_launch(call):
 
 @pytest.mark.parametrize("shape,kw,want", [
     # prime-like stage lengths (chains of many multiply-adds) on grids of few tiles: dense
-    ((61, 61), {}, "TTTT"), ((57, 63), {}, "TTTT"), ((45, 45), {}, "TTTT"), ((123, 123), {}, "TTTT"),
-    ((59, 59), {"boundary": "neumann"}, "TTTT"), ((61, 58), {}, "TTTT"), ((100, 123), {}, "TTTT"),
-    ((100, 127), {}, "TTTT"),
+    ((61, 61), {}, "TTTT"), ((57, 57), {}, "TTTT"), ((45, 45), {}, "TTTT"), ((61, 58), {}, "TTTT"),
+    ((59, 59), {"boundary": "neumann"}, "TTTT"), ((100, 123), {}, "TTTT"),
     ((57, 57, 57), {}, "TTTTTT"), ((64, 64, 64), {}, "TTTTTT"), ((61, 63, 63), {}, "TTTTTT"),
     ((61, 61, 58), {}, "TTTTTT"), ((127, 61, 61), {}, "TTTTTT"), ((64, 64, 64), {"problem": "system"}, "TTTTTT"),
     # short chains, longer axes or a second field: factored
-    ((63, 63), {}, "FFF"), ((51, 51), {}, "FFF"), ((86, 86), {}, "FFF"), ((61, 511), {}, "FFF"), ((31, 17), {}, "FFF"),
-    ((63, 58), {}, "TFT"), ((127, 100), {}, "TFT"), ((100, 255), {}, "FTTF"), ((1023, 33), {}, "FFF"),
-    ((63, 63, 63), {}, "FFFFF"), ((15, 15, 15), {}, "FFFFF"), ((51, 51, 51), {"problem": "system"}, "FFFFF"),
+    ((63, 63), {}, "FFF"), ((51, 51), {}, "FFF"), ((57, 63), {}, "FFF"), ((92, 92), {}, "FFF"), ((123, 123), {}, "FFF"),
+    ((61, 511), {}, "FFF"), ((31, 17), {}, "FFF"), ((1023, 33), {}, "FFF"),
+    ((63, 58), {}, "TFT"), ((127, 100), {}, "TFT"), ((100, 127), {}, "FTTF"), ((100, 255), {}, "FTTF"),
+    ((63, 63, 63), {}, "FFFFF"), ((15, 15, 15), {}, "FFFFF"), ((51, 51, 51), {}, "FFFFF"),
+    ((45, 45, 45), {"problem": "system"}, "FFFFF"),
     ((61, 58, 58), {}, "TTFTT"), ((31, 31, 123), {}, "FFFFF"), ((61, 127, 127), {}, "FFFFF"), ((61, 255, 255), {}, "FFFFF"),
 ])
 def test_factored_axes_of_small_grids(shape, kw, want):
@@ -94,9 +95,10 @@ def test_factored_axes_of_small_grids(shape, kw, want):
 
 
 def test_factored_classes_of_batches():
-    sizes = [61] * 300 + [57] * 20 + [63] * 700 + [127] * 40
-    rows, = trace([{"sizes": sizes, "ncomp": [1] * len(sizes), "precision": "fp64"}])
-    assert sorted(forms(rows)) == sorted("TTTT" + "FFF" + "FFF" + "FFF")
+    for n, count, want in ((61, 300, "TTTT"), (61, 100, "FFF"), (57, 160, "TTTT"), (64, 112, "FFF"), (64, 113, "TTTT"),
+                           (56, 1024, "TTTT"), (54, 1024, "FFF"), (63, 700, "FFF"), (127, 40, "FFF")):
+        rows, = trace([{"sizes": [n] * count, "ncomp": [1] * count, "precision": "fp64"}])
+        assert forms(rows) == want, (n, count)
 
 
 @pytest.mark.parametrize("shape,problem,want", [
